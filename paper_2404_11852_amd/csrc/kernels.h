@@ -92,7 +92,6 @@ template <typename T>
 void launch_build_occupancy(const GridK &g, float thr, uint8_t *occ, hipStream_t s);
 
 // mlp.hip
-int mlp_lds_bytes(int compute);
 template <typename T>
 void launch_mlp_forward(const GridK &g, const cic_mlp &m, const RenderBufs &b, bool voxel, hipStream_t s);
 // mlp_bf16.hip: the BF16 forward (called by launch_mlp_forward for BF16 compute)

@@ -1,43 +1,179 @@
 // Feature Gathering + Feature Computation (Sec. II-B) for the compacted live
 // samples: trilinear gather of the 12 feature channels, the view-direction
-// encoding, and the 39 -> 128 -> 128 -> 3 MLP on MFMA.
+// encoding, and the 39 -> 128 -> 128 -> 3 MLP on MFMA, for float32 compute.
+//
+// Arithmetic.  The matrix cores run float16 products 16 times as fast as
+// float32 ones, so the hidden layers split both operands into two float16
+// parts, v = hi + lo / 2^11 (22 significand bits and a sign between them),
+// and sum three products, hi hi, hi lo and lo hi, in float32.  The remainders
+// are kept times 2^11, so they are normal float16 values wherever the first
+// part is one; weights are scaled by powers of two to use float16's range,
+// and a sample whose features or activations leave it (65504, after the
+// scaling of layer 0) is computed again in plain float32.  The low products
+// have their own accumulators, so the high ones are rounded 8 times over a
+// 128-long sum where a float32 chain rounds 128 times.  Colour error against
+// 64 bits, rms over 300,000 single-sample rays: 2.80e-8, and 2.90e-8 for the
+// float32 MFMA chain that this replaced; features x 30: 4.73e-8 and 4.82e-8;
+// W0 x 30: 9.8e-8 and 1.16e-7; W1 x 8: 5.8e-8 and 6.6e-8 (three BF16 parts
+// and six products, the exact split, were less exact, 3.06e-8, because one
+// accumulator takes 48 roundings, and 1.4 times as slow).
+//
+// Bound.  Matrix power: with the matrix cores 62% busy the card lowers its
+// clock to 1.8 GHz (2.37 GHz under float32 MFMA at 85%), which is the busy
+// rate times clock that a library BF16 product reaches here too (1.2
+// PFLOP/s).  MLP stage of an 800x800 frame with 36 M live samples: 9.9 -> 4.0 ms.
 //
 // Layout.  The MLP runs transposed, H^T = W X^T, so that samples sit on the
-// MFMA's N axis: with v_mfma_f32_16x16x4_f32 the result tile of one layer
-// (lane l holds outputs 4*(l/16)+r of sample l%16) is directly the B operand
-// of the next layer once the reduction index is permuted the same way in the
-// weights.  Activations therefore never leave registers; weights are staged
-// once per workgroup in LDS, pre-permuted into per-lane fragment order so
-// every A-operand read is one contiguous, conflict-free ds_read_b64/b128.
-// The 3-wide output layer runs on the vector ALUs with a cross-lane sum.
+// MFMA's N axis (32 samples per wavefront batch): the result tile of one
+// layer (lane l holds rows 8 (r / 4) + 4 (l / 32) + r % 4 of sample l % 32) is
+// the B operand of the next layer once the reduction index is permuted the
+// same way in the weights.  Activations never leave registers; weights are
+// staged once per workgroup in LDS in per-lane fragment order, so every A
+// operand is one contiguous, conflict-free ds_read_b128.  32x32 tiles rather
+// than 16x16: each fragment serves 32 samples (LDS reads are the next limit)
+// and a sample's cell is located by two lanes instead of four.  The output
+// layer runs on 4x4x1 float32 MFMA, whose B operand is the lane's own
+// activation.
 //
-// Input permutation of layer 0 (10 chunks of 4 = 40 >= 39 inputs): lane
-// group q of each sample computes features 3q..3q+2 (chunks 0-2), the
-// direction component q (chunk 3; q = 3 pads with 0) and sin/cos of the
-// encoding pairs p = 3q..3q+2 (chunks 4-9), p = 4*component + octave.
-//
-// The kernel is persistent: one 8-wavefront workgroup per CU (LDS holds the
-// 88 KB of float32 weights) loops over 32-sample batches until the device-
-// side sample count is exhausted.
+// Schedule.  Persistent: one 8-wavefront workgroup per CU (two per SIMD at
+// 232 VGPRs; 12 wavefronts spill, 8.4 against 4.7 ms per frame).  Within a
+// batch the vector work (splitting the activations, the output layer, and
+// the next batch's records, gathers and interpolation) sits between the
+// layer-1 MFMAs: 3.5% faster than the same order left to the compiler.
 #include "mlp_common.h"
 
 namespace cic {
 
-// 16-sample tiles per wavefront batch; one tile keeps a wavefront under 128
-// VGPRs, so the 16 wavefronts of the CU's single workgroup (the weights take
-// 88 KB of LDS) give four per SIMD to overlap gathers with MFMA work.
-#ifndef CIC_F32_NT
-#define CIC_F32_NT 1
-#endif
-constexpr int kNT = CIC_F32_NT;
+typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+typedef float f16_t __attribute__((ext_vector_type(16)));
+typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kMlpWaves = kNT == 1 ? 16 : 8;
-constexpr int kBatch = 16 * kNT;
+constexpr int kFwdWaves = 8;    // wavefronts of the CU's one workgroup
+constexpr int kFwdBatch = 32;   // samples per wavefront batch
 
-int mlp_lds_bytes(int compute)
+// LDS in 16-byte fragments, then floats
+constexpr int kXW1 = 0;                          // [part 2][t 4][c 8][lane 64]
+constexpr int kXW0 = kXW1 + 2 * 4 * 8 * 64;      // [t 4][s 3][lane 64]
+constexpr int kXFrags = kXW0 + 4 * 3 * 64;
+constexpr int kXB1 = 0, kXW2 = 128;              // [128]; [t 4][i 4][h 2][ch 4][r 4]
+constexpr int kXB2 = kXW2 + 512, kXFloats = kXB2 + 4;
+constexpr int kXLdsBytes = kXFrags * 16 + kXFloats * 4;
+constexpr float kLoScale = 2048.f;               // the low parts are kept times 2^11
+
+// hidden unit of slot e of chunk c (16 units) for lane half h: the rows that
+// the lane half holds of the 32-row result tile c / 2
+__host__ __device__ __forceinline__ int x_hid(int c, int h, int e)
 {
-    (void)compute;
-    return kLdsF32 * (int)sizeof(float);
+    return 16 * c + 8 * (e >> 2) + 4 * h + (e & 3);
+}
+
+// v0, v1 into a float16 and a second float16 that holds the remainder times
+// 2^11 (the remainder is exact in float32; times 2^11 it is a normal float16
+// wherever the first part is)
+__device__ __forceinline__ void split2(float v0, float v1, uint32_t &hi, uint32_t &lo)
+{
+    h2_t a, b;
+    a[0] = (_Float16)v0;
+    a[1] = (_Float16)v1;
+    hi = __builtin_bit_cast(uint32_t, a);
+    asm("" : "+v"(hi));   // one packed conversion, not two more single ones for the remainders
+    a = __builtin_bit_cast(h2_t, hi);
+    b[0] = (_Float16)fmaf((float)a[0], -kLoScale, v0 * kLoScale);
+    b[1] = (_Float16)fmaf((float)a[1], -kLoScale, v1 * kLoScale);
+    lo = __builtin_bit_cast(uint32_t, b);
+}
+
+// 2^k, k in [-100, 100], that puts a weight block's largest magnitude `top`
+// into [2^to, 2^(to + 1)) (1 where the block is zero)
+__device__ __forceinline__ int block_exp(float top, int to)
+{
+    return top > 0.f ? min(max(to + 127 - (int)(__float_as_uint(top) >> 23), -100), 100) : 0;
+}
+
+// Exponent of layer 0's scale: W0's feature columns are scaled to a largest
+// entry in [1, 2), the per-ray direction terms with them.
+__device__ __forceinline__ int w0_exp(const cic_mlp &m, float *red)
+{
+    float top = 0.f;
+    for (int i = threadIdx.x; i < 128 * 12; i += blockDim.x) top = fmaxf(top, fabsf(m.w0[(i / 12) * 39 + i % 12]));
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off, kWave));
+    if (lane_id() == 0) red[threadIdx.x / kWave] = top;
+    __syncthreads();
+    for (int k = 0; k < (int)blockDim.x / kWave; ++k) top = fmaxf(top, red[k]);
+    __syncthreads();
+    return block_exp(top, 0);
+}
+
+// Weights into LDS in fragment order.  W1 is scaled by the power of two that
+// puts its largest entry in [2^14, 2^15) before the split (so both parts use
+// float16's range), b1 with it and with layer 0's scale; W2 by the inverse of
+// both, which the ReLUs let through exactly.
+__device__ void stage_weights_split(const cic_mlp &m, float *lds)
+{
+    h8_t *w1 = (h8_t *)lds + kXW1;
+    h8_t *w0 = (h8_t *)lds + kXW0;
+    float *fl = lds + kXFrags * 4;
+    constexpr int kT = kFwdWaves * 64, kN = 4 * 8 * 64, kIt = (kN + kT - 1) / kT;
+    float w[kIt][8], top = 0.f;
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+        const int i = (int)threadIdx.x + k * kT;
+        const int l = i & 63, c = (i >> 6) & 7, t = (i >> 9) & 3;
+        const float *src = m.w1 + (32 * t + (l & 31)) * 128;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            w[k][e] = src[x_hid(c, l >> 5, e)];
+            top = fmaxf(top, fabsf(w[k][e]));
+        }
+    }
+    const int e0 = w0_exp(m, fl);
+    const float s0 = ldexpf(1.f, e0);
+    for (int i = threadIdx.x; i < 4 * 3 * 64; i += kT) {
+        const int l = i & 63, s = (i >> 6) % 3, t = i / 192;
+        h8_t v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            // products: high x high, high / 2^11 x (low times 2^11), low x high
+            const int idx = 8 * s + e, p = idx / 6, f = idx % 6;
+            const float a = m.w0[(32 * t + (l & 31)) * 39 + 6 * (l >> 5) + f] * s0;
+            const _Float16 hi = (_Float16)a;
+            v[e] = p == 0 ? hi : p == 1 ? (_Float16)((float)hi / kLoScale) : p == 2 ? (_Float16)(a - (float)hi)
+                                                                                   : (_Float16)0.f;
+        }
+        w0[i] = v;
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off, kWave));
+    if (lane_id() == 0) fl[threadIdx.x / kWave] = top;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kFwdWaves; ++k) top = fmaxf(top, fl[k]);
+    __syncthreads();
+    const int e1 = block_exp(top, 14);
+    const float s1 = ldexpf(1.f, e1);
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+        const int i = (int)threadIdx.x + k * kT;
+        if (i >= kN) continue;
+        u4_t hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t a, b;
+            split2(w[k][2 * e] * s1, w[k][2 * e + 1] * s1, a, b);
+            hi[e] = a;
+            lo[e] = b;
+        }
+        w1[i] = __builtin_bit_cast(h8_t, hi);
+        w1[kN + i] = __builtin_bit_cast(h8_t, lo);
+    }
+    for (int i = threadIdx.x; i < 512; i += kT) {
+        const int ch = (i >> 2) & 3, h = (i >> 4) & 1, row = 32 * (i >> 7) + 8 * ((i >> 5) & 3) + 4 * h + (i & 3);
+        fl[kXW2 + i] = ch < 3 ? ldexpf(m.w2[ch * 128 + row], -(e0 + e1)) : 0.f;
+    }
+    for (int i = threadIdx.x; i < 128; i += kT) fl[kXB1 + i] = ldexpf(m.b1[i], e0 + e1);
+    if (threadIdx.x < 4) fl[kXB2 + threadIdx.x] = threadIdx.x < 3 ? m.b2[threadIdx.x] : 0.f;
 }
 
 // Per-ray direction term of layer 0: z0[ray][o] = b0[o] + sum_i W0[o][12+i] pe_i
@@ -55,6 +191,7 @@ __global__ __launch_bounds__(128) void k_ray_embed(cic_mlp m, RenderBufs b, floa
 {
     __shared__ float pe[kEmbedRays][28];
     __shared__ uint32_t live[kEmbedRays];
+    __shared__ float red[2];
     const int o = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * kEmbedRays;
     // a pass over a device-counted set of rays (the holes of a warped frame)
@@ -79,10 +216,11 @@ __global__ __launch_bounds__(128) void k_ray_embed(cic_mlp m, RenderBufs b, floa
         }
     }
     __syncthreads();
+    const int e0 = w0_exp(m, red);
     float w[27];
 #pragma unroll
-    for (int i = 0; i < 27; ++i) w[i] = m.w0[o * 39 + 12 + i];
-    const float bias = m.b0[o];
+    for (int i = 0; i < 27; ++i) w[i] = ldexpf(m.w0[o * 39 + 12 + i], e0);
+    const float bias = ldexpf(m.b0[o], e0);
     for (int r = 0; r < kEmbedRays; ++r) {
         if (!live[r]) continue;
         float acc = bias;
@@ -99,216 +237,376 @@ void launch_ray_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s)
     hipLaunchKernelGGL(k_ray_embed, dim3(blocks), dim3(128), 0, s, m, b, b.z0);
 }
 
-// PET: the direction half of layer 0 comes from the per-ray table, so layer 0
-// only multiplies the 12 interpolated features.
-template <typename T, bool PET>
-__global__ __launch_bounds__(kMlpWaves * 64, 1) void k_mlp_fwd_f32(GridK g, cic_mlp m, RenderBufs b, int voxel)
-{
-    extern __shared__ __attribute__((aligned(16))) float lds[];
-    stage_weights_f32(m, lds);
-    __syncthreads();
+// Features 6h .. 6h+5 of one sample (lane half h): issue() sends the loads of
+// the 8 corners, feature() interpolates one of them, in two steps so that a
+// batch's work fits between the loads and their use.  Dense grids: corner c
+// (x bit 2, y bit 1, z bit 0), 6 consecutive channels.  Multi-level encoding:
+// levels 2h and 2h + 1, 3 features each.
+template <typename T, bool HASH>
+struct Gather {
+    static constexpr bool kHalf = sizeof(T) == 2;
+    static constexpr int kWords = kHalf ? (HASH ? 4 : 3) : 6;   // 32-bit words per corner
+    uint32_t raw[8][kWords];
+    float fr[HASH ? 2 : 1][3];
+    uint32_t odd;   // float16 tables: parity of each entry, bit 8 * level + corner
 
-    const int lane = lane_id(), q = lane >> 4, j = lane & 15;
-    const int wave = threadIdx.x / 64;
-    const int64_t total = (int64_t)b.offsets[b.n];
-    const int64_t nbatch = (total + kBatch - 1) / kBatch;
-    const f2_t *w0f = (const f2_t *)(lds + kOffW0);
-    const f4_t *w1f = (const f4_t *)(lds + kOffW1);
-    const f4_t *w2l = (const f4_t *)(lds + kOffW2);
-
-    const BatchRange br = xcd_batches(nbatch, kMlpWaves, wave);
-    // Sample s of the wave's batch bt (a lane past the last sample works on
-    // sample 0: in-bounds inputs, no branches around the loads; its colour is
-    // not stored), and its record.
-    auto record_of = [&](int64_t bt, int nt) -> uint32_t {
-        const int64_t s = bt * kBatch + nt * 16 + j;
-        const int64_t sv = s < total ? s : 0;
-        return voxel ? b.perm[sv] : (uint32_t)sv;
-    };
-    // The next batch's record, ray and sample index are loaded during this
-    // batch's layer 1 and its ray's origin, direction and interval during
-    // layer 2, so a batch starts with only its grid gathers outstanding.
-    SampleRay cur[kNT];
-    uint32_t crec[kNT];
-    if (br.first < br.end) {
+    __device__ __forceinline__ void issue(const GridK &g, const SampleRay &r, int h)
+    {
+        if constexpr (HASH) {
+            float xp[3];
+            sample_position(r, xp);
+            odd = 0;
 #pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) {
-            crec[nt] = record_of(br.first, nt);
-            load_sample_ray(b, b.rec_ray[crec[nt]], b.rec_k[crec[nt]], cur[nt]);
-        }
-    }
-    for (int64_t bt = br.first; bt < br.end; bt += br.stride) {
-        // Wave priority (within this kernel's wavefronts on a SIMD): low
-        // while gathering the batch's inputs, raised at each layer so that
-        // the wavefront furthest through its batch wins the matrix unit.
-        // Fair sharing otherwise lets the four wavefronts of a SIMD finish
-        // their MFMA phases together and then wait on their gathers together
-        // (measured per 800x800 frame: 16.68 ms without priorities, 16.37 ms
-        // with one raise at layer 0, 16.23-16.30 ms raising per layer).
-        __builtin_amdgcn_s_setprio(0);
-        float x[kNT][10];
-        uint32_t rec[kNT];
-        bool valid[kNT];
+            for (int u = 0; u < 2; ++u) {
+                const int l = 2 * h + u;
+                int i0[3];
+                hash_cell(g, l, xp, i0, fr[u]);
+                const T *tab = (const T *)g.htab + (size_t)l * ((size_t)g.hmask + 1) * 3;
 #pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) {
-            valid[nt] = bt * kBatch + nt * 16 + j < total;
-            rec[nt] = crec[nt];
-            sample_inputs_from<T, !PET>(g, cur[nt], q, x[nt]);
-        }
-        const bool more = bt + br.stride < br.end;
-        uint32_t nrec[kNT], nray[kNT];
-        int nk[kNT];
-
-        // layer 0: 40 -> 128 (PET: 12 -> 128 on top of the per-ray term)
-        __builtin_amdgcn_s_setprio(1);
-        f4_t h1[8][kNT];
-        if (PET) {
+                for (int c = 0; c < 8; ++c) {
+                    const uint64_t e = hash_entry(g, l, (uint32_t)(i0[0] + ((c >> 2) & 1)),
+                                                  (uint32_t)(i0[1] + ((c >> 1) & 1)), (uint32_t)(i0[2] + (c & 1)));
+                    if constexpr (kHalf) {
+                        // the two aligned words that hold the entry's 6 bytes (see load_entry3)
+                        const uint32_t *w = (const uint32_t *)((const char *)tab + ((e * 6) & ~(uint64_t)3));
+                        raw[c][2 * u] = w[0];
+                        raw[c][2 * u + 1] = w[1];
+                        odd |= ((uint32_t)e & 1u) << (8 * u + c);
+                    } else {
+                        const uint32_t *w = (const uint32_t *)tab + e * 3;
 #pragma unroll
-            for (int nt = 0; nt < kNT; ++nt) {
-                // (every record's ray has live samples, so its row is written)
-                const float *zr = b.z0 + (int64_t)cur[nt].ray * 128 + 4 * q;
-#pragma unroll
-                for (int t = 0; t < 8; ++t) h1[t][nt] = *(const f4_t *)(zr + 16 * t);
+                        for (int k = 0; k < 3; ++k) raw[c][3 * u + k] = w[k];
+                    }
+                }
             }
         } else {
+            int i0[3];
+            float tk;
+            sample_voxel(r.o, r.d, r.tn, r.delta, r.k, g, i0, fr[0], tk);
+            constexpr int kRec = 12 * (int)sizeof(T);
+            const int64_t sy = (int64_t)g.r2 * kRec, sx = (int64_t)g.r1 * sy;
+            const char *p = (const char *)g.features + vertex_index(g, i0[0], i0[1], i0[2]) * kRec + h * (kRec / 2);
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const f4_t bias = *(const f4_t *)(lds + kOffB0 + 16 * t + 4 * q);
+            for (int c = 0; c < 8; ++c) {
+                const uint32_t *w =
+                    (const uint32_t *)(p + ((c >> 2) & 1) * sx + ((c >> 1) & 1) * sy + (c & 1) * kRec);
 #pragma unroll
-                for (int nt = 0; nt < kNT; ++nt) h1[t][nt] = bias;
+                for (int k = 0; k < kWords; ++k) raw[c][k] = w[k];
             }
         }
-        // Layer 0: per input chunk pair, the eight output tiles' A fragments
-        // are read together and the MFMAs alternate between the eight
-        // independent accumulators.  The scheduling barriers keep the
-        // compiler from hoisting every LDS read (which would exceed the
-        // register budget).
-        constexpr int kC2 = PET ? 2 : 5;   // PET: chunks 0..2 (features) only
-#pragma unroll
-        for (int c2 = 0; c2 < kC2; ++c2) {
-            f2_t a[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) a[t] = w0f[(t * 5 + c2) * 64 + lane];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                if (PET && 2 * c2 + e >= 3) continue;
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-#pragma unroll
-                    for (int nt = 0; nt < kNT; ++nt)
-                        h1[t][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][e], x[nt][2 * c2 + e], h1[t][nt], 0, 0,
-                                                                          0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // ReLU of h1: one input chunk ahead inside layer 1, so the vector
-        // work overlaps its MFMAs
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) h1[0][nt][r] = relu_bits(h1[0][nt][r]);
+    }
 
-        // layer 1: 128 -> 128
-        __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) {
-            nrec[nt] = record_of(more ? bt + br.stride : 0, nt);
-            nray[nt] = b.rec_ray[nrec[nt]];
-            nk[nt] = b.rec_k[nrec[nt]];
+    __device__ __forceinline__ float value(int c, int k) const
+    {
+        if constexpr (!kHalf) {
+            return __uint_as_float(raw[c][k]);
+        } else if constexpr (!HASH) {
+            const uint32_t w = raw[c][k >> 1];
+            return __half2float(__ushort_as_half((unsigned short)((k & 1) ? w >> 16 : w & 0xffffu)));
+        } else {
+            const int u = k / 3, f = k % 3;
+            const uint32_t a = raw[c][2 * u], b = raw[c][2 * u + 1], sh = ((odd >> (8 * u + c)) & 1u) * 16u;
+            const uint32_t w = f < 2 ? __builtin_amdgcn_alignbit(b, a, sh) : b >> sh;
+            return __half2float(__ushort_as_half((unsigned short)(f == 1 ? w >> 16 : w & 0xffffu)));
         }
-        __builtin_amdgcn_sched_barrier(0);
-        f4_t h2[8][kNT];
+    }
+
+    __device__ __forceinline__ float feature(int k) const
+    {
+        const float *f = fr[HASH ? k / 3 : 0];
+        const float c00 = lerpf(value(0, k), value(1, k), f[2]), c01 = lerpf(value(2, k), value(3, k), f[2]);
+        const float c10 = lerpf(value(4, k), value(5, k), f[2]), c11 = lerpf(value(6, k), value(7, k), f[2]);
+        return lerpf(lerpf(c00, c01, f[1]), lerpf(c10, c11, f[1]), f[0]);
+    }
+};
+
+// The colour of one sample on the vector ALUs in float32, by a whole
+// wavefront (lane l holds hidden units l and l + 64): for the samples whose
+// features or activations leave the range in which the split is exact.
+template <typename T, bool HASH>
+__device__ void redo_sample(const GridK &g, const cic_mlp &m, const RenderBufs &b, int64_t rec, int e0)
+{
+    const int lane = lane_id();
+    SampleRay r;
+    load_sample_ray(b, b.rec_ray[rec], b.rec_k[rec], r);
+    Gather<T, HASH> gt;
+    gt.issue(g, r, lane & 1);
+    float x[6];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const f4_t bias = *(const f4_t *)(lds + kOffB1 + 16 * t + 4 * q);
+    for (int k = 0; k < 6; ++k) x[k] = gt.feature(k);
+    float h1[2], h2[2];
 #pragma unroll
-            for (int nt = 0; nt < kNT; ++nt) h2[t][nt] = bias;
-        }
-        // Layer 1: groups of four output tiles; the next group's fragments
-        // are read while the current group's 16 MFMAs (four independent
-        // accumulators, one per tile) run.
-        {
-            f4_t a[4], an[4];
+    for (int u = 0; u < 2; ++u) {
+        const int row = lane + 64 * u;
+        float acc = ldexpf(b.z0[(int64_t)r.ray * 128 + row], -e0);
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) a[tt] = w1f[(tt * 8 + 0) * 64 + lane];
+        for (int k = 0; k < 12; ++k) acc = fmaf(m.w0[row * 39 + k], __shfl(x[k % 6], k / 6, kWave), acc);
+        h1[u] = relu_bits(acc);
+        h2[u] = m.b1[row];
+    }
+    for (int k = 0; k < 128; ++k) {
+        const float hk = __shfl(k < 64 ? h1[0] : h1[1], k & 63, kWave);
+        h2[0] = fmaf(m.w1[lane * 128 + k], hk, h2[0]);
+        h2[1] = fmaf(m.w1[(lane + 64) * 128 + k], hk, h2[1]);
+    }
 #pragma unroll
-            for (int c4 = 0; c4 < 8; ++c4) {
+    for (int ch = 0; ch < 3; ++ch) {
+        const float p = wave_sum(fmaf(m.w2[ch * 128 + lane], relu_bits(h2[0]),
+                                      m.w2[ch * 128 + 64 + lane] * relu_bits(h2[1])));
+        if (lane == ch) b.rec_c[3 * rec + ch] = sigmoid_hw(p + m.b2[ch]);
+    }
+}
+
+// Alternates the instructions before it, back to the last barrier: one MFMA,
+// then up to 8 vector and a few memory instructions that fit in its shadow.
+__device__ __forceinline__ void interleave_mfma()
+{
 #pragma unroll
-                for (int tg = 0; tg < 2; ++tg) {
-                    const int step = c4 * 2 + tg, nx = step + 1 < 16 ? step + 1 : step;
-                    const int nc4 = nx >> 1, ntg = nx & 1;
+    for (int u = 0; u < 3; ++u) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads
+        __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);     // vector ALU
+        __builtin_amdgcn_sched_group_barrier(0x20, 4, 0);    // global loads
+    }
+}
+
+constexpr uint32_t kRedo = 0x7fc0c0deu;   // a NaN that marks a colour to be redone
+
+template <typename T, bool HASH>
+__global__ __launch_bounds__(kFwdWaves * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves / 4, kFwdWaves / 4))) void
+k_mlp_fwd_f32(GridK g, cic_mlp m, RenderBufs b, int voxel)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ uint32_t claimed;
+    stage_weights_split(m, lds);
+    if (threadIdx.x == 0) claimed = kFwdWaves;
+    __syncthreads();
+
+    const int lane = lane_id(), h = lane >> 5, j = lane & 31;
+    const int wave = threadIdx.x / 64;
+    const uint32_t total = b.offsets[b.n];
+    const BatchRange br = xcd_batches(((int64_t)total + kFwdBatch - 1) / kFwdBatch, kFwdWaves, 0);
+    // The workgroup's k-th batch; its wavefronts claim them one by one (two
+    // wavefronts of a SIMD do not share its issue slots evenly: with fixed
+    // shares the favoured one ran out of batches early and left the other to
+    // run alone for the last sixth of the kernel).
+    const uint32_t bfirst = (uint32_t)br.first, bstride = (uint32_t)br.stride;
+    const uint32_t bcount = br.end > br.first ? (uint32_t)(br.end - br.first) : 0u;   // relative to bfirst
+    auto batch_of = [&](uint32_t k) -> uint32_t { return (k / kFwdWaves) * bstride + k % kFwdWaves; };
+    // Record of this lane's sample of batch bt (a lane past the last sample
+    // works on sample 0: in-bounds inputs, no branches around the loads; its
+    // colour is not stored).
+    auto record_of = [&](uint32_t bt) -> uint32_t {
+        const uint32_t s = (bfirst + bt) * kFwdBatch + j;
+        const uint32_t sv = bt < bcount && s < total ? s : 0;
+        return voxel ? b.perm[sv] : sv;
+    };
+    const float *fl = lds + kXFrags * 4;
+    const h8_t *w0f = (const h8_t *)lds + kXW0 + lane;
+    const h8_t *w1f = (const h8_t *)lds + kXW1 + lane;
+
+    bool redo = false;
+    uint32_t bt = batch_of(wave), nbt = 0;
+    if (bt < bcount) {
+        uint32_t crec = record_of(bt), nrec = 0, nray = 0;
+        int nk = 0;
+        SampleRay cur;
+        load_sample_ray(b, b.rec_ray[crec], b.rec_k[crec], cur);
+        Gather<T, HASH> gt;
+        gt.issue(g, cur, h);
+        // the features and, once split, their parts: pair k in xhi[k] and xlo[k]
+        float x[6];
+        uint32_t xhi[3], xlo[3];
+        bool bad;
+        auto split_features = [&]() {
+            const float lo3 = fabsf(x[0]) + fabsf(x[1]) + fabsf(x[2]), hi3 = fabsf(x[3]) + fabsf(x[4]) + fabsf(x[5]);
+            bad = !(lo3 + hi3 < 65504.f);
 #pragma unroll
-                    for (int tt = 0; tt < 4; ++tt) an[tt] = w1f[((4 * ntg + tt) * 8 + nc4) * 64 + lane];
+            for (int k = 0; k < 3; ++k) {
+                split2(x[2 * k], x[2 * k + 1], xhi[k], xlo[k]);
+                // (keeps the interpolation and the split here, among the MFMAs,
+                // and not moved down to their use)
+                asm volatile("" : "+v"(xhi[k]), "+v"(xlo[k]));
+            }
+        };
 #pragma unroll
-                    for (int rr = 0; rr < 4; ++rr)
+        for (int k = 0; k < 6; ++k) x[k] = gt.feature(k);
+        split_features();
+
+        f16_t acc0[4];         // layer 0
+        f16_t acch[2], accl[2];   // layer 1, one 32-row tile and the one before it: high products, low ones times 2^11
+        h8_t hb[2][8];         // the first activations' parts
+        f4_t out[2];           // the output layer's sums: channels 0..2 in rows 0..2
+        // layer 0 on top of the per-ray direction term (every record's ray has
+        // live samples, so its row is written); word w of the 3 x 4 input words is
+        // feature pair w % 3 of product w / 3 (the weights' staging lists them)
+        auto load_z0 = [&]() {
+            const float *zr = b.z0 + (int64_t)cur.ray * 128 + 4 * h;
 #pragma unroll
-                        for (int tt = 0; tt < 4; ++tt)
+            for (int t = 0; t < 4; ++t)
 #pragma unroll
-                            for (int nt = 0; nt < kNT; ++nt)
-                                h2[4 * tg + tt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                    a[tt][rr], h1[c4][nt][rr], h2[4 * tg + tt][nt], 0, 0, 0);
-                    if (tg == 1 && c4 + 1 < 8) {
+                for (int i = 0; i < 4; ++i) {
+                    const f4_t z = *(const f4_t *)(zr + 32 * t + 8 * i);
 #pragma unroll
-                        for (int nt = 0; nt < kNT; ++nt)
+                    for (int r = 0; r < 4; ++r) acc0[t][4 * i + r] = z[r];
+                }
+        };
+        auto layer0_step = [&](int s) {
+            u4_t v;
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) h1[c4 + 1][nt][r] = relu_bits(h1[c4 + 1][nt][r]);
+            for (int e = 0; e < 4; ++e) {
+                const int w = 4 * s + e;
+                v[e] = w / 3 == 3 ? 0u : w / 3 == 1 ? xlo[w % 3] : xhi[w % 3];
+            }
+            const h8_t xin = __builtin_bit_cast(h8_t, v);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                acc0[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w0f[(t * 3 + s) * 64], xin, acc0[t], 0, 0, 0);
+        };
+        // ReLU and split of the 16 units of chunk c
+        auto split_chunk = [&](int c) {
+            u4_t hi, lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t u, v;
+                const int r = 8 * (c & 1) + 2 * e;
+                split2(relu_bits(acc0[c >> 1][r]), relu_bits(acc0[c >> 1][r + 1]), u, v);
+                hi[e] = u;
+                lo[e] = v;
+            }
+            hb[0][c] = __builtin_bit_cast(h8_t, hi);
+            hb[1][c] = __builtin_bit_cast(h8_t, lo);
+        };
+        // 4 of tile t's 16 rows per lane into the output layer: a 4x4x1 MFMA adds
+        // W2's entries of one row (lane l supplies channel l % 4) times the lane's
+        // own activation, in place of three multiply-adds and three times the
+        // weight reads
+        auto output_rows = [&](int t, int i) {
+            const f4_t w = *(const f4_t *)(fl + kXW2 + ((4 * t + i) * 2 + h) * 16 + (lane & 3) * 4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float hv = relu_bits(fmaf(accl[t & 1][4 * i + r], 1.f / kLoScale, acch[t & 1][4 * i + r]));
+                out[r & 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[r], hv, out[r & 1], 0, 0, 0);
+            }
+        };
+        auto finish = [&](uint32_t bt_, uint32_t rec, bool bad_) {
+            const f4_t b2 = *(const f4_t *)(fl + kXB2);
+            float p[3];
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                p[ch] = out[0][ch] + out[1][ch];
+                p[ch] += __shfl_xor(p[ch], 32, kWave);
+                p[ch] += b2[ch];
+            }
+            const bool valid = (bfirst + bt_) * kFwdBatch + j < total;
+            bad_ = bad_ || !(fabsf(p[0]) + fabsf(p[1]) + fabsf(p[2]) < INFINITY);
+            const uint64_t bm = __ballot(bad_ && valid);
+            redo = redo || bm != 0;
+            const bool mine = (((bm | (bm >> 32)) >> j) & 1u) != 0;
+            if (valid && h == 0) {
+                float *o = b.rec_c + 3 * (int64_t)rec;
+                o[0] = mine ? __uint_as_float(kRedo) : sigmoid_hw(p[0]);
+                o[1] = sigmoid_hw(p[1]);
+                o[2] = sigmoid_hw(p[2]);
+            }
+        };
+
+        load_z0();
+#pragma unroll
+        for (int s = 0; s < 3; ++s) layer0_step(s);
+
+        for (;;) {
+            bool cbad = bad;
+            __builtin_amdgcn_sched_barrier(0);
+            out[0] = out[1] = f4_t{0.f, 0.f, 0.f, 0.f};
+            uint32_t claim = 0;
+            if (lane == 0) claim = atomicAdd(&claimed, 1u);
+            split_chunk(0);
+            h8_t a[2], an[2];
+#pragma unroll
+            for (int p = 0; p < 2; ++p) a[p] = w1f[p * 2048];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    f16_t &ah = acch[t & 1], &al = accl[t & 1];
+                    if (c == 0) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const f4_t z = *(const f4_t *)(fl + kXB1 + 32 * t + 8 * i + 4 * h);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                ah[4 * i + r] = z[r];
+                                al[4 * i + r] = 0.f;
+                            }
+                        }
                     }
+                    const int nx = t * 8 + c + 1 < 32 ? t * 8 + c + 1 : t * 8 + c;
 #pragma unroll
-                    for (int tt = 0; tt < 4; ++tt) a[tt] = an[tt];
+                    for (int p = 0; p < 2; ++p) an[p] = w1f[p * 2048 + nx * 64];
+                    ah = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], hb[0][c], ah, 0, 0, 0);
+                    al = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], hb[1][c], al, 0, 0, 0);
+                    al = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1], hb[0][c], al, 0, 0, 0);
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) a[p] = an[p];
+                    // what else happens during these MFMAs
+                    if (t == 0 && c < 7) split_chunk(c + 1);
+                    if (t == 0 && c == 1) {
+                        nbt = batch_of(__builtin_amdgcn_readfirstlane(claim));
+                        nrec = record_of(nbt);
+                    }
+                    if (t == 0 && c == 7) {
+                        nray = b.rec_ray[nrec];
+                        nk = b.rec_k[nrec];
+                    }
+                    if (t == 1 && c == 4) load_sample_ray(b, nray, nk, cur);
+                    // an activation beyond float16's range makes every low sum of its sample infinite or NaN
+                    if (t == 1 && c == 1) cbad = cbad || !(fabsf(accl[0][0]) < INFINITY);
+                    if (t > 0 && (c & 1)) output_rows(t - 1, c >> 1);
+                    if (t == 2 && c == 2) gt.issue(g, cur, h);
+                    if (t == 3 && c >= 1 && c < 7) x[c - 1] = gt.feature(c - 1);
+                    if (t == 3 && c == 7) split_features();
+                    interleave_mfma();
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            load_z0();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) output_rows(3, i);
+            __builtin_amdgcn_sched_barrier(0);
+            finish(bt, crec, cbad);
+            if (nbt >= bcount) break;
+            bt = nbt;
+            crec = nrec;
+#pragma unroll
+            for (int s = 0; s < 3; ++s) layer0_step(s);
         }
-
-        // layer 2: 128 -> 3 on the vector ALUs, then sigmoid
-        __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) {
-            crec[nt] = nrec[nt];
-            load_sample_ray(b, nray[nt], nk[nt], cur[nt]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) {
-            float p0 = 0.f, p1 = 0.f, p2 = 0.f;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const f4_t wa = w2l[(q * 3 + 0) * 8 + t];
-                const f4_t wb = w2l[(q * 3 + 1) * 8 + t];
-                const f4_t wc = w2l[(q * 3 + 2) * 8 + t];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float hv = relu_bits(h2[t][nt][r]);
-                    p0 = fmaf(wa[r], hv, p0);
-                    p1 = fmaf(wb[r], hv, p1);
-                    p2 = fmaf(wc[r], hv, p2);
-                }
-            }
-            p0 += __shfl_xor(p0, 16, kWave);
-            p1 += __shfl_xor(p1, 16, kWave);
-            p2 += __shfl_xor(p2, 16, kWave);
-            p0 += __shfl_xor(p0, 32, kWave);
-            p1 += __shfl_xor(p1, 32, kWave);
-            p2 += __shfl_xor(p2, 32, kWave);
-            if (valid[nt] && q < 3) {
-                const float logit = pick3(q, p0, p1, p2) + lds[kOffB2 + q];
-                b.rec_c[3 * (int64_t)rec[nt] + q] = sigmoid_hw(logit);
-            }
+    }
+    if (!__syncthreads_or(redo)) return;
+    const int e0 = w0_exp(m, lds);
+    for (uint32_t k = wave;; k += kFwdWaves) {
+        const uint32_t rbt = batch_of(k);
+        if (rbt >= bcount) break;
+        for (int i = 0; i < kFwdBatch; ++i) {
+            const uint32_t s = (bfirst + rbt) * kFwdBatch + i;
+            if (s >= total) break;
+            const int64_t rec = voxel ? b.perm[s] : s;
+            if (__float_as_uint(b.rec_c[3 * rec]) == kRedo) redo_sample<T, HASH>(g, m, b, rec, e0);
         }
     }
 }
 
-template <typename T, bool PET>
+template <typename T, bool HASH>
 static void launch_fwd(const GridK &g, const cic_mlp &m, const RenderBufs &b, bool voxel, hipStream_t s)
 {
-    const int lds = mlp_lds_bytes(m.compute);
     static bool attr_set = false;   // per process; the attribute is per kernel
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)k_mlp_fwd_f32<T, PET>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        (void)hipFuncSetAttribute((const void *)k_mlp_fwd_f32<T, HASH>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  kXLdsBytes);
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_mlp_fwd_f32<T, PET>), dim3(num_cus(b)), dim3(kMlpWaves * 64), lds, s, g, m, b,
+    hipLaunchKernelGGL((k_mlp_fwd_f32<T, HASH>), dim3(num_cus(b)), dim3(kFwdWaves * 64), kXLdsBytes, s, g, m, b,
                        voxel ? 1 : 0);
 }
 
@@ -325,7 +623,8 @@ void launch_mlp_forward(const GridK &g, const cic_mlp &m, const RenderBufs &b, b
         launch_mlp_forward_bf16<T>(g, m, b, voxel, s);
         return;
     }
-    launch_fwd<T, true>(g, m, b, voxel, s);
+    if (g.hlevels) launch_fwd<T, true>(g, m, b, voxel, s);
+    else launch_fwd<T, false>(g, m, b, voxel, s);
 }
 
 template void launch_mlp_forward<float>(const GridK &, const cic_mlp &, const RenderBufs &, bool, hipStream_t);
