@@ -292,31 +292,39 @@ __global__ __launch_bounds__(256) void k_compact(GridK g, RenderBufs b, int voxe
     compact_ray(g, b, ray, voxel != 0, b.brick_off);
 }
 
-// Voxel mode with an LDS histogram of the bricks: a block compacts
-// kHistRays consecutive rays, counting their runs in LDS, and then adds each
-// brick it touched to the global count once.  The rays of a block cross
-// largely the same bricks, so this takes far fewer device-wide atomics than
-// one per run.
+// Voxel mode with an LDS histogram of the bricks: a block compacts `rays`
+// consecutive rays, counting their runs in LDS, and then adds each brick it
+// touched to the global count once.  The rays of a block cross largely the
+// same bricks, so this takes far fewer device-wide atomics than one per run,
+// and neighbouring rays' runs do not queue at the same counter.  With fewer
+// rays per block in smaller passes the histogram pays down to about 2000 rays
+// (compaction + scatter: 333x257 frame of a 97x113x81 grid 471 -> 44 us,
+// 240x180 of 160^3 126 -> 42, 64x64 of 64^3 31 -> 11; 8192 training rays,
+// which are not neighbours, 38 -> 36 us); below that it is not measured to.
 constexpr int kHistBins = 16384;   // largest brick count of the LDS path (64 KB)
-constexpr int kHistRays = 256;     // rays per block
-// 16 wavefronts per block, 16 rays each: the rays' dependent load chains
-// overlap across wavefronts (measured on eight 800x800 views: compaction +
-// sort 6.5 ms with 4 wavefronts per block, 4.9 ms with 8, 4.7 ms with 16)
+constexpr int64_t kHistMin = 2048;   // fewest rays of the LDS path
+// 16 wavefronts per block: the rays' dependent load chains overlap across
+// wavefronts (measured on eight 800x800 views with 256 rays per block:
+// compaction + sort 6.5 ms with 4 wavefronts per block, 4.9 ms with 8, 4.7 ms
+// with 16)
 constexpr int kHistThreads = 1024;
-// The LDS path needs enough blocks to fill the chip (small launches, such as
-// a training step's few thousand rays, keep the per-run global atomics).
-static bool use_hist(const RenderBufs &b)
+// Rays per block: 256 where that still gives 512 blocks, else fewer, down to
+// one per wavefront; 0 = the per-run global atomics.
+static int hist_rays(const RenderBufs &b)
 {
-    return b.n_bricks <= kHistBins && b.n >= (int64_t)kHistRays * 512;
+    if (b.n_bricks > kHistBins || b.n < kHistMin) return 0;
+    int r = 256;
+    while (r > kHistThreads / kWave && b.n < (int64_t)r * 512) r >>= 1;
+    return r;
 }
 
-__global__ __launch_bounds__(kHistThreads) void k_compact_hist(GridK g, RenderBufs b)
+__global__ __launch_bounds__(kHistThreads) void k_compact_hist(GridK g, RenderBufs b, int rays)
 {
     extern __shared__ uint32_t hist[];
     for (int64_t i = threadIdx.x; i < b.n_bricks; i += blockDim.x) hist[i] = 0u;
     __syncthreads();
-    const int64_t ray0 = (int64_t)blockIdx.x * kHistRays;
-    const int64_t ray1 = ray0 + kHistRays < b.n ? ray0 + kHistRays : b.n;
+    const int64_t ray0 = (int64_t)blockIdx.x * rays;
+    const int64_t ray1 = ray0 + rays < b.n ? ray0 + rays : b.n;
     for (int64_t ray = ray0 + threadIdx.x / kWave; ray < ray1; ray += blockDim.x / kWave)
         compact_ray(g, b, ray, true, hist);
     __syncthreads();
@@ -329,9 +337,11 @@ __global__ __launch_bounds__(kHistThreads) void k_compact_hist(GridK g, RenderBu
 void launch_compact(const GridK &g, const RenderBufs &b, bool voxel_keys, hipStream_t s)
 {
     if (b.n == 0) return;
-    if (voxel_keys && use_hist(b)) {
-        const unsigned blocks = (unsigned)((b.n + kHistRays - 1) / kHistRays);
-        hipLaunchKernelGGL(k_compact_hist, dim3(blocks), dim3(kHistThreads), b.n_bricks * sizeof(uint32_t), s, g, b);
+    const int rays = voxel_keys ? hist_rays(b) : 0;
+    if (rays) {
+        const unsigned blocks = (unsigned)((b.n + rays - 1) / rays);
+        hipLaunchKernelGGL(k_compact_hist, dim3(blocks), dim3(kHistThreads), b.n_bricks * sizeof(uint32_t), s, g, b,
+                           rays);
         return;
     }
     const unsigned blocks = (unsigned)((b.n + kRayWaves - 1) / kRayWaves);
@@ -364,19 +374,19 @@ __global__ __launch_bounds__(256) void k_brick_scatter(RenderBufs b)
     }
 }
 
-// LDS-histogram scatter over the same blocks of kHistRays rays, whose
+// LDS-histogram scatter over the same blocks of rays, whose
 // samples are one contiguous range of records: count the block's samples
 // per brick in LDS, reserve each touched brick's share of the global cursor
 // with one atomic, then hand out positions from the LDS cursors (one LDS
 // atomic per run of equal bricks).
-__global__ __launch_bounds__(kHistThreads) void k_brick_scatter_hist(RenderBufs b)
+__global__ __launch_bounds__(kHistThreads) void k_brick_scatter_hist(RenderBufs b, int rays)
 {
     extern __shared__ uint32_t hist[];
     const int lane = lane_id(), wave = threadIdx.x / kWave, nwaves = blockDim.x / kWave;
     for (int64_t i = threadIdx.x; i < b.n_bricks; i += blockDim.x) hist[i] = 0u;
     __syncthreads();
-    const int64_t ray0 = (int64_t)blockIdx.x * kHistRays;
-    const int64_t ray1 = ray0 + kHistRays < b.n ? ray0 + kHistRays : b.n;
+    const int64_t ray0 = (int64_t)blockIdx.x * rays;
+    const int64_t ray1 = ray0 + rays < b.n ? ray0 + rays : b.n;
     const uint32_t s0 = b.offsets[ray0], s1 = b.offsets[ray1];
     for (uint32_t w0 = s0 + (uint32_t)wave * kWave; w0 < s1; w0 += (uint32_t)nwaves * kWave) {
         const uint32_t sidx = w0 + lane;
@@ -410,9 +420,11 @@ __global__ __launch_bounds__(kHistThreads) void k_brick_scatter_hist(RenderBufs 
 void launch_brick_scatter(const RenderBufs &b, hipStream_t s)
 {
     if (b.n == 0) return;
-    if (use_hist(b)) {
-        const unsigned blocks = (unsigned)((b.n + kHistRays - 1) / kHistRays);
-        hipLaunchKernelGGL(k_brick_scatter_hist, dim3(blocks), dim3(kHistThreads), b.n_bricks * sizeof(uint32_t), s, b);
+    const int rays = hist_rays(b);
+    if (rays) {
+        const unsigned blocks = (unsigned)((b.n + rays - 1) / rays);
+        hipLaunchKernelGGL(k_brick_scatter_hist, dim3(blocks), dim3(kHistThreads), b.n_bricks * sizeof(uint32_t), s, b,
+                           rays);
         return;
     }
     const unsigned blocks = (unsigned)((b.n + kRayWaves - 1) / kRayWaves);

@@ -1,0 +1,29 @@
+"""Voxel-order bucketing at the edges of its rule for rays per block (per-run
+counters below 2048 rays, then blocks of 16 to 256 rays, the last one ragged):
+voxel order must give ray order's bits, which it does only if every sample's
+place in the permutation is taken exactly once."""
+import pytest
+import torch
+
+import synth
+from helpers import print_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("res,n_rays", [(33, 2047), (33, 2048), (33, 2049), (33, 16 * 512 - 1), (33, 32 * 512),
+                                        (33, 64 * 512 + 1), (33, 128 * 512 + 100), (201, 2100), (209, 2100)])
+def test_voxel_order_equals_ray_order(res, n_rays):
+    import paper_2404_11852_amd as cic
+    print_case("bucketing, %d^3 grid, %d rays" % (res, n_rays))   # 201: 15,625 bricks, 209: 17,576 (no LDS histogram)
+    dens = torch.full((res,) * 3, 1.0)
+    feats = torch.randn((res,) * 3 + (12,), generator=torch.Generator().manual_seed(n_rays)) if res < 100 else \
+        torch.linspace(-1.0, 1.0, 12).expand((res,) * 3 + (12,))
+    m = cic.Model(dens, feats, synth.make_mlp(1, bias_std=0.1), density_shift=0.0)
+    o, d = (torch.from_numpy(t).cuda() for t in synth.random_rays(n_rays, seed=3))
+    got = []
+    for order in (cic.CIC_ORDER_RAY, cic.CIC_ORDER_VOXEL):
+        n = torch.zeros(1, dtype=torch.int64, device="cuda")
+        got.append((*cic.render_rays(m, cic.make_opts(40, order=order), o, d, n_eval=n), n))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
