@@ -93,6 +93,14 @@ __device__ __forceinline__ float sample_t(float tn, float delta, int k)
     return tn + ((float)k + 0.5f) * delta;
 }
 
+// (int)floorf(u) in one instruction
+__device__ __forceinline__ int floor_int(float u)
+{
+    int i;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(u));
+    return i;
+}
+
 // World position -> lower vertex index of the voxel and fraction inside it.
 __device__ __forceinline__ void locate(const float x[3], const GridK &g, int i0[3], float fr[3])
 {
@@ -100,9 +108,7 @@ __device__ __forceinline__ void locate(const float x[3], const GridK &g, int i0[
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         float u = (x[k] - g.lo[k]) * g.scale[k];
-        int i = (int)floorf(u);
-        i = i < 0 ? 0 : i;
-        i = i > rr[k] - 2 ? rr[k] - 2 : i;
+        int i = min(max(floor_int(u), 0), rr[k] - 2);
         float f = u - (float)i;
         fr[k] = clamp01_bits(f);
         i0[k] = i;
@@ -117,6 +123,27 @@ __device__ __forceinline__ int64_t cell_index(const GridK &g, const int i0[3])
 __device__ __forceinline__ int64_t vertex_index(const GridK &g, int x, int y, int z)
 {
     return ((int64_t)x * g.r1 + y) * (int64_t)g.r2 + z;
+}
+
+// The same indices in 32 bits: at most 1024 vertices per axis, so they stay
+// below 2^30 and every product has 24-bit operands (one full-rate multiply-add
+// each, where the 64-bit forms take four quarter-rate multiplies).
+__device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t r;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+    return r;
+}
+
+__device__ __forceinline__ uint32_t cell_index32(const GridK &g, const int i0[3])
+{
+    const uint32_t row = mad_u24((uint32_t)i0[0], (uint32_t)(g.r1 - 1), (uint32_t)i0[1]);
+    return mad_u24(row, (uint32_t)(g.r2 - 1), (uint32_t)i0[2]);
+}
+
+__device__ __forceinline__ uint32_t vertex_index32(const GridK &g, const int i0[3])
+{
+    return mad_u24(mad_u24((uint32_t)i0[0], (uint32_t)g.r1, (uint32_t)i0[1]), (uint32_t)g.r2, (uint32_t)i0[2]);
 }
 
 __device__ __forceinline__ uint32_t brick_of(const GridK &g, const int i0[3])
@@ -170,6 +197,47 @@ __device__ __forceinline__ float trilerp1(const T *v, const GridK &g, const int 
     float c00 = lerpf(v000, v001, fr[2]), c01 = lerpf(v010, v011, fr[2]);
     float c10 = lerpf(v100, v101, fr[2]), c11 = lerpf(v110, v111, fr[2]);
     float c0 = lerpf(c00, c01, fr[1]), c1 = lerpf(c10, c11, fr[1]);
+    return lerpf(c0, c1, fr[0]);
+}
+
+// a + t (b - a) of a pair of neighbouring values: float32, or float16 packed
+// in a word, whose conversions the mixed-precision multiply-adds carry (b - a
+// as b x 1 - a: the same rounding)
+template <typename T> struct PairAt;
+template <> struct PairAt<float> {
+    float a, b;
+    __device__ __forceinline__ PairAt(const char *base, uint32_t off)
+    {
+        const float *p = (const float *)(base + off);
+        a = p[0];
+        b = p[1];
+    }
+    __device__ __forceinline__ float lerp(float t) const { return lerpf(a, b, t); }
+};
+template <> struct PairAt<__half> {
+    uint32_t w;
+    __device__ __forceinline__ PairAt(const char *base, uint32_t off) { __builtin_memcpy(&w, base + off, 4); }
+    __device__ __forceinline__ float lerp(float t) const
+    {
+        float d, r;
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(w));
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(r) : "v"(t), "v"(d), "v"(w));
+        return r;
+    }
+};
+
+// The density grid at cell i0: trilerp1 with stride 1, the vertices' byte
+// offset in 32 bits (below 2^32 for 1024^3 float32 vertices) and the four
+// rows' bases uniform.
+template <typename T>
+__device__ __forceinline__ float density_at(const GridK &g, const int i0[3], const float fr[3])
+{
+    const char *p = (const char *)g.density;
+    const int64_t sy = (int64_t)g.r2 * (int64_t)sizeof(T), sx = (int64_t)g.r1 * sy;
+    const uint32_t off = vertex_index32(g, i0) * (uint32_t)sizeof(T);
+    const PairAt<T> p00(p, off), p01(p + sy, off), p10(p + sx, off), p11(p + sx + sy, off);
+    const float c0 = lerpf(p00.lerp(fr[2]), p01.lerp(fr[2]), fr[1]);
+    const float c1 = lerpf(p10.lerp(fr[2]), p11.lerp(fr[2]), fr[1]);
     return lerpf(c0, c1, fr[0]);
 }
 
