@@ -620,30 +620,52 @@ void launch_generate_rays(const cic_camera &cam, int64_t n, int64_t base, const 
 }
 
 // Occupancy: a voxel is occupied iff any vertex has raw + shift > thr
-// (thr = log(expm1(occ_sigma)) rounded to float32 on the host).
+// (thr = log(expm1(occ_sigma)) rounded to float32 on the host).  One
+// wavefront tests the 64 vertices from z0 in the vertex rows y and y + 1 of
+// kOccX + 1 consecutive x (all its loads go out together), as one 64-bit mask
+// per x; the voxels' bytes are ORs of neighbouring masks and their shifts.  A
+// row's vertices are loaded twice rather than eight times, coalesced, with no
+// division per voxel.  Bound by the read of the density (160^3 float32: 16.4
+// MB and 4.0 MB of bytes written: 8.3 us, before 18.7; float16 10.2 and 21.4).
+constexpr int kOccX = 8;           // voxels per wavefront along x (2: 12.0 us, 4: 9.2, 8: 8.3)
+constexpr int kOccZ = kWave - 1;   // and along z
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_build_occupancy(GridK g, float thr, uint8_t *occ)
+__global__ __launch_bounds__(256) void k_build_occupancy(GridK g, float thr, uint8_t *occ, uint32_t nx, uint32_t nz)
 {
-    const int64_t c1 = g.r1 - 1, c2 = g.r2 - 1;
-    const int64_t nc = (int64_t)(g.r0 - 1) * c1 * c2;
+    const uint32_t c1 = g.r1 - 1, c2 = g.r2 - 1;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + threadIdx.x / kWave);
+    const uint32_t xg = wave / (c1 * nz), y = (wave / nz) % c1, z0 = (wave % nz) * kOccZ;
+    if (xg >= nx) return;
+    const int lane = lane_id();
+    const uint32_t z = min(z0 + (uint32_t)lane, (uint32_t)g.r2 - 1u), x0 = xg * kOccX;
     const T *dens = (const T *)g.density;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += (int64_t)gridDim.x * blockDim.x) {
-        const int x = (int)(c / (c1 * c2)), y = (int)((c / c2) % c1), z = (int)(c % c2);
-        bool any = false;
+    float v[kOccX + 1][2];
 #pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const float s = ldv(dens, vertex_index(g, x + ((v >> 2) & 1), y + ((v >> 1) & 1), z + (v & 1))) + g.shift;
-            any |= s > thr;
-        }
-        occ[c] = any ? 1 : 0;
+    for (int i = 0; i <= kOccX; ++i) {
+        const T *row = dens + ((int64_t)min(x0 + i, (uint32_t)g.r0 - 1u) * g.r1 + y) * g.r2;
+        v[i][0] = ldv(row, z);
+        v[i][1] = ldv(row, z + (uint32_t)g.r2);
+    }
+    uint64_t m[kOccX + 1];
+#pragma unroll
+    for (int i = 0; i <= kOccX; ++i)
+        m[i] = __builtin_amdgcn_ballot_w64(v[i][0] + g.shift > thr || v[i][1] + g.shift > thr);
+    if (lane >= kOccZ || z0 + (uint32_t)lane >= c2) return;
+#pragma unroll
+    for (int i = 0; i < kOccX; ++i) {
+        if (x0 + i >= (uint32_t)g.r0 - 1u) break;
+        const uint64_t any = m[i] | m[i + 1];
+        occ[((int64_t)(x0 + i) * c1 + y) * c2 + z] = (uint8_t)(((any | any >> 1) >> lane) & 1u);
     }
 }
 
 template <typename T>
 void launch_build_occupancy(const GridK &g, float thr, uint8_t *occ, hipStream_t s)
 {
-    const int64_t nc = (int64_t)(g.r0 - 1) * (g.r1 - 1) * (g.r2 - 1);
-    hipLaunchKernelGGL(k_build_occupancy<T>, dim3(fill_blocks(nc)), dim3(256), 0, s, g, thr, occ);
+    const uint32_t nx = (uint32_t)(g.r0 - 1 + kOccX - 1) / kOccX, nz = (uint32_t)(g.r2 - 1 + kOccZ - 1) / kOccZ;
+    const uint64_t waves = (uint64_t)nx * (uint64_t)(g.r1 - 1) * nz;   // at most 2^22
+    hipLaunchKernelGGL(k_build_occupancy<T>, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, g, thr, occ, nx, nz);
 }
 template void launch_build_occupancy<float>(const GridK &, float, uint8_t *, hipStream_t);
 template void launch_build_occupancy<__half>(const GridK &, float, uint8_t *, hipStream_t);
