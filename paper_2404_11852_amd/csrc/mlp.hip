@@ -91,119 +91,136 @@ __device__ __forceinline__ int block_exp(float top, int to)
     return top > 0.f ? min(max(to + 127 - (int)(__float_as_uint(top) >> 23), -100), 100) : 0;
 }
 
-// Exponent of layer 0's scale: W0's feature columns are scaled to a largest
-// entry in [1, 2), the per-ray direction terms with them.
-__device__ __forceinline__ int w0_exp(const cic_mlp &m, float *red)
+// Largest of a value over the block (red: one float per wavefront and block
+// maximum; a barrier before its next use is the caller's).
+__device__ __forceinline__ float block_max(float v, float *red)
 {
-    float top = 0.f;
-    for (int i = threadIdx.x; i < 128 * 12; i += blockDim.x) top = fmaxf(top, fabsf(m.w0[(i / 12) * 39 + i % 12]));
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off, kWave));
-    if (lane_id() == 0) red[threadIdx.x / kWave] = top;
+    for (int off = kWave / 2; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
+    if (lane_id() == 0) red[threadIdx.x / kWave] = v;
     __syncthreads();
-    for (int k = 0; k < (int)blockDim.x / kWave; ++k) top = fmaxf(top, red[k]);
-    __syncthreads();
-    return block_exp(top, 0);
+    for (int k = 0; k < (int)blockDim.x / kWave; ++k) v = fmaxf(v, red[k]);
+    return v;
 }
 
-// Weights into LDS in fragment order.  W1 is scaled by the power of two that
-// puts its largest entry in [2^14, 2^15) before the split (so both parts use
-// float16's range), b1 with it and with layer 0's scale; W2 by the inverse of
-// both, which the ReLUs let through exactly.
-__device__ void stage_weights_split(const cic_mlp &m, float *lds)
+// Weights into LDS in fragment order.  W0's feature columns are scaled by the
+// power of two 2^e0 that puts their largest entry in [1, 2) (the per-ray
+// direction terms with them), W1 by the one that puts its largest entry in
+// [2^14, 2^15) before the split (so both parts use float16's range), b1 by
+// both; W2 by the inverse of both, which the ReLUs let through exactly.
+// Returns e0.  Every load goes out before the first barrier (a SpaRW target's
+// MLP stage 215 -> 209 us against loading between the barriers).
+__device__ int stage_weights_split(const cic_mlp &m, float *lds)
 {
     h8_t *w1 = (h8_t *)lds + kXW1;
     h8_t *w0 = (h8_t *)lds + kXW0;
     float *fl = lds + kXFrags * 4;
-    constexpr int kT = kFwdWaves * 64, kN = 4 * 8 * 64, kIt = (kN + kT - 1) / kT;
-    float w[kIt][8], top = 0.f;
+    constexpr int kT = kFwdWaves * 64, kN = 4 * 8 * 64, kIt = kN / kT, kN0 = 4 * 3 * 64, kIt0 = (kN0 + kT - 1) / kT;
+    static_assert(kN % kT == 0 && kT == 512, "one W2 entry and the W1 fragments per thread");
+    const int tid = threadIdx.x;
+    f4_t w[kIt][2];
+    float v0[kIt0][8], top1 = 0.f, top0 = 0.f;
 #pragma unroll
     for (int k = 0; k < kIt; ++k) {
-        const int i = (int)threadIdx.x + k * kT;
-        const int l = i & 63, c = (i >> 6) & 7, t = (i >> 9) & 3;
+        const int i = tid + k * kT, l = i & 63, c = (i >> 6) & 7, t = i >> 9;
         const float *src = m.w1 + (32 * t + (l & 31)) * 128;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            w[k][e] = src[x_hid(c, l >> 5, e)];
-            top = fmaxf(top, fabsf(w[k][e]));
-        }
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[k][u][e] = src[x_hid(c, l >> 5, 4 * u) + e];
     }
-    const int e0 = w0_exp(m, fl);
-    const float s0 = ldexpf(1.f, e0);
-    for (int i = threadIdx.x; i < 4 * 3 * 64; i += kT) {
-        const int l = i & 63, s = (i >> 6) % 3, t = i / 192;
+#pragma unroll
+    for (int k = 0; k < kIt0; ++k) {
+        const int i = min(tid + k * kT, kN0 - 1), l = i & 63, s = (i >> 6) % 3, t = i / 192;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v0[k][e] = m.w0[(32 * t + (l & 31)) * 39 + 6 * (l >> 5) + (8 * s + e) % 6];
+    }
+    const int ch2 = (tid >> 2) & 3, h2 = (tid >> 4) & 1;
+    const int row2 = 32 * (tid >> 7) + 8 * ((tid >> 5) & 3) + 4 * h2 + (tid & 3);
+    const float v2 = m.w2[min(ch2, 2) * 128 + row2], vb1 = m.b1[tid & 127], vb2 = m.b2[min(tid & 3, 2)];
+#pragma unroll
+    for (int k = 0; k < kIt; ++k)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) top1 = fmaxf(top1, fabsf(w[k][u][e]));
+#pragma unroll
+    for (int k = 0; k < kIt0; ++k)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) top0 = fmaxf(top0, fabsf(v0[k][e]));
+    // (the two reductions' floats lie where the fragments come later)
+    top0 = block_max(top0, fl);
+    top1 = block_max(top1, fl + 16);
+    __syncthreads();
+    const int e0 = block_exp(top0, 0), e1 = block_exp(top1, 14);
+    const float s0 = ldexpf(1.f, e0), s1 = ldexpf(1.f, e1);
+#pragma unroll
+    for (int k = 0; k < kIt0; ++k) {
+        const int i = tid + k * kT, s = (i >> 6) % 3;
         h8_t v;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             // products: high x high, high / 2^11 x (low times 2^11), low x high
-            const int idx = 8 * s + e, p = idx / 6, f = idx % 6;
-            const float a = m.w0[(32 * t + (l & 31)) * 39 + 6 * (l >> 5) + f] * s0;
+            const int p = (8 * s + e) / 6;
+            const float a = v0[k][e] * s0;
             const _Float16 hi = (_Float16)a;
-            v[e] = p == 0 ? hi : p == 1 ? (_Float16)((float)hi / kLoScale) : p == 2 ? (_Float16)(a - (float)hi)
-                                                                                   : (_Float16)0.f;
+            v[e] = p == 0 ? hi : p == 1 ? (_Float16)((float)hi * (1.f / kLoScale)) : p == 2 ? (_Float16)(a - (float)hi)
+                                                                                           : (_Float16)0.f;
         }
-        w0[i] = v;
+        if (i < kN0) w0[i] = v;
     }
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off, kWave));
-    if (lane_id() == 0) fl[threadIdx.x / kWave] = top;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kFwdWaves; ++k) top = fmaxf(top, fl[k]);
-    __syncthreads();
-    const int e1 = block_exp(top, 14);
-    const float s1 = ldexpf(1.f, e1);
-#pragma unroll
     for (int k = 0; k < kIt; ++k) {
-        const int i = (int)threadIdx.x + k * kT;
-        if (i >= kN) continue;
         u4_t hi, lo;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             uint32_t a, b;
-            split2(w[k][2 * e] * s1, w[k][2 * e + 1] * s1, a, b);
+            split2(w[k][e >> 1][2 * (e & 1)] * s1, w[k][e >> 1][2 * (e & 1) + 1] * s1, a, b);
             hi[e] = a;
             lo[e] = b;
         }
-        w1[i] = __builtin_bit_cast(h8_t, hi);
-        w1[kN + i] = __builtin_bit_cast(h8_t, lo);
+        w1[tid + k * kT] = __builtin_bit_cast(h8_t, hi);
+        w1[kN + tid + k * kT] = __builtin_bit_cast(h8_t, lo);
     }
-    for (int i = threadIdx.x; i < 512; i += kT) {
-        const int ch = (i >> 2) & 3, h = (i >> 4) & 1, row = 32 * (i >> 7) + 8 * ((i >> 5) & 3) + 4 * h + (i & 3);
-        fl[kXW2 + i] = ch < 3 ? ldexpf(m.w2[ch * 128 + row], -(e0 + e1)) : 0.f;
-    }
-    for (int i = threadIdx.x; i < 128; i += kT) fl[kXB1 + i] = ldexpf(m.b1[i], e0 + e1);
-    if (threadIdx.x < 4) fl[kXB2 + threadIdx.x] = threadIdx.x < 3 ? m.b2[threadIdx.x] : 0.f;
+    fl[kXW2 + tid] = ch2 < 3 ? ldexpf(v2, -(e0 + e1)) : 0.f;
+    if (tid < 128) fl[kXB1 + tid] = ldexpf(vb1, e0 + e1);
+    if (tid < 4) fl[kXB2 + tid] = tid < 3 ? vb2 : 0.f;
+    return e0;
 }
 
-// Per-ray direction term of layer 0: z0[ray][o] = b0[o] + sum_i W0[o][12+i] pe_i
-// over the 27 direction inputs (d, sin, cos), once per ray with live samples
-// (float32; used by the FP32 MLP in either order).  A block stages the
-// inputs of kEmbedRays rays in LDS (one sincosf per argument gives both its
-// sine and cosine input), and each of its 128 threads then forms output o for
-// every ray with its 27 weights held in registers.
-#ifndef CIC_EMBED_RAYS
-#define CIC_EMBED_RAYS 64
-#endif
-constexpr int kEmbedRays = CIC_EMBED_RAYS;
-
+// Per-ray direction term of layer 0: z0[ray][o] = 2^e0 (b0[o] + sum_i
+// W0[o][12+i] pe_i) over the 27 direction inputs (d, sin, cos), once per ray
+// with live samples (float32, scaled as the MLP scales W0; used in either
+// order).  A block stages the inputs of RAYS rays in LDS (one sincosf per
+// argument gives both its sine and cosine input), and each of its 128 threads
+// then forms output o for every ray with its 27 weights held in registers.
+// The weight rows (whose first 12 entries give e0) and the rays are loaded
+// together, before the first barrier.  64 rays per block amortise the weight
+// reads in large passes; small ones take 16, so that the launch spreads over
+// the chip (4096 rays: 19.4 -> 7.3 us; 85,581: 16 per block 22.7, 64 27.3;
+// 640,000: 110 and 90).
+template <int RAYS>
 __global__ __launch_bounds__(128) void k_ray_embed(cic_mlp m, RenderBufs b, float *z0)
 {
-    __shared__ float pe[kEmbedRays][28];
-    __shared__ uint32_t live[kEmbedRays];
+    __shared__ __attribute__((aligned(16))) float pe[RAYS][28];
+    __shared__ uint32_t live[RAYS];
     __shared__ float red[2];
     const int o = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * kEmbedRays;
+    const int64_t base = (int64_t)blockIdx.x * RAYS;
     // a pass over a device-counted set of rays (the holes of a warped frame)
     // skips the blocks past its count, whose rays have no live samples
     if (b.n_active && (uint64_t)base >= *b.n_active) return;
-    for (int r = threadIdx.x; r < kEmbedRays; r += 128) live[r] = base + r < b.n ? b.count[base + r] : 0u;
-    __syncthreads();
+    float w[39];
+#pragma unroll
+    for (int i = 0; i < 39; ++i) w[i] = m.w0[o * 39 + i];
+    const float bias = m.b0[o];
+    for (int r = threadIdx.x; r < RAYS; r += 128) live[r] = base + r < b.n ? b.count[base + r] : 0u;
     // entries 0..2: the direction; argument k = 4c + octave (k < 12): sine at
-    // 3 + k, cosine at 15 + k
-    for (int e = threadIdx.x; e < kEmbedRays * 15; e += 128) {
+    // 3 + k, cosine at 15 + k (also for rays without live samples: their
+    // entries are not used)
+    for (int e = threadIdx.x; e < RAYS * 15; e += 128) {
         const int r = e / 15, i = e % 15;
-        if (!live[r]) continue;
+        if (base + r >= b.n) continue;
         const float *d = b.rays_d + 3 * (base + r);
         if (i < 3) {
             pe[r][i] = d[i];
@@ -215,26 +232,30 @@ __global__ __launch_bounds__(128) void k_ray_embed(cic_mlp m, RenderBufs b, floa
             pe[r][15 + k] = cs;
         }
     }
-    __syncthreads();
-    const int e0 = w0_exp(m, red);
-    float w[27];
+    float top = 0.f;
 #pragma unroll
-    for (int i = 0; i < 27; ++i) w[i] = ldexpf(m.w0[o * 39 + 12 + i], e0);
-    const float bias = ldexpf(m.b0[o], e0);
-    for (int r = 0; r < kEmbedRays; ++r) {
+    for (int i = 0; i < 12; ++i) top = fmaxf(top, fabsf(w[i]));
+    const int e0 = block_exp(block_max(top, red), 0);   // its barrier also covers pe and live
+    for (int r = 0; r < RAYS; ++r) {
         if (!live[r]) continue;
         float acc = bias;
 #pragma unroll
-        for (int i = 0; i < 27; ++i) acc = fmaf(w[i], pe[r][i], acc);
-        z0[(base + r) * 128 + o] = acc;
+        for (int i = 0; i < 27; ++i) acc = fmaf(w[12 + i], pe[r][i], acc);
+        z0[(base + r) * 128 + o] = ldexpf(acc, e0);
     }
+}
+
+template <int RAYS>
+static void launch_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_ray_embed<RAYS>, dim3((unsigned)((b.n + RAYS - 1) / RAYS)), dim3(128), 0, s, m, b, b.z0);
 }
 
 void launch_ray_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s)
 {
     if (b.n == 0 || m.compute != CIC_F32) return;
-    const unsigned blocks = (unsigned)((b.n + kEmbedRays - 1) / kEmbedRays);
-    hipLaunchKernelGGL(k_ray_embed, dim3(blocks), dim3(128), 0, s, m, b, b.z0);
+    if (b.n < 131072) launch_embed<16>(m, b, s);
+    else launch_embed<64>(m, b, s);
 }
 
 // Features 6h .. 6h+5 of one sample (lane half h): issue() sends the loads of
@@ -378,7 +399,7 @@ k_mlp_fwd_f32(GridK g, cic_mlp m, RenderBufs b, int voxel)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ uint32_t claimed;
-    stage_weights_split(m, lds);
+    const int e0 = stage_weights_split(m, lds);
     if (threadIdx.x == 0) claimed = kFwdWaves;
     __syncthreads();
 
@@ -584,7 +605,6 @@ k_mlp_fwd_f32(GridK g, cic_mlp m, RenderBufs b, int voxel)
         }
     }
     if (!__syncthreads_or(redo)) return;
-    const int e0 = w0_exp(m, lds);
     for (uint32_t k = wave;; k += kFwdWaves) {
         const uint32_t rbt = batch_of(k);
         if (rbt >= bcount) break;
