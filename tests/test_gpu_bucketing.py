@@ -27,3 +27,21 @@ def test_voxel_order_equals_ray_order(res, n_rays):
         got.append((*cic.render_rays(m, cic.make_opts(40, order=order), o, d, n_eval=n), n))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n_rays", [1, 3, 1023, 1025, 4096, 4097, 16381, 16385, 2048 * 9 + 1])
+def test_scan_edges(n_rays):
+    """Record offsets at the edges of the one-block scan and of the blocks of
+    the longer one: rays rendered together equal rays rendered in two calls."""
+    import paper_2404_11852_amd as cic
+    print_case("scan, %d rays" % n_rays)
+    dens, feats = synth.make_scene(24, seed=0)
+    m = cic.Model(dens, feats, synth.make_mlp(1, bias_std=0.1), density_shift=synth.DENSITY_SHIFT)
+    m.build_occupancy(synth.OCC_SIGMA)
+    o, d = (torch.from_numpy(t).cuda() for t in synth.random_rays(n_rays, seed=4))
+    opts = cic.make_opts(33, 1e-4, True)
+    whole = cic.render_rays(m, opts, o, d)
+    k = n_rays // 3
+    parts = [cic.render_rays(m, opts, o[a:b], d[a:b]) for a, b in ((0, k), (k, n_rays)) if b > a]
+    for i, t in enumerate(whole):
+        assert torch.equal(t, torch.cat([p[i] for p in parts]))
