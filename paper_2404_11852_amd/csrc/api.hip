@@ -462,7 +462,7 @@ struct StageTimer {
 // Full render pipeline on one pass of rays.
 void run_pipeline(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, const OptsK &ok_, bool voxel,
                   RenderBufs &b, float *rgb, float *depth, float *acc, const int32_t *out_map,
-                  const cic_camera *frame_cam, int64_t *n_eval, hipStream_t s)
+                  const cic_camera *frame_cam, int64_t *n_eval, hipStream_t s, int64_t *n_masked = nullptr)
 {
     const bool f16 = grid->storage == CIC_F16;
     {
@@ -495,7 +495,7 @@ void run_pipeline(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, con
     }
     {
         StageTimer t(CIC_STAGE_REDUCE, s);
-        launch_reduce(b, ok_, rgb, depth, acc, out_map, frame_cam, n_eval, s);
+        launch_reduce(b, ok_, rgb, depth, acc, out_map, frame_cam, n_eval, n_masked, s);
     }
 }
 
@@ -530,8 +530,7 @@ void sparw_frame(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, cons
         StageTimer t(CIC_STAGE_RAYGEN, s);
         launch_generate_rays(tgt, np, 0, nullptr, w.hole_idx, w.n_holes, (float *)b.rays_o, (float *)b.rays_d, s);
     }
-    run_pipeline(grid, gk, mlp, ok_, voxel, b, out_rgb, out_dz, nullptr, w.hole_idx, &tgt, n_eval, s);
-    if (n_masked) launch_sparw_finish(w.n_holes, n_masked, s);
+    run_pipeline(grid, gk, mlp, ok_, voxel, b, out_rgb, out_dz, nullptr, w.hole_idx, &tgt, n_eval, s, n_masked);
 }
 
 // Events that order render_sequence's two streams.  They live for one call:

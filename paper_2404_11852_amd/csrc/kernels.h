@@ -83,9 +83,11 @@ void launch_brick_segments(const RenderBufs &b, int seg, bool table, hipStream_t
 // upsample.hip
 void launch_upsample_bilinear(const float *lo, int w, int h, float *out, int W, int H, int s, hipStream_t st);
 // Final per-ray accumulation.  out_map (nullable) maps ray -> output slot;
-// frame_cam (nullable) switches depth output to frame z-depth.
+// frame_cam (nullable) switches depth output to frame z-depth; n_masked
+// (nullable) receives the number of active rays.
 void launch_reduce(const RenderBufs &b, const OptsK &o, float *rgb, float *depth, float *acc,
-                   const int32_t *out_map, const cic_camera *frame_cam, int64_t *n_eval, hipStream_t s);
+                   const int32_t *out_map, const cic_camera *frame_cam, int64_t *n_eval, int64_t *n_masked,
+                   hipStream_t s);
 void launch_generate_rays(const cic_camera &cam, int64_t n, int64_t base, const int64_t *pix, const int32_t *pix32,
                           const uint32_t *n_active, float *o, float *d, hipStream_t s);
 template <typename T>
@@ -106,7 +108,6 @@ void launch_ray_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s);
 void launch_warp(const cic_camera &ref, const cic_camera &tgt, const float T[12], float cmin, const float *ref_rgb,
                  const float *ref_depth, uint64_t *zbuf, float *tgt_rgb, float *tgt_depth, uint8_t *mask,
                  int32_t *src_index, int32_t *hole_idx, uint32_t *n_holes, hipStream_t s);
-void launch_sparw_finish(const uint32_t *n_holes, int64_t *n_masked, hipStream_t s);
 
 // backward.hip
 struct BackwardBufs {

@@ -542,12 +542,13 @@ __device__ __forceinline__ float group16_sum(float v)
 
 __global__ __launch_bounds__(256) void k_reduce(RenderBufs b, OptsK op, float *rgb, float *depth, float *acc,
                                                 const int32_t *out_map, cic_camera cam, int frame,
-                                                unsigned long long *n_eval)
+                                                unsigned long long *n_eval, int64_t *n_masked)
 {
     const int sub = (int)(threadIdx.x % kReduceLanes);
     const int64_t ray = (int64_t)blockIdx.x * kReduceRays + (threadIdx.x / kReduceLanes);
     if (n_eval && ray == 0 && sub == 0) atomicAdd(n_eval, (unsigned long long)b.offsets[b.n]);
     const uint32_t n_act = b.n_active ? *b.n_active : (uint32_t)b.n;
+    if (n_masked && ray == 0 && sub == 0) *n_masked = (int64_t)n_act;
     const bool active = ray < b.n && (uint64_t)ray < n_act;
     const uint32_t cnt = active ? b.count[ray] : 0u, off = active ? b.offsets[ray] : 0u;
     float r = 0.f, gg = 0.f, bb = 0.f;
@@ -584,13 +585,14 @@ __global__ __launch_bounds__(256) void k_reduce(RenderBufs b, OptsK op, float *r
 }
 
 void launch_reduce(const RenderBufs &b, const OptsK &o, float *rgb, float *depth, float *acc,
-                   const int32_t *out_map, const cic_camera *frame_cam, int64_t *n_eval, hipStream_t s)
+                   const int32_t *out_map, const cic_camera *frame_cam, int64_t *n_eval, int64_t *n_masked,
+                   hipStream_t s)
 {
     const int64_t blocks = (b.n + kReduceRays - 1) / kReduceRays;
     cic_camera cam{};
     if (frame_cam) cam = *frame_cam;
     hipLaunchKernelGGL(k_reduce, dim3((unsigned)(blocks < 1 ? 1 : blocks)), dim3(256), 0, s, b, o, rgb, depth, acc,
-                       out_map, cam, frame_cam ? 1 : 0, (unsigned long long *)n_eval);
+                       out_map, cam, frame_cam ? 1 : 0, (unsigned long long *)n_eval, n_masked);
 }
 
 // Pixel rays; pixel index from pix (int64), pix32 (int32) or identity.

@@ -216,17 +216,29 @@ __global__ __launch_bounds__(256) void k_warp_resolve(int64_t np, const unsigned
     }
 }
 
+// Empty z-buffer, and no holes yet (n_holes nullable).
+__global__ __launch_bounds__(256) void k_warp_clear(ulonglong2 *zbuf, int64_t pairs, unsigned long long *last,
+                                                    uint32_t *n_holes)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < pairs) zbuf[i] = ulonglong2{~0ull, ~0ull};
+    if (i == 0) {
+        if (last) *last = ~0ull;
+        if (n_holes) *n_holes = 0u;
+    }
+}
+
 void launch_warp(const cic_camera &ref, const cic_camera &tgt, const float T[12], float cmin, const float *ref_rgb,
                  const float *ref_depth, uint64_t *zbuf, float *tgt_rgb, float *tgt_depth, uint8_t *mask,
                  int32_t *src_index, int32_t *hole_idx, uint32_t *n_holes, hipStream_t s)
 {
     const int64_t nt = (int64_t)tgt.width * tgt.height;
-    const int64_t nr = (int64_t)ref.width * ref.height;
     WarpT wt;
     for (int k = 0; k < 12; ++k) wt.m[k] = T[k];
-    launch_fill_u64(zbuf, ~0ull, nt, s);
-    if (n_holes) launch_fill_u32(n_holes, 0u, 1, s);
-    (void)nr;
+    // (the z-buffer is at least 256-byte aligned; one launch with the counter)
+    const int64_t pairs = nt / 2;
+    hipLaunchKernelGGL(k_warp_clear, dim3((unsigned)(pairs / 256 + 1)), dim3(256), 0, s, (ulonglong2 *)zbuf, pairs,
+                       (nt & 1) ? (unsigned long long *)zbuf + nt - 1 : nullptr, n_holes);
     const dim3 grid((unsigned)((ref.width + kSplatBlock - 1) / kSplatBlock),
                     (unsigned)((ref.height + kSplatBlock - 1) / kSplatBlock));
     hipLaunchKernelGGL(k_warp_splat, grid, dim3(kSplatBlock * kSplatBlock), 0, s, ref, tgt, wt, ref_depth,
@@ -235,16 +247,6 @@ void launch_warp(const cic_camera &ref, const cic_camera &tgt, const float T[12]
     hipLaunchKernelGGL(k_warp_resolve, dim3((unsigned)((nt + per_block - 1) / per_block)), dim3(256), 0, s, nt,
                        (const unsigned long long *)zbuf, ref, wt, cmin, ref_depth, ref_rgb, tgt_rgb, tgt_depth, mask,
                        src_index, hole_idx, n_holes);
-}
-
-__global__ void k_sparw_finish(const uint32_t *n_holes, int64_t *n_masked)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) *n_masked = (int64_t)*n_holes;
-}
-
-void launch_sparw_finish(const uint32_t *n_holes, int64_t *n_masked, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_sparw_finish, dim3(1), dim3(64), 0, s, n_holes, n_masked);
 }
 
 }  // namespace cic
