@@ -135,7 +135,9 @@ def _ptr(t):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle of the current device's current stream, without building
+    # a torch Stream object (2.8 us of every call)
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 # ---------------------------------------------------------------------------
