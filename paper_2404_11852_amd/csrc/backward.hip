@@ -350,7 +350,7 @@ constexpr int kAdjTPW = (kWgTiles + kAdjWaves - 1) / kAdjWaves;
 // puts the 64 lanes on 64 distinct banks (row stride 16 mod 64 words).
 constexpr int kAdjRow = kStDP1 + 128 + 24;
 static_assert(kAdjRow % 64 == 16, "adjoint LDS row stride");
-typedef F32Lds<true> AdjLds;                              // forward weights, W1 padded
+typedef F32Lds AdjLds;                                    // forward weights, W1 padded
 constexpr int kAOffW0T = AdjLds::kSize;                  // [c4 8][lane 64][4]
 constexpr int kAOffRows = kAOffW0T + 8 * 64 * 4;        // [16][kAdjRow]
 constexpr int kALds = kAOffRows + 16 * kAdjRow;
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
     GridK g, cic_mlp m, RenderBufs b, BackwardBufs bb)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    stage_weights_f32<true>(m, lds);
+    stage_weights_f32(m, lds);
     for (int i = threadIdx.x; i < 8 * 64 * 4; i += blockDim.x) {
         const int rr = i & 3, l = (i >> 2) & 63, c4 = i >> 8;
         const int col = l & 15;
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
         // adds nothing to the weight gradients and stores nothing
         const uint32_t rec = valid ? (uint32_t)s : 0u;
         float x[10];
-        sample_inputs<float, true>(g, b, rec, q, x);
+        sample_inputs(g, b, rec, q, x);
         // forward: layer 0 (40 -> 128), the same products in the same order
         // as the forward kernel's full-input path
         f4_t h1[8];

@@ -115,11 +115,6 @@ __device__ __forceinline__ void locate(const float x[3], const GridK &g, int i0[
     }
 }
 
-__device__ __forceinline__ int64_t cell_index(const GridK &g, const int i0[3])
-{
-    return ((int64_t)i0[0] * (g.r1 - 1) + i0[1]) * (int64_t)(g.r2 - 1) + i0[2];
-}
-
 __device__ __forceinline__ int64_t vertex_index(const GridK &g, int x, int y, int z)
 {
     return ((int64_t)x * g.r1 + y) * (int64_t)g.r2 + z;
@@ -241,30 +236,38 @@ __device__ __forceinline__ float density_at(const GridK &g, const int i0[3], con
     return lerpf(c0, c1, fr[0]);
 }
 
-// Cell of level l holding position x: lower vertex index (clamped to the
+// Cell, of N per axis, holding position x: lower vertex index (clamped to the
 // level's cells) and fraction inside it (float32 locate, as the dense grid's).
-__device__ __forceinline__ void hash_cell(const GridK &g, int l, const float x[3], int i0[3], float fr[3])
+__device__ __forceinline__ void hash_cell_n(const float lo[3], int N, const float scale[3], const float x[3], int i0[3],
+                                            float fr[3])
 {
-    const int N = g.hN[l];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const float u = (x[a] - g.lo[a]) * g.hscale[l][a];
-        int i = (int)floorf(u);
-        i = i < 0 ? 0 : i;
-        i = i > N - 1 ? N - 1 : i;
+        const float u = (x[a] - lo[a]) * scale[a];
+        const int i = min(max(floor_int(u), 0), N - 1);
         const float f = u - (float)i;
         fr[a] = clamp01_bits(f);
         i0[a] = i;
     }
 }
 
+// The same for level l.
+__device__ __forceinline__ void hash_cell(const GridK &g, int l, const float x[3], int i0[3], float fr[3])
+{
+    hash_cell_n(g.lo, g.hN[l], g.hscale[l], x, i0, fr);
+}
+
 // Table entry of vertex (vx, vy, vz) of level l: dense index on levels whose
 // (N+1)^3 vertices fit the table, spatial hash (XOR of the coordinates times
 // per-axis primes, modulo the table size) on the others.
+__device__ __forceinline__ uint32_t hash_entry_n(int N, int dense, uint32_t mask, uint32_t vx, uint32_t vy, uint32_t vz)
+{
+    const uint32_t n1 = (uint32_t)N + 1u;
+    return dense ? (vx * n1 + vy) * n1 + vz : (vx ^ (vy * 2654435761u) ^ (vz * 805459861u)) & mask;
+}
 __device__ __forceinline__ uint32_t hash_entry(const GridK &g, int l, uint32_t vx, uint32_t vy, uint32_t vz)
 {
-    const uint32_t n1 = (uint32_t)g.hN[l] + 1u;
-    return g.hdense[l] ? (vx * n1 + vy) * n1 + vz : (vx ^ (vy * 2654435761u) ^ (vz * 805459861u)) & g.hmask;
+    return hash_entry_n(g.hN[l], g.hdense[l], g.hmask, vx, vy, vz);
 }
 
 // Trilinear interpolation of a cell's 8 corner values v[c][f] (corner c =
@@ -313,52 +316,12 @@ __device__ __forceinline__ void hash_corners(const GridK &g, int l, const int i0
     }
 }
 
-// Features 3q .. 3q+2 of the dense 12-channel feature grid at cell i0.
-template <typename T>
-__device__ __forceinline__ void trilerp3(const T *feat, const GridK &g, const int i0[3], const float fr[3], int q,
-                                         float out[3])
-{
-    const int64_t sx = (int64_t)g.r1 * g.r2, sy = g.r2;
-    const int64_t b = vertex_index(g, i0[0], i0[1], i0[2]);
-    float v[8][3];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const int64_t vtx = b + ((c >> 2) & 1) * sx + ((c >> 1) & 1) * sy + (c & 1);
-        load_entry3(feat, (uint64_t)(4 * vtx + q), v[c]);
-    }
-    lerp3_corners(v, fr, out);
-}
-
-// One level of the multi-level encoding at position x: 3 features,
-// trilinear over the level's cell.
-template <typename T>
-__device__ __forceinline__ void hash_level3(const GridK &g, int l, const float x[3], float out[3])
-{
-    int i0[3];
-    float fr[3], v[8][3];
-    hash_cell(g, l, x, i0, fr);
-    hash_corners<T>(g, l, i0, v);
-    lerp3_corners(v, fr, out);
-}
-
 __device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 // --------------------------------------------------------------------------
 // wavefront primitives
 // --------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
-
-// Inclusive prefix sum across the 64 lanes (Hillis-Steele).
-__device__ __forceinline__ float wave_incl_scan(float v)
-{
-    const int l = lane_id();
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        float u = __shfl_up(v, off, kWave);
-        if (l >= off) v += u;
-    }
-    return v;
-}
 
 // Sum across the wave; every lane gets the identical value.
 __device__ __forceinline__ float wave_sum(float v)

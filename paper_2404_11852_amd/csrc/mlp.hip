@@ -61,13 +61,6 @@ constexpr int kXB2 = kXW2 + 512, kXFloats = kXB2 + 4;
 constexpr int kXLdsBytes = kXFrags * 16 + kXFloats * 4;
 constexpr float kLoScale = 2048.f;               // the low parts are kept times 2^11
 
-// hidden unit of slot e of chunk c (16 units) for lane half h: the rows that
-// the lane half holds of the 32-row result tile c / 2
-__host__ __device__ __forceinline__ int x_hid(int c, int h, int e)
-{
-    return 16 * c + 8 * (e >> 2) + 4 * h + (e & 3);
-}
-
 // v0, v1 into a float16 and a second float16 that holds the remainder times
 // 2^11 (the remainder is exact in float32; times 2^11 it is a normal float16
 // wherever the first part is)
@@ -258,89 +251,6 @@ void launch_ray_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s)
     else launch_embed<64>(m, b, s);
 }
 
-// Features 6h .. 6h+5 of one sample (lane half h): issue() sends the loads of
-// the 8 corners, feature() interpolates one of them, in two steps so that a
-// batch's work fits between the loads and their use.  Dense grids: corner c
-// (x bit 2, y bit 1, z bit 0), 6 consecutive channels.  Multi-level encoding:
-// levels 2h and 2h + 1, 3 features each.
-template <typename T, bool HASH>
-struct Gather {
-    static constexpr bool kHalf = sizeof(T) == 2;
-    static constexpr int kWords = kHalf ? (HASH ? 4 : 3) : 6;   // 32-bit words per corner
-    uint32_t raw[8][kWords];
-    float fr[HASH ? 2 : 1][3];
-    uint32_t odd;   // float16 tables: parity of each entry, bit 8 * level + corner
-
-    __device__ __forceinline__ void issue(const GridK &g, const SampleRay &r, int h)
-    {
-        if constexpr (HASH) {
-            float xp[3];
-            sample_position(r, xp);
-            odd = 0;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int l = 2 * h + u;
-                int i0[3];
-                hash_cell(g, l, xp, i0, fr[u]);
-                const T *tab = (const T *)g.htab + (size_t)l * ((size_t)g.hmask + 1) * 3;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const uint64_t e = hash_entry(g, l, (uint32_t)(i0[0] + ((c >> 2) & 1)),
-                                                  (uint32_t)(i0[1] + ((c >> 1) & 1)), (uint32_t)(i0[2] + (c & 1)));
-                    if constexpr (kHalf) {
-                        // the two aligned words that hold the entry's 6 bytes (see load_entry3)
-                        const uint32_t *w = (const uint32_t *)((const char *)tab + ((e * 6) & ~(uint64_t)3));
-                        raw[c][2 * u] = w[0];
-                        raw[c][2 * u + 1] = w[1];
-                        odd |= ((uint32_t)e & 1u) << (8 * u + c);
-                    } else {
-                        const uint32_t *w = (const uint32_t *)tab + e * 3;
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) raw[c][3 * u + k] = w[k];
-                    }
-                }
-            }
-        } else {
-            int i0[3];
-            float tk;
-            sample_voxel(r.o, r.d, r.tn, r.delta, r.k, g, i0, fr[0], tk);
-            constexpr int kRec = 12 * (int)sizeof(T);
-            const int64_t sy = (int64_t)g.r2 * kRec, sx = (int64_t)g.r1 * sy;
-            const char *p = (const char *)g.features + vertex_index(g, i0[0], i0[1], i0[2]) * kRec + h * (kRec / 2);
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const uint32_t *w =
-                    (const uint32_t *)(p + ((c >> 2) & 1) * sx + ((c >> 1) & 1) * sy + (c & 1) * kRec);
-#pragma unroll
-                for (int k = 0; k < kWords; ++k) raw[c][k] = w[k];
-            }
-        }
-    }
-
-    __device__ __forceinline__ float value(int c, int k) const
-    {
-        if constexpr (!kHalf) {
-            return __uint_as_float(raw[c][k]);
-        } else if constexpr (!HASH) {
-            const uint32_t w = raw[c][k >> 1];
-            return __half2float(__ushort_as_half((unsigned short)((k & 1) ? w >> 16 : w & 0xffffu)));
-        } else {
-            const int u = k / 3, f = k % 3;
-            const uint32_t a = raw[c][2 * u], b = raw[c][2 * u + 1], sh = ((odd >> (8 * u + c)) & 1u) * 16u;
-            const uint32_t w = f < 2 ? __builtin_amdgcn_alignbit(b, a, sh) : b >> sh;
-            return __half2float(__ushort_as_half((unsigned short)(f == 1 ? w >> 16 : w & 0xffffu)));
-        }
-    }
-
-    __device__ __forceinline__ float feature(int k) const
-    {
-        const float *f = fr[HASH ? k / 3 : 0];
-        const float c00 = lerpf(value(0, k), value(1, k), f[2]), c01 = lerpf(value(2, k), value(3, k), f[2]);
-        const float c10 = lerpf(value(4, k), value(5, k), f[2]), c11 = lerpf(value(6, k), value(7, k), f[2]);
-        return lerpf(lerpf(c00, c01, f[1]), lerpf(c10, c11, f[1]), f[0]);
-    }
-};
-
 // The colour of one sample on the vector ALUs in float32, by a whole
 // wavefront (lane l holds hidden units l and l + 64): for the samples whose
 // features or activations leave the range in which the split is exact.
@@ -351,7 +261,9 @@ __device__ void redo_sample(const GridK &g, const cic_mlp &m, const RenderBufs &
     SampleRay r;
     load_sample_ray(b, b.rec_ray[rec], b.rec_k[rec], r);
     Gather<T, HASH> gt;
-    gt.issue(g, r, lane & 1);
+    float xp[3];
+    sample_position(r, xp);
+    gt.issue(g, xp, lane & 1);
     float x[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) x[k] = gt.feature(k);
@@ -375,19 +287,6 @@ __device__ void redo_sample(const GridK &g, const cic_mlp &m, const RenderBufs &
         const float p = wave_sum(fmaf(m.w2[ch * 128 + lane], relu_bits(h2[0]),
                                       m.w2[ch * 128 + 64 + lane] * relu_bits(h2[1])));
         if (lane == ch) b.rec_c[3 * rec + ch] = sigmoid_hw(p + m.b2[ch]);
-    }
-}
-
-// Alternates the instructions before it, back to the last barrier: one MFMA,
-// then up to 8 vector and a few memory instructions that fit in its shadow.
-__device__ __forceinline__ void interleave_mfma()
-{
-#pragma unroll
-    for (int u = 0; u < 3; ++u) {
-        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads
-        __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);     // vector ALU
-        __builtin_amdgcn_sched_group_barrier(0x20, 4, 0);    // global loads
     }
 }
 
@@ -434,7 +333,11 @@ k_mlp_fwd_f32(GridK g, cic_mlp m, RenderBufs b, int voxel)
         SampleRay cur;
         load_sample_ray(b, b.rec_ray[crec], b.rec_k[crec], cur);
         Gather<T, HASH> gt;
-        gt.issue(g, cur, h);
+        {
+            float xp[3];
+            sample_position(cur, xp);
+            gt.issue(g, xp, h);
+        }
         // the features and, once split, their parts: pair k in xhi[k] and xlo[k]
         float x[6];
         uint32_t xhi[3], xlo[3];
@@ -585,10 +488,14 @@ k_mlp_fwd_f32(GridK g, cic_mlp m, RenderBufs b, int voxel)
                     // an activation beyond float16's range makes every low sum of its sample infinite or NaN
                     if (t == 1 && c == 1) cbad = cbad || !(fabsf(accl[0][0]) < INFINITY);
                     if (t > 0 && (c & 1)) output_rows(t - 1, c >> 1);
-                    if (t == 2 && c == 2) gt.issue(g, cur, h);
+                    if (t == 2 && c == 2) {
+                        float xp[3];
+                        sample_position(cur, xp);
+                        gt.issue(g, xp, h);
+                    }
                     if (t == 3 && c >= 1 && c < 7) x[c - 1] = gt.feature(c - 1);
                     if (t == 3 && c == 7) split_features();
-                    interleave_mfma();
+                    interleave_mfma<3>();
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }

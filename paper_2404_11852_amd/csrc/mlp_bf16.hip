@@ -5,26 +5,35 @@
 
 namespace cic {
 
-// BF16 compute: lane group q's seven view-encoding inputs of every ray with
-// live samples, rounded to BF16 (the rounding the MLP kernel applies to its
-// inputs) and packed as 8 BF16 (last slot 0) into words 4q..4q+3 of the ray.
+// BF16 compute: the view-encoding inputs of every ray with live samples,
+// rounded to BF16 (the rounding the MLP kernel applies to its inputs).  Row of
+// a ray: for each lane half 15 values and a zero; half 0: the direction and
+// the 12 sines, half 1: the 12 cosines and three ones (layer 0's bias).  Four
+// threads per ray, three encoding arguments each.
+typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void k_ray_encode_bf16(RenderBufs b)
 {
+    __shared__ __attribute__((aligned(16))) __bf16 rows[64][32];   // stored 16 bytes per thread
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t ray = t >> 2;
     const int q = (int)(t & 3);
-    if (ray >= b.n || b.count[ray] == 0) return;
-    float d[3], x[7];
+    const bool live = ray < b.n && b.count[ray] != 0;
+    __bf16 *row = rows[threadIdx.x >> 2];
+    if (live) {
+        float d[3], x[7];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) d[a] = b.rays_d[3 * ray + a];
-    encode_group(d, q, x);
-    typedef __bf16 bf8v_t __attribute__((ext_vector_type(8)));
-    bf8v_t v;
+        for (int a = 0; a < 3; ++a) d[a] = b.rays_d[3 * ray + a];
+        encode_group(d, q, x);
+        row[q < 3 ? q : 15] = (__bf16)x[0];   // (the fourth thread's is the pad, 0)
 #pragma unroll
-    for (int e = 0; e < 7; ++e) v[e] = (__bf16)x[e];
-    v[7] = (__bf16)1.0f;   // the constant input of layer 0's bias
-    typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-    *(u4_t *)(b.enc + ray * 16 + 4 * q) = __builtin_bit_cast(u4_t, v);
+        for (int k = 0; k < 3; ++k) {
+            row[3 + 3 * q + k] = (__bf16)x[1 + 2 * k];
+            row[16 + 3 * q + k] = (__bf16)x[2 + 2 * k];
+        }
+        row[16 + 12 + q] = (__bf16)(q < 3 ? 1.0f : 0.0f);
+    }
+    __syncthreads();
+    if (live) *(u4_t *)(b.enc + ray * 16 + 4 * q) = *(const u4_t *)(row + 8 * q);
 }
 
 void launch_ray_encode_bf16(const RenderBufs &b, hipStream_t s)
@@ -45,29 +54,14 @@ void launch_ray_encode_bf16(const RenderBufs &b, hipStream_t s)
 // dependent loads that locate a sample (its record, its ray, the ray's
 // origin and direction) are issued by the whole workgroup at once.
 // ---------------------------------------------------------------------------
-// Launch shape (measured on the 8-view workload, MLP stage): a BF16 MFMA does
-// a 16-sample tile's layer in 1/16 of the FP32 time, so each batch carries
-// little MFMA work against its dependent gather loads and its weight reads
-// from LDS; 16 wavefronts per CU (a 128-VGPR budget each) with two tiles per
-// batch hide the loads best and read each weight fragment for 32 samples
-// (43.3 ms; 4 waves x 3 workgroups x 2 tiles 56.6 ms, 16 x 1 x 1 tile 44.4 ms;
-// later, with the layers converted pair by pair: 3 tiles x 12 waves 23.95 and
-// 4 tiles x 8 waves 25.2 against 23.54 ms).
-#ifndef CIC_BF_NT
-#define CIC_BF_NT 2
-#endif
-
-#ifndef CIC_BF_WAVES
-#define CIC_BF_WAVES 16
-#endif
-#ifndef CIC_BF_WGS
-#define CIC_BF_WGS 1
-#endif
-constexpr int kBfWaves = CIC_BF_WAVES;   // wavefronts per workgroup
-constexpr int kBfWgs = CIC_BF_WGS;       // workgroups per CU (each holds its own 53 KB of LDS weights)
-constexpr int kBfNT = CIC_BF_NT;         // 16-sample tiles per wavefront batch
-constexpr int kBfBatch = 16 * kBfNT;
-constexpr int kTileThreads = kBfWaves * 64;   // threads of a workgroup of the LDS-tile kernels
+// Launch shapes.  The gathering kernel (ray order): 8 wavefronts per CU (two
+// per SIMD), 64 samples per batch, the next batch's gather among this batch's
+// MFMAs.  The brick kernels: 16 wavefronts of 32 samples, whose batches come
+// from LDS and are short between the segments' barriers.
+constexpr int kRayWaves8 = 8;
+constexpr int kBfWaves = 16;                  // wavefronts per workgroup of the brick kernels
+constexpr int kBfBatch = 32;                  // samples per wavefront batch there
+constexpr int kTileThreads = kBfWaves * 64;   // threads of a workgroup there
 
 constexpr int kFTileV = kBrick + 1;
 // Brick tile: channel ch of vertex (lx, ly, lz) at
@@ -449,48 +443,33 @@ __device__ __forceinline__ void hash_level3_tiled(const GridK &g, const LevelTil
 }
 
 // ---------------------------------------------------------------------------
-// BF16 variant: every layer on v_mfma_f32_16x16x32_bf16 (inputs rounded to
-// BF16 with round-to-nearest-even, FP32 accumulation, FP32 bias and
-// activations).  K = 32 per instruction: lane (q, j) supplies 8 consecutive
-// reduction slots.  Layer 0 uses two K-chunks (64 slots >= 39 inputs, same
-// per-lane input assignment as the FP32 kernel: the ten values of lane group
-// q fill chunk 0 and the first two slots of chunk 1).  Its bias rides in
-// the third slot of chunk 1 of lane groups 0-2: the per-ray encoding row
-// carries a constant 1 there, and the weights hold the three BF16 parts of
-// the float32 bias, whose sum is the bias exactly, so the layer reads no
-// bias from LDS.  Layers 1 and 2 take
-// their B operand from two consecutive 16-row result tiles of the previous
-// layer: chunk c of lane group q covers rows 32c + 4q + (0..3) and
-// 32c + 16 + 4q + (0..3), and the weight fragments are laid out to match.
-// The 3-wide output layer is one zero-padded 16-row tile.
+// Layers.  Inputs and activations are rounded to BF16 (round to nearest even),
+// products accumulate in FP32 on v_mfma_f32_32x32x16_bf16, 32 samples on the N
+// axis: lane (h, j) holds rows 8 (r / 4) + 4 h + r % 4 of sample j's 32-row
+// result tile and supplies 8 of a chunk's 16 reduction slots, so a result tile
+// becomes two input chunks of the next layer once the weights' columns are
+// permuted alike.  Layer 0 takes 24 slots per lane half: features 6h .. 6h+5,
+// the half's 15 encoding values and 3 pads.  Its bias rides on the encoding's
+// three ones: the weights hold the three BF16 parts of the float32 bias, whose
+// sum is the bias exactly, so the layer reads no bias from LDS.  The 3-wide
+// output layer runs on 4x4x4 MFMA, whose B operand is four activations of the
+// lane's own sample.  Every kernel below runs the same sums in the same order
+// for a sample, so ray and voxel order give the same bits.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 
+typedef float f16_t __attribute__((ext_vector_type(16)));
+typedef short s4_t __attribute__((ext_vector_type(4)));
+
 // LDS layout in 16-byte fragments, then floats
-constexpr int kBfW0 = 0;                           // [t 8][c 2][lane 64]
-constexpr int kBfW1 = kBfW0 + 8 * 2 * 64;          // [t 8][c 4][lane 64]
-constexpr int kBfW2 = kBfW1 + 8 * 4 * 64;          // [c 4][lane 64]
-constexpr int kBfFrags = kBfW2 + 4 * 64;
+constexpr int kBfW0 = 0;                           // [t 4][c 3][lane 64]
+constexpr int kBfW1 = kBfW0 + 4 * 3 * 64;          // [t 4][c 8][lane 64]
+constexpr int kBfW2 = kBfW1 + 4 * 8 * 64;          // [t 4][i 4][h 2][ch 4] of 4 BF16
+constexpr int kBfFrags = kBfW2 + 4 * 4 * 2 * 4 / 2;
 constexpr int kBfB1 = 0, kBfB2 = 128, kBfFloats = 132;
 constexpr int kLdsBf16 = kBfFrags * 16 + kBfFloats * 4;
 static_assert(kLdsBf16 + (kFTileFloats + kSegWords) * 4 <= 160 * 1024 - 1024, "brick tile kernel LDS");
-
-// reduction index of slot e of chunk c for lane group q in layers 1 and 2
-__host__ __device__ __forceinline__ int hid_k(int c, int q, int e)
-{
-    return e < 4 ? 32 * c + 4 * q + e : 32 * c + 16 + 4 * q + (e - 4);
-}
-
-// input index of slot e of chunk c for lane group q in layer 0 (-1 = pad)
-__host__ __device__ __forceinline__ int bf_l0_input(int c, int q, int e)
-{
-    const int slot = 8 * c + e;
-    return slot < 10 ? l0_input(slot, q) : -1;
-}
-
-// slot of chunk 1 (lane groups 0-2) that carries layer 0's bias: input 1.0
-// (encoding slot 7), weight the group's part of the bias
-constexpr int kBfBiasSlot = 2;
+static_assert(kLdsBf16 + kHSegWords * 4 + kHTileBytes <= 160 * 1024 - 2048, "level box kernel LDS");
 
 // part p of float32 b split into three BF16 values b0 + b1 + b2 = b (each
 // remainder is exact in float32, and the last has at most 8 significant bits)
@@ -501,234 +480,427 @@ __device__ __forceinline__ float bf16_part(float b, int p)
     return p == 0 ? hi : p == 1 ? mid : r2;
 }
 
+// (every load goes out before the first conversion: a small launch waits for
+// one round trip to memory here)
+template <int THREADS>
 __device__ void stage_weights_bf16(const cic_mlp &m, bf8_t *frag, float *fl)
 {
-    const int nt = blockDim.x;
-    for (int i = threadIdx.x; i < 8 * 2 * 64; i += nt) {
-        const int l = i & 63, c = (i >> 6) & 1, t = i >> 7;
-        const int row = 16 * t + (l & 15), q = l >> 4;
+    constexpr int kN0 = 4 * 3 * 64, kIt0 = (kN0 + THREADS - 1) / THREADS, kN1 = 4 * 8 * 64, kIt1 = kN1 / THREADS;
+    static_assert(kN1 % THREADS == 0 && THREADS >= 512, "whole rounds of W1 fragments, one W2 entry per thread");
+    const int tid = threadIdx.x;
+    float w0[kIt0][8], w1[kIt1][8], b0[kIt0];
+#pragma unroll
+    for (int k = 0; k < kIt1; ++k) {
+        const int i = tid + k * THREADS, l = i & 63, c = (i >> 6) & 7, t = i >> 9;
+        const float *src = m.w1 + (32 * t + (l & 31)) * 128;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w1[k][4 * u + e] = src[x_hid(c, l >> 5, 4 * u) + e];
+    }
+#pragma unroll
+    for (int k = 0; k < kIt0; ++k) {
+        const int i = min(tid + k * THREADS, kN0 - 1), l = i & 63, c = (i >> 6) % 3, t = i / 192;
+        const int row = 32 * t + (l & 31), h = l >> 5;
+        b0[k] = m.b0[row];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int s = 8 * c + e;   // slot: features, then encoding values 15h + s - 6
+            w0[k][e] = m.w0[row * 39 + (s < 6 ? 6 * h + s : 12 + min(15 * h + s - 6, 26))];
+        }
+    }
+    const int ch2 = (tid >> 2) & 3, h2 = (tid >> 4) & 1;
+    const int row2 = 32 * ((tid >> 7) & 3) + 8 * ((tid >> 5) & 3) + 4 * h2 + (tid & 3);
+    const float v2 = m.w2[min(ch2, 2) * 128 + row2], vb1 = m.b1[tid & 127], vb2 = m.b2[min(tid & 3, 2)];
+#pragma unroll
+    for (int k = 0; k < kIt1; ++k) {
+        bf8_t v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (__bf16)w1[k][e];
+        frag[kBfW1 + tid + k * THREADS] = v;
+    }
+#pragma unroll
+    for (int k = 0; k < kIt0; ++k) {
+        const int i = tid + k * THREADS, l = i & 63, c = (i >> 6) % 3, h = l >> 5;
         bf8_t v;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int src = bf_l0_input(c, q, e);
-            float w = src >= 0 ? m.w0[row * 39 + src] : 0.f;
-            if (c == 1 && e == kBfBiasSlot) w = q < 3 ? bf16_part(m.b0[row], q) : 0.f;   // exact in BF16
-            v[e] = (__bf16)w;
+            const int s = 8 * c + e, part = 15 * h + s - 6 - 27;
+            const float w = s >= 6 && part >= 0 ? bf16_part(b0[k], part) : w0[k][e];   // the bias's parts are exact
+            v[e] = (__bf16)(s < 21 ? w : 0.f);
         }
-        frag[kBfW0 + i] = v;
+        if (i < kN0) frag[kBfW0 + i] = v;
     }
-    for (int i = threadIdx.x; i < 8 * 4 * 64; i += nt) {
-        const int l = i & 63, c = (i >> 6) & 3, t = i >> 8;
-        const int row = 16 * t + (l & 15), q = l >> 4;
-        bf8_t v;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (__bf16)m.w1[row * 128 + hid_k(c, q, e)];
-        frag[kBfW1 + i] = v;
-    }
-    for (int i = threadIdx.x; i < 4 * 64; i += nt) {
-        const int l = i & 63, c = i >> 6;
-        const int row = l & 15, q = l >> 4;
-        bf8_t v;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (__bf16)(row < 3 ? m.w2[row * 128 + hid_k(c, q, e)] : 0.f);
-        frag[kBfW2 + i] = v;
-    }
-    for (int i = threadIdx.x; i < 128; i += nt) fl[kBfB1 + i] = m.b1[i];
-    if (threadIdx.x < 4) fl[kBfB2 + threadIdx.x] = threadIdx.x < 3 ? m.b2[threadIdx.x] : 0.f;
+    if (tid < 512) ((__bf16 *)(frag + kBfW2))[tid] = (__bf16)(ch2 < 3 ? v2 : 0.f);
+    if (tid < 128) fl[kBfB1 + tid] = vb1;
+    if (tid < 4) fl[kBfB2 + tid] = tid < 3 ? vb2 : 0.f;
 }
 
-__device__ __forceinline__ bf8_t pack_bf8(const f4_t a, const f4_t b)
+__device__ __forceinline__ uint32_t pack_bf2(float a, float b)
 {
-    bf8_t v;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        v[e] = (__bf16)a[e];
-        v[4 + e] = (__bf16)b[e];
-    }
-    return v;
+    typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+    bf2_t v;
+    v[0] = (__bf16)a;
+    v[1] = (__bf16)b;
+    return __builtin_bit_cast(uint32_t, v);
 }
 
 // ReLU of BF16 values as 16-bit integers: a negative BF16 (sign bit set) is
 // a negative int16, so max(bits, 0) zeroes exactly the negatives (and -0).
 // Rounding to BF16 preserves sign, so this equals rounding after the ReLU.
-typedef short s8_t __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ bf8_t relu_bf8(bf8_t v)
+__device__ __forceinline__ uint32_t relu_bf2(uint32_t v)
 {
-    s8_t s = __builtin_bit_cast(s8_t, v);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s[e] = s[e] > 0 ? s[e] : (short)0;
-    return __builtin_bit_cast(bf8_t, s);
+    typedef short s2_t __attribute__((ext_vector_type(2)));
+    s2_t s = __builtin_bit_cast(s2_t, v);
+    s[0] = s[0] > 0 ? s[0] : (short)0;
+    s[1] = s[1] > 0 ? s[1] : (short)0;
+    return __builtin_bit_cast(uint32_t, s);
 }
 
-// TILE: 0 = gathers from the grid (ray order, or voxel order through the
-// sample permutation); 1 = voxel order with the brick's features staged in
-// LDS (dense grids); 2 = voxel order with the segment's multi-level encoding
-// boxes staged in LDS.
+// rows r .. r + 3 of a result tile as four BF16 activations
+__device__ __forceinline__ void act4(const f16_t &a, int r, uint32_t &lo, uint32_t &hi)
+{
+    lo = relu_bf2(pack_bf2(a[r], a[r + 1]));
+    hi = relu_bf2(pack_bf2(a[r + 2], a[r + 3]));
+}
+
+// The network on NT groups of 32 samples; a wavefront's working set.
+template <int NT>
+struct BfNet {
+    const bf8_t *w0f, *w1f;
+    const s4_t *w2f;
+    const float *b1;
+    f16_t acc[2][NT];    // a result tile and the one before it
+    bf8_t hb[NT][8];     // the first hidden layer's activations
+    f4_t out[NT][2];     // channels 0..2 in rows 0..2, even and odd row groups
+
+    __device__ __forceinline__ BfNet(const bf8_t *frag, const float *fl, int lane)
+        : w0f(frag + kBfW0 + lane), w1f(frag + kBfW1 + lane),
+          w2f((const s4_t *)(frag + kBfW2) + (lane >> 5) * 4 + (lane & 3)), b1(fl + kBfB1 + 4 * (lane >> 5))
+    {
+    }
+    // layer 0, tile t (xin: features and encoding in three chunks)
+    __device__ __forceinline__ void layer0(int t, const bf8_t (&xin)[NT][3])
+    {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const bf8_t a = w0f[(t * 3 + c) * 64];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                if (c == 0)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[t & 1][nt][r] = 0.f;
+                acc[t & 1][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xin[nt][c], acc[t & 1][nt], 0, 0, 0);
+            }
+        }
+    }
+    // ReLU and rounding of tile t: input chunks 2t, 2t + 1 of layer 1
+    __device__ __forceinline__ void activate(int t)
+    {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                uint32_t w[4];
+                act4(acc[t & 1][nt], 8 * hh, w[0], w[1]);
+                act4(acc[t & 1][nt], 8 * hh + 4, w[2], w[3]);
+                hb[nt][2 * t + hh] = __builtin_bit_cast(bf8_t, u4_t{w[0], w[1], w[2], w[3]});
+            }
+    }
+    // layer 1, tile t, chunk c
+    __device__ __forceinline__ void layer1(int t, int c, const bf8_t a)
+    {
+        if (c == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f4_t z = *(const f4_t *)(b1 + 32 * t + 8 * i);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[t & 1][nt][4 * i + r] = z[r];
+            }
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            acc[t & 1][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, hb[nt][c], acc[t & 1][nt], 0, 0, 0);
+    }
+    // rows 4i .. 4i + 3 of tile t into the output layer
+    __device__ __forceinline__ void output(int t, int i)
+    {
+        const s4_t w = w2f[(4 * t + i) * 8];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            uint32_t lo, hi;
+            act4(acc[t & 1][nt], 4 * i, lo, hi);
+            typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
+            const f4_t z = f4_t{0.f, 0.f, 0.f, 0.f};
+            out[nt][i & 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(w, __builtin_bit_cast(s4_t, u2_t{lo, hi}),
+                                                                     t == 0 && i < 2 ? z : out[nt][i & 1], 0, 0, 0);
+        }
+    }
+    __device__ __forceinline__ float logit(int nt, int ch, float b2) const
+    {
+        float p = out[nt][0][ch] + out[nt][1][ch];
+        p += __shfl_xor(p, 32, kWave);
+        return p + b2;
+    }
+};
+
+// layer 0's input chunks of a sample: its 6 features and its ray's half row
+__device__ __forceinline__ void bf_inputs(const float x[6], const u4_t e0, const u4_t e1, bf8_t xin[3])
+{
+    xin[0] = __builtin_bit_cast(bf8_t, u4_t{pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3]), pack_bf2(x[4], x[5]), e0[0]});
+    xin[1] = __builtin_bit_cast(bf8_t, u4_t{e0[1], e0[2], e0[3], e1[0]});
+    xin[2] = __builtin_bit_cast(bf8_t, u4_t{e1[1], e1[2], e1[3], 0u});
+}
+
+// Samples gathered from the grid or the tables: ray order, or voxel order
+// through the permutation.  Persistent, one workgroup per CU; its wavefronts
+// claim batches of 64 samples from an LDS counter.  As in the FP32 kernel, the
+// next batch's records, gathers and interpolation sit between this batch's
+// layer-1 MFMAs; 64 samples share each weight fragment read from LDS, which 32
+// would read at the LDS's full rate.  800x800 frame over a float16 grid with 36
+// M live samples: 2.36 -> 1.77 ms (the matrix power limit of the 46,000
+// operations per sample that the padded tiles execute is 1.43 ms), multi-level
+// encoding 2.45 -> 2.16 ms.  The brick kernel with the same 32-row tiles: 5.04
+// -> 4.90 ms per 2^21 rays of eight views, its own power limit being 4.7 ms.
+template <typename T, bool HASH>
+__global__ __launch_bounds__(kRayWaves8 * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+k_mlp_fwd_bf16_gather(GridK g, cic_mlp m, RenderBufs b, int voxel)
+{
+    constexpr int NT = 2, kBatch = 32 * NT;
+    extern __shared__ __attribute__((aligned(16))) float lds_raw[];   // 16-byte fragments
+    __shared__ uint32_t claimed;
+    bf8_t *frag = (bf8_t *)lds_raw;
+    float *fl = lds_raw + kBfFrags * 4;
+    stage_weights_bf16<kRayWaves8 * 64>(m, frag, fl);
+    if (threadIdx.x == 0) claimed = kRayWaves8;
+    __syncthreads();
+
+    const int lane = lane_id(), h = lane >> 5, j = lane & 31;
+    const uint32_t total = b.offsets[b.n];
+    const BatchRange br = xcd_batches(((int64_t)total + kBatch - 1) / kBatch, kRayWaves8, 0);
+    const uint32_t bfirst = (uint32_t)br.first, bstride = (uint32_t)br.stride;
+    const uint32_t bcount = br.end > br.first ? (uint32_t)(br.end - br.first) : 0u;   // relative to bfirst
+    auto batch_of = [&](uint32_t k) -> uint32_t { return (k / kRayWaves8) * bstride + k % kRayWaves8; };
+    // (a lane past the last sample works on sample 0: in-bounds inputs, no
+    // branches around the loads; its colour is not stored)
+    auto record_of = [&](uint32_t bt, int nt) -> uint32_t {
+        const uint32_t s = (bfirst + bt) * kBatch + 32 * nt + j;
+        const uint32_t sv = bt < bcount && s < total ? s : 0;
+        return voxel ? b.perm[sv] : sv;
+    };
+    uint32_t bt = batch_of(threadIdx.x / kWave);
+    if (bt >= bcount) return;
+
+    BfNet<NT> net(frag, fl, lane);
+    const f4_t b2 = *(const f4_t *)(fl + kBfB2);
+    uint32_t crec[NT], nrec[NT], nray[NT];
+    int nk[NT];
+    float xp[NT][3];
+    Gather<T, HASH> gt;
+    float x[6];
+    bf8_t xin[NT][3];
+    u4_t enc[NT][2];
+    auto load_enc = [&](int nt, uint32_t ray) {
+        const u4_t *e = (const u4_t *)(b.enc + (int64_t)ray * 16 + 8 * h);
+        enc[nt][0] = e[0];
+        enc[nt][1] = e[1];
+    };
+    auto position = [&](int nt, uint32_t ray, int k) {
+        SampleRay r;
+        load_sample_ray(b, ray, k, r);
+        sample_position(r, xp[nt]);
+    };
+    auto inputs = [&](int nt) {
+        bf_inputs(x, enc[nt][0], enc[nt][1], xin[nt]);
+        // (keeps the interpolation here, among the MFMAs, and not moved down
+        // to its use)
+        asm volatile("" : "+v"(xin[nt][0]));
+    };
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        crec[nt] = record_of(bt, nt);
+        const uint32_t ray = b.rec_ray[crec[nt]];
+        position(nt, ray, b.rec_k[crec[nt]]);
+        load_enc(nt, ray);
+        gt.issue(g, xp[nt], h);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) x[k] = gt.feature(k);
+        inputs(nt);
+    }
+    for (;;) {
+        uint32_t claim = 0;
+        if (lane == 0) claim = atomicAdd(&claimed, 1u);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t <= 4; ++t) {
+            if (t < 4) net.layer0(t, xin);
+            if (t > 0) net.activate(t - 1);
+            interleave_mfma<6>();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const uint32_t nbt = batch_of(__builtin_amdgcn_readfirstlane(claim));
+        bf8_t a = net.w1f[0];
+        static_for<32>([&](auto step) {
+            constexpr int t = step / 8, c = step % 8;
+            const bf8_t an = net.w1f[(step + 1 < 32 ? step + 1 : step) * 64];
+            net.layer1(t, c, a);
+            a = an;
+            // what else happens during these MFMAs
+            if constexpr (t > 0 && (c & 1)) net.output(t - 1, c >> 1);
+            if constexpr (t == 0 && c == 0) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) nrec[nt] = record_of(nbt, nt);
+            }
+            if constexpr (t == 0 && c == 2) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    nray[nt] = b.rec_ray[nrec[nt]];
+                    nk[nt] = b.rec_k[nrec[nt]];
+                }
+            }
+            if constexpr (t == 1 && c == 0) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    position(nt, nray[nt], nk[nt]);
+                    load_enc(nt, nray[nt]);
+                }
+            }
+            if constexpr (t == 1 && c == 6) gt.issue(g, xp[0], h);
+            if constexpr (t == 2 && c >= 2 && c < 5) {
+                x[2 * (c - 2)] = gt.feature(2 * (c - 2));
+                x[2 * (c - 2) + 1] = gt.feature(2 * (c - 2) + 1);
+            }
+            if constexpr (t == 2 && c == 5) {
+                inputs(0);
+                gt.issue(g, xp[1], h);
+            }
+            if constexpr (t == 3 && c >= 3 && c < 6) {
+                x[2 * (c - 3)] = gt.feature(2 * (c - 3));
+                x[2 * (c - 3) + 1] = gt.feature(2 * (c - 3) + 1);
+            }
+            if constexpr (t == 3 && c == 6) inputs(1);
+            interleave_mfma<NT>();
+            __builtin_amdgcn_sched_barrier(0);
+        });
+#pragma unroll
+        for (int i = 0; i < 4; ++i) net.output(3, i);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const float p0 = net.logit(nt, 0, b2[0]), p1 = net.logit(nt, 1, b2[1]), p2 = net.logit(nt, 2, b2[2]);
+            if ((bfirst + bt) * kBatch + 32 * nt + j < total && h == 0) {
+                float *out = b.rec_c + 3 * (int64_t)crec[nt];
+                out[0] = sigmoid_hw(p0);
+                out[1] = sigmoid_hw(p1);
+                out[2] = sigmoid_hw(p2);
+            }
+            crec[nt] = nrec[nt];
+        }
+        if (nbt >= bcount) return;
+        bt = nbt;
+    }
+}
+
+// TILE: 1 = voxel order with the brick's features staged in LDS (dense
+// grids); 2 = voxel order with the segment's multi-level encoding boxes
+// staged in LDS.
 template <typename T, int TILE>
-__global__ __launch_bounds__(kBfWaves * 64) void k_mlp_fwd_bf16(GridK g, cic_mlp m, RenderBufs b, int voxel)
+__global__ __launch_bounds__(kBfWaves * 64) void k_mlp_fwd_bf16(GridK g, cic_mlp m, RenderBufs b)
 {
     typedef typename HashVtx<T>::type HV;
     extern __shared__ __attribute__((aligned(16))) float lds_raw[];   // 16-byte fragments
     bf8_t *frag = (bf8_t *)lds_raw;
     float *fl = lds_raw + kBfFrags * 4;
     float *tile = lds_raw + kBfFrags * 4 + kBfFloats;    // TILE 1: the brick's features
-    // TILE 1, 2: the segment's records
+    // the segment's records
     uint32_t *seg = TILE == 1 ? (uint32_t *)(tile + kFTileFloats) : (uint32_t *)tile;
     HV *htile = (HV *)(seg + kHSegWords);                // TILE 2: the staged level boxes
     __shared__ TileWork seg_slot;
     __shared__ HashSegInfo hinfo;
     __shared__ LevelTile ltab[4];
-    stage_weights_bf16(m, frag, fl);
+    stage_weights_bf16<kTileThreads>(m, frag, fl);
     __syncthreads();
 
-    const int lane = lane_id(), q = lane >> 4, j = lane & 15;
+    const int lane = lane_id(), h = lane >> 5, j = lane & 31;
     const int wave = threadIdx.x / 64;
-    const int64_t total = (int64_t)b.offsets[b.n];
 
-    // one batch of kBfNT tiles: samples s0 + nt*16 + j below send (TILE:
-    // positions in the staged segment)
-    auto batch = [&](int64_t s0, int64_t send) {
-        // wave priority raised at each layer, as in the FP32 kernel (measured:
-        // MLP stage 27.0 -> 26.7 ms in voxel order, 45.3 -> 45.0 ms in ray order)
+    // one batch: positions s0 + j below send in the staged segment
+    auto batch = [&](int s0, int send) {
+        // wave priority raised at each layer (measured: MLP stage 27.0 -> 26.7 ms)
         __builtin_amdgcn_s_setprio(0);
-        bf8_t xin[kBfNT][2];
-        int64_t rec[kBfNT];
-        bool valid[kBfNT];
-#pragma unroll
-        for (int nt = 0; nt < kBfNT; ++nt) {
-            const int64_t s = s0 + nt * 16 + j;
-            valid[nt] = s < send;
-            // a lane past the batch's last sample works on the first sample of
-            // the range (in-bounds inputs, no branches around the loads); its
-            // colour is not stored
-            const int64_t sv = valid[nt] ? s : 0;
-            if (TILE) rec[nt] = (int64_t)seg[sv];
-            else rec[nt] = voxel ? (int64_t)b.perm[sv] : sv;
-            float x[10];
-            uint32_t ray;
-            if constexpr (TILE == 2) {
-                ray = seg[kTileSeg + sv];
-                const float xp[3] = {__uint_as_float(seg[2 * kTileSeg + sv]), __uint_as_float(seg[3 * kTileSeg + sv]),
-                                     __uint_as_float(seg[4 * kTileSeg + sv])};
-                hash_level3_tiled<T>(g, ltab[q], htile, q, xp, x);
-            } else if constexpr (TILE == 1) {
-                ray = seg[kTileSeg + sv];
-                const float fr[3] = {__uint_as_float(seg[2 * kTileSeg + sv]), __uint_as_float(seg[3 * kTileSeg + sv]),
-                                     __uint_as_float(seg[4 * kTileSeg + sv])};
-                const uint32_t cell = seg[5 * kTileSeg + sv];
-                tile_gather3(tile, (int)(cell & 15u), (int)((cell >> 4) & 15u), (int)(cell >> 8), fr, q, x);
-            } else {
-                sample_inputs<T, false>(g, b, rec[nt], q, x);
-                ray = b.rec_ray[rec[nt]];
-            }
-            typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-            const bf8_t ev = __builtin_bit_cast(bf8_t, *(const u4_t *)(b.enc + (int64_t)ray * 16 + 4 * q));
-            // chunk 0: features 3q..3q+2 then encoding slots 0..4; chunk 1:
-            // encoding slots 5, 6 and the bias slot's constant 1 (slot 7)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                xin[nt][0][e] = e < 3 ? (__bf16)x[e] : ev[e - 3];
-                xin[nt][1][e] = e < 3 ? ev[5 + e] : (__bf16)0.0f;
-            }
-
+        const int s = s0 + j;
+        const bool valid = s < send;
+        // (a lane past the batch's last sample works on the segment's first)
+        const int sv = valid ? s : 0;
+        const int64_t rec = (int64_t)seg[sv];
+        const uint32_t ray = seg[kTileSeg + sv];
+        const u4_t *er = (const u4_t *)(b.enc + (int64_t)ray * 16 + 8 * h);
+        const u4_t e0 = er[0], e1 = er[1];
+        const float p[3] = {__uint_as_float(seg[2 * kTileSeg + sv]), __uint_as_float(seg[3 * kTileSeg + sv]),
+                            __uint_as_float(seg[4 * kTileSeg + sv])};
+        float x[6];
+        if constexpr (TILE == 2) {
+            hash_level3_tiled<T>(g, ltab[2 * h], htile, 2 * h, p, x);
+            hash_level3_tiled<T>(g, ltab[2 * h + 1], htile, 2 * h + 1, p, x + 3);
+        } else {
+            const uint32_t cell = seg[5 * kTileSeg + sv];
+            const int lx = (int)(cell & 15u), ly = (int)((cell >> 4) & 15u), lz = (int)(cell >> 8);
+            tile_gather3(tile, lx, ly, lz, p, 2 * h, x);
+            tile_gather3(tile, lx, ly, lz, p, 2 * h + 1, x + 3);
         }
-        // layer 0.  A finished pair of row blocks (32 hidden units) becomes
-        // one BF16 input chunk of layer 1 while the next pair's MFMAs issue:
-        // one row block per scheduling region, the pair before it converted in
-        // the region of the next even block.
+        BfNet<1> net(frag, fl, lane);
+        bf8_t xin[1][3];
+        bf_inputs(x, e0, e1, xin[0]);
         __builtin_amdgcn_s_setprio(1);
-        // (the bias comes in through input chunk 1)
-        bf8_t hb[4][kBfNT];
-        f4_t h1[2][2][kBfNT];   // [pair parity][block of the pair][tile]
 #pragma unroll
-        for (int t = 0; t <= 8; ++t) {
-            const f4_t zero = f4_t{0.f, 0.f, 0.f, 0.f};
-            if (t < 8) {
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const bf8_t a = frag[kBfW0 + (t * 2 + c) * 64 + lane];
-#pragma unroll
-                    for (int nt = 0; nt < kBfNT; ++nt)
-                        h1[(t >> 1) & 1][t & 1][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            a, xin[nt][c], c == 0 ? zero : h1[(t >> 1) & 1][t & 1][nt], 0, 0, 0);
-                }
-            }
-            if ((t & 1) == 0 && t > 0) {
-                const int pr = (t >> 1) - 1;
-#pragma unroll
-                for (int nt = 0; nt < kBfNT; ++nt)
-                    hb[pr][nt] = relu_bf8(pack_bf8(h1[pr & 1][0][nt], h1[pr & 1][1][nt]));
-            }
+        for (int t = 0; t <= 4; ++t) {
+            if (t < 4) net.layer0(t, xin);
+            if (t > 0) net.activate(t - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // layer 1, and the output layer (one zero-padded tile) fed pair by
-        // pair: the output MFMA of a finished pair of row blocks issues in the
-        // region of the next even block (the same sums in the same order as
-        // after the whole layer)
         __builtin_amdgcn_s_setprio(2);
-        f4_t h2[2][2][kBfNT];
-        f4_t o3[kBfNT];
-        const f4_t bias2 = *(const f4_t *)(fl + kBfB2);
 #pragma unroll
-        for (int t = 0; t <= 8; ++t) {
-            if (t < 8) {
-                const f4_t bias = *(const f4_t *)(fl + kBfB1 + 16 * t + 4 * q);
+        for (int t = 0; t <= 4; ++t) {
+            if (t < 4) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const bf8_t a = frag[kBfW1 + (t * 4 + c) * 64 + lane];
-#pragma unroll
-                    for (int nt = 0; nt < kBfNT; ++nt)
-                        h2[(t >> 1) & 1][t & 1][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            a, hb[c][nt], c == 0 ? bias : h2[(t >> 1) & 1][t & 1][nt], 0, 0, 0);
-                }
+                for (int c = 0; c < 8; ++c) net.layer1(t, c, net.w1f[(t * 8 + c) * 64]);
             }
-            if ((t & 1) == 0 && t > 0) {
-                const int pr = (t >> 1) - 1;
-                const bf8_t a = frag[kBfW2 + pr * 64 + lane];
+            if (t > 0) {
 #pragma unroll
-                for (int nt = 0; nt < kBfNT; ++nt)
-                    o3[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        a, relu_bf8(pack_bf8(h2[pr & 1][0][nt], h2[pr & 1][1][nt])), pr == 0 ? bias2 : o3[nt], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) net.output(t - 1, i);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(3);
-        // lanes of group 0 hold rows 0..3 (colour channels 0..2) of their sample
-#pragma unroll
-        for (int nt = 0; nt < kBfNT; ++nt) {
-            if (valid[nt] && q == 0) {
-                float *out = b.rec_c + 3 * rec[nt];
-                out[0] = sigmoid_hw(o3[nt][0]);
-                out[1] = sigmoid_hw(o3[nt][1]);
-                out[2] = sigmoid_hw(o3[nt][2]);
-            }
+        const f4_t b2 = *(const f4_t *)(fl + kBfB2);
+        const float p0 = net.logit(0, 0, b2[0]), p1 = net.logit(0, 1, b2[1]), p2 = net.logit(0, 2, b2[2]);
+        if (valid && h == 0) {
+            float *out = b.rec_c + 3 * rec;
+            out[0] = sigmoid_hw(p0);
+            out[1] = sigmoid_hw(p1);
+            out[2] = sigmoid_hw(p2);
         }
     };
 
-    if constexpr (TILE != 0) {
-        TileWork w;
-        ClaimState cs{0, 0, -1};   // used by thread 0 only
-        while (claim_segment<TILE == 1 ? kClaimRun : 1>(b, &seg_slot, cs, w)) {
-            const int n = (int)(w.end - w.start);
-            if constexpr (TILE == 2) {
-                stage_segment_hash(g, b, w.start, n, seg, hinfo);
-                __syncthreads();
-                if (threadIdx.x == 0) plan_hash_levels<T>(g, n, hinfo, ltab);
-                __syncthreads();
-                load_hash_tiles<T>(g, hinfo, htile);
-            } else {
-                const BrickBase base = brick_base(g, w.brick);
-                if (!w.reuse) load_feature_tile<T>(g, base, tile);
-                stage_segment(g, b, w.start, n, base, seg);
-            }
+    TileWork w;
+    ClaimState cs{0, 0, -1};   // used by thread 0 only
+    while (claim_segment<TILE == 1 ? kClaimRun : 1>(b, &seg_slot, cs, w)) {
+        const int n = (int)(w.end - w.start);
+        if constexpr (TILE == 2) {
+            stage_segment_hash(g, b, w.start, n, seg, hinfo);
             __syncthreads();
-            const int nb = (n + kBfBatch - 1) / kBfBatch;
-            for (int bi = wave; bi < nb; bi += kBfWaves) batch((int64_t)bi * kBfBatch, (int64_t)n);
+            if (threadIdx.x == 0) plan_hash_levels<T>(g, n, hinfo, ltab);
+            __syncthreads();
+            load_hash_tiles<T>(g, hinfo, htile);
+        } else {
+            const BrickBase base = brick_base(g, w.brick);
+            if (!w.reuse) load_feature_tile<T>(g, base, tile);
+            stage_segment(g, b, w.start, n, base, seg);
         }
-    } else {
-        const int64_t nbatch = (total + kBfBatch - 1) / kBfBatch;
-        const BatchRange br = xcd_batches(nbatch, kBfWaves, wave);
-        for (int64_t bt = br.first; bt < br.end; bt += br.stride) batch(bt * kBfBatch, total);
+        __syncthreads();
+        const int nb = (n + kBfBatch - 1) / kBfBatch;
+        for (int bi = wave; bi < nb; bi += kBfWaves) batch(bi * kBfBatch, n);
     }
 }
 
@@ -736,22 +908,32 @@ __global__ __launch_bounds__(kBfWaves * 64) void k_mlp_fwd_bf16(GridK g, cic_mlp
 #define CIC_VOXEL_TILE 1
 #endif
 template <typename T, int TILE>
-static void launch_bf16_k(const GridK &g, const cic_mlp &m, const RenderBufs &b, bool voxel, hipStream_t s)
+static void launch_bf16_tile(const GridK &g, const cic_mlp &m, const RenderBufs &b, hipStream_t s)
 {
-    const int lds = kLdsBf16 + (TILE == 1 ? (kFTileFloats + kSegWords) * 4 : TILE == 2 ? kHSegWords * 4 + kHTileBytes : 0);
+    const int lds = kLdsBf16 + (TILE == 1 ? (kFTileFloats + kSegWords) * 4 : kHSegWords * 4 + kHTileBytes);
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute((const void *)k_mlp_fwd_bf16<T, TILE>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   lds);
         attr_set = true;
     }
-    if (TILE) {
-        launch_brick_segments(b, kTileSeg, true, s);
-        launch_fill_u32(b.work_ctr, 0u, kXcds, s);
+    launch_brick_segments(b, kTileSeg, true, s);
+    launch_fill_u32(b.work_ctr, 0u, kXcds, s);
+    // at least one workgroup per XCD range of segments
+    const int grid = std::max(num_cus(b), kXcds);
+    hipLaunchKernelGGL((k_mlp_fwd_bf16<T, TILE>), dim3(grid), dim3(kBfWaves * 64), lds, s, g, m, b);
+}
+
+template <typename T, bool HASH>
+static void launch_bf16_gather(const GridK &g, const cic_mlp &m, const RenderBufs &b, bool voxel, hipStream_t s)
+{
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void *)k_mlp_fwd_bf16_gather<T, HASH>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBf16);
+        attr_set = true;
     }
-    // TILE: at least one workgroup per XCD range of segments
-    const int grid = TILE ? std::max(num_cus(b) * kBfWgs, kXcds) : num_cus(b) * kBfWgs;
-    hipLaunchKernelGGL((k_mlp_fwd_bf16<T, TILE>), dim3(grid), dim3(kBfWaves * 64), lds, s, g, m, b,
+    hipLaunchKernelGGL((k_mlp_fwd_bf16_gather<T, HASH>), dim3(num_cus(b)), dim3(kRayWaves8 * 64), kLdsBf16, s, g, m, b,
                        voxel ? 1 : 0);
 }
 
@@ -759,10 +941,12 @@ template <typename T>
 void launch_mlp_forward_bf16(const GridK &g, const cic_mlp &m, const RenderBufs &b, bool voxel, hipStream_t s)
 {
     if (CIC_VOXEL_TILE && voxel) {
-        if (g.hlevels == 0) launch_bf16_k<T, 1>(g, m, b, true, s);
-        else launch_bf16_k<T, 2>(g, m, b, true, s);
+        if (g.hlevels == 0) launch_bf16_tile<T, 1>(g, m, b, s);
+        else launch_bf16_tile<T, 2>(g, m, b, s);
+    } else if (g.hlevels) {
+        launch_bf16_gather<T, true>(g, m, b, voxel, s);
     } else {
-        launch_bf16_k<T, 0>(g, m, b, voxel, s);
+        launch_bf16_gather<T, false>(g, m, b, voxel, s);
     }
 }
 

@@ -2,6 +2,9 @@
 // inputs of layer 0 (trilinear feature gather or multi-level encoding, and
 // the view-direction encoding) and the persistent grids' size.
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "kernels.h"
 
 namespace cic {
@@ -21,17 +24,16 @@ __host__ __device__ __forceinline__ int l0_input(int c, int q)
 __device__ __forceinline__ float pick3(int i, float a, float b, float c) { return i == 0 ? a : (i == 1 ? b : c); }
 
 // float32 weights in LDS (in floats), pre-permuted into per-lane MFMA
-// fragment order: W0 [t 8][c2 5][lane 64][2] (lane l of output tile t holds
-// row 16t + l%16 at the inputs of chunks 2*c2, 2*c2+1 of lane group l/16),
-// W1 [t 8][c4 8][lane 64][4] (row 16t + l%16, columns 16*c4 + 4*(l/16) + r),
-// W2 [q 4][ch 3][t 8][r 4] (column 16t + 4q + r of output row ch), biases.
-// PAD inserts 4 floats after every 16 lanes of a W1 block: the fragment reads
-// stay conflict-free, and a read of W1 transposed (lane l taking row
-// 16 c4 + 4 (l/16) + rr, column 16 ti + l%16) puts the 64 lanes on 64
-// distinct banks instead of 16.
-template <bool PAD>
+// fragment order (the adjoint's recomputed forward): W0 [t 8][c2 5][lane 64][2]
+// (lane l of output tile t holds row 16t + l%16 at the inputs of chunks 2*c2,
+// 2*c2+1 of lane group l/16), W1 [t 8][c4 8][lane 64][4] (row 16t + l%16,
+// columns 16*c4 + 4*(l/16) + r), W2 [q 4][ch 3][t 8][r 4] (column 16t + 4q + r
+// of output row ch), biases.  4 floats after every 16 lanes of a W1 block keep
+// the fragment reads conflict-free, and put a read of W1 transposed (lane l
+// taking row 16 c4 + 4 (l/16) + rr, column 16 ti + l%16) on 64 distinct banks
+// instead of 16.
 struct F32Lds {
-    static constexpr int kW1Block = PAD ? 272 : 256;
+    static constexpr int kW1Block = 272;
     static constexpr int kW0 = 0;
     static constexpr int kW1 = kW0 + 8 * 5 * 64 * 2;
     static constexpr int kW2 = kW1 + 64 * kW1Block;
@@ -42,21 +44,13 @@ struct F32Lds {
     // first float of lane `lane` of W1 block (t * 8 + c4)
     __host__ __device__ static constexpr int w1(int blk, int lane)
     {
-        return kW1 + blk * kW1Block + 4 * (PAD ? lane + (lane >> 4) : lane);
+        return kW1 + blk * kW1Block + 4 * (lane + (lane >> 4));
     }
 };
-constexpr int kOffW0 = F32Lds<false>::kW0;
-constexpr int kOffW1 = F32Lds<false>::kW1;
-constexpr int kOffW2 = F32Lds<false>::kW2;
-constexpr int kOffB0 = F32Lds<false>::kB0;
-constexpr int kOffB1 = F32Lds<false>::kB1;
-constexpr int kOffB2 = F32Lds<false>::kB2;
-constexpr int kLdsF32 = F32Lds<false>::kSize;
 
-template <bool PAD = false>
 __device__ __forceinline__ void stage_weights_f32(const cic_mlp &m, float *lds)
 {
-    typedef F32Lds<PAD> L;
+    typedef F32Lds L;
     const int nt = blockDim.x;
     for (int i = threadIdx.x; i < 8 * 10 * 64; i += nt) {
         const int l = i & 63, c = (i >> 6) % 10, t = i / 640;
@@ -127,43 +121,136 @@ __device__ __forceinline__ void sample_position(const SampleRay &r, float xp[3])
     for (int a = 0; a < 3; ++a) xp[a] = r.o[a] + tk * r.d[a];
 }
 
-// Layer-0 inputs of one sample for this lane's group q (PE = false: only
-// the three feature channels; the direction terms come from a per-ray
-// table).
-template <typename T, bool PE = true>
-__device__ __forceinline__ void sample_inputs_from(const GridK &g, const SampleRay &r, int q, float x[10])
-{
-    if (g.hlevels) {
-        // multi-level encoding: lane group q gathers level q
-        float xp[3];
-        sample_position(r, xp);
-        hash_level3<T>(g, q, xp, x);
-    } else {
-        int i0[3];
-        float fr[3], tk;
-        sample_voxel(r.o, r.d, r.tn, r.delta, r.k, g, i0, fr, tk);
-        const T *feat = (const T *)g.features;
-        if constexpr (sizeof(T) == 2) {
-            trilerp3(feat, g, i0, fr, q, x);   // float16: one 64-bit load per vertex
-        } else {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) x[c] = trilerp1(feat, g, i0, fr, 12, 3 * q + c);
-        }
-    }
-    if (!PE) {
-#pragma unroll
-        for (int c = 3; c < 10; ++c) x[c] = 0.f;
-        return;
-    }
-    encode_group(r.d, q, x + 3);
-}
-
-template <typename T, bool PE = true>
+// Layer-0 inputs of one sample of a dense float32 grid for this lane's group
+// q of four (the adjoint): features 3q .. 3q+2 and the group's encoding.
 __device__ __forceinline__ void sample_inputs(const GridK &g, const RenderBufs &b, int64_t rec, int q, float x[10])
 {
     SampleRay r;
     load_sample_ray(b, b.rec_ray[rec], b.rec_k[rec], r);
-    sample_inputs_from<T, PE>(g, r, q, x);
+    int i0[3];
+    float fr[3], tk;
+    sample_voxel(r.o, r.d, r.tn, r.delta, r.k, g, i0, fr, tk);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) x[c] = trilerp1((const float *)g.features, g, i0, fr, 12, 3 * q + c);
+    encode_group(r.d, q, x + 3);
+}
+
+// Features 6h .. 6h+5 of one sample (lane half h): issue() sends the loads of
+// the 8 corners, feature() interpolates one of them, in two steps so that a
+// batch's work fits between the loads and their use.  Dense grids: corner c
+// (x bit 2, y bit 1, z bit 0), 6 consecutive channels.  Multi-level encoding:
+// levels 2h and 2h + 1, 3 features each.
+template <typename T, bool HASH>
+struct Gather {
+    static constexpr bool kHalf = sizeof(T) == 2;
+    static constexpr int kWords = kHalf ? (HASH ? 4 : 3) : 6;   // 32-bit words per corner
+    uint32_t raw[8][kWords];
+    float fr[HASH ? 2 : 1][3];
+    uint32_t odd;   // float16 tables: parity of each entry, bit 8 * level + corner
+
+    // xp: the sample's position
+    __device__ __forceinline__ void issue(const GridK &g, const float xp[3], int h)
+    {
+        if constexpr (HASH) {
+            odd = 0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                // level 2h + u (its parameters selected, not indexed by lane)
+                const int N = h ? g.hN[2 + u] : g.hN[u], dense = h ? g.hdense[2 + u] : g.hdense[u];
+                float scale[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) scale[a] = h ? g.hscale[2 + u][a] : g.hscale[u][a];
+                int i0[3];
+                hash_cell_n(g.lo, N, scale, xp, i0, fr[u]);
+                const T *tab = (const T *)g.htab + (size_t)(2 * h + u) * ((size_t)g.hmask + 1) * 3;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const uint64_t e = hash_entry_n(N, dense, g.hmask, (uint32_t)(i0[0] + ((c >> 2) & 1)),
+                                                    (uint32_t)(i0[1] + ((c >> 1) & 1)), (uint32_t)(i0[2] + (c & 1)));
+                    if constexpr (kHalf) {
+                        // the two aligned words that hold the entry's 6 bytes (see load_entry3)
+                        const uint32_t *w = (const uint32_t *)((const char *)tab + ((e * 6) & ~(uint64_t)3));
+                        raw[c][2 * u] = w[0];
+                        raw[c][2 * u + 1] = w[1];
+                        odd |= ((uint32_t)e & 1u) << (8 * u + c);
+                    } else {
+                        const uint32_t *w = (const uint32_t *)tab + e * 3;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) raw[c][3 * u + k] = w[k];
+                    }
+                }
+            }
+        } else {
+            int i0[3];
+            locate(xp, g, i0, fr[0]);
+            constexpr int kRec = 12 * (int)sizeof(T);
+            const int64_t sy = (int64_t)g.r2 * kRec, sx = (int64_t)g.r1 * sy;
+            const char *p = (const char *)g.features + vertex_index(g, i0[0], i0[1], i0[2]) * kRec + h * (kRec / 2);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const uint32_t *w =
+                    (const uint32_t *)(p + ((c >> 2) & 1) * sx + ((c >> 1) & 1) * sy + (c & 1) * kRec);
+#pragma unroll
+                for (int k = 0; k < kWords; ++k) raw[c][k] = w[k];
+            }
+        }
+    }
+
+    __device__ __forceinline__ float value(int c, int k) const
+    {
+        if constexpr (!kHalf) {
+            return __uint_as_float(raw[c][k]);
+        } else if constexpr (!HASH) {
+            const uint32_t w = raw[c][k >> 1];
+            return __half2float(__ushort_as_half((unsigned short)((k & 1) ? w >> 16 : w & 0xffffu)));
+        } else {
+            const int u = k / 3, f = k % 3;
+            const uint32_t a = raw[c][2 * u], b = raw[c][2 * u + 1], sh = ((odd >> (8 * u + c)) & 1u) * 16u;
+            const uint32_t w = f < 2 ? __builtin_amdgcn_alignbit(b, a, sh) : b >> sh;
+            return __half2float(__ushort_as_half((unsigned short)(f == 1 ? w >> 16 : w & 0xffffu)));
+        }
+    }
+
+    __device__ __forceinline__ float feature(int k) const
+    {
+        const float *f = fr[HASH ? k / 3 : 0];
+        const float c00 = lerpf(value(0, k), value(1, k), f[2]), c01 = lerpf(value(2, k), value(3, k), f[2]);
+        const float c10 = lerpf(value(4, k), value(5, k), f[2]), c11 = lerpf(value(6, k), value(7, k), f[2]);
+        return lerpf(lerpf(c00, c01, f[1]), lerpf(c10, c11, f[1]), f[0]);
+    }
+};
+
+// f(0), f(1), .. f(N - 1) with compile-time arguments (a loop whose body is as
+// long as a batch's exceeds the compiler's unrolling limit)
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_seq(std::integer_sequence<int, I...>, const F &f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void static_for(const F &f)
+{
+    static_for_seq(std::make_integer_sequence<int, N>{}, f);
+}
+
+// Alternates the instructions before it, back to the last barrier: N times one MFMA,
+// then up to 8 vector and a few memory instructions that fit in its shadow.
+template <int N>
+__device__ __forceinline__ void interleave_mfma()
+{
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads
+        __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);     // vector ALU
+        __builtin_amdgcn_sched_group_barrier(0x20, 4, 0);    // global loads
+    }
+}
+
+// hidden unit of slot e of chunk c (16 units) for lane half h: the rows that
+// the lane half holds of the 32-row result tile c / 2
+__host__ __device__ __forceinline__ int x_hid(int c, int h, int e)
+{
+    return 16 * c + 8 * (e >> 2) + 4 * h + (e & 3);
 }
 
 // Output sigmoid from the hardware base-2 exponential and reciprocal:
