@@ -459,16 +459,17 @@ struct StageTimer {
     }
 };
 
-// Full render pipeline on one pass of rays.
-void run_pipeline(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, const OptsK &ok_, bool voxel,
+// Full render pipeline on one pass of rays; width: they are the pixels of
+// whole image rows of this width, or 0.
+void run_pipeline(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, const OptsK &ok_, bool voxel, int width,
                   RenderBufs &b, float *rgb, float *depth, float *acc, const int32_t *out_map,
                   const cic_camera *frame_cam, int64_t *n_eval, hipStream_t s, int64_t *n_masked = nullptr)
 {
     const bool f16 = grid->storage == CIC_F16;
     {
         StageTimer t(CIC_STAGE_MARCH, s);
-        if (f16) launch_march<__half>(gk, ok_, b, s);
-        else launch_march<float>(gk, ok_, b, s);
+        if (f16) launch_march<__half>(gk, ok_, b, width, s);
+        else launch_march<float>(gk, ok_, b, width, s);
     }
     {
         StageTimer t(CIC_STAGE_COMPACT, s);
@@ -499,6 +500,13 @@ void run_pipeline(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, con
     }
 }
 
+// Width of the image rows that a pass of pixels c0 .. c0 + nc - 1 consists of,
+// 0 if it cuts one.
+int rows_width(const cic_camera &cam, int64_t c0, int64_t nc)
+{
+    return c0 % cam.width == 0 && nc % cam.width == 0 ? cam.width : 0;
+}
+
 // Full render of one frame that fits one pass (np <= kChunkRays); b carved
 // with generated rays.
 void full_frame(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, const OptsK &ok_, bool voxel,
@@ -510,7 +518,7 @@ void full_frame(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, const
         StageTimer t(CIC_STAGE_RAYGEN, s);
         launch_generate_rays(cam, np, 0, nullptr, nullptr, nullptr, (float *)b.rays_o, (float *)b.rays_d, s);
     }
-    run_pipeline(grid, gk, mlp, ok_, voxel, b, rgb, depth_z, nullptr, nullptr, &cam, n_eval, s);
+    run_pipeline(grid, gk, mlp, ok_, voxel, cam.width, b, rgb, depth_z, nullptr, nullptr, &cam, n_eval, s);
 }
 
 // Warp from a reference, then render the holes in place (Eq. 4).
@@ -530,7 +538,7 @@ void sparw_frame(const cic_grid *grid, const GridK &gk, const cic_mlp *mlp, cons
         StageTimer t(CIC_STAGE_RAYGEN, s);
         launch_generate_rays(tgt, np, 0, nullptr, w.hole_idx, w.n_holes, (float *)b.rays_o, (float *)b.rays_d, s);
     }
-    run_pipeline(grid, gk, mlp, ok_, voxel, b, out_rgb, out_dz, nullptr, w.hole_idx, &tgt, n_eval, s, n_masked);
+    run_pipeline(grid, gk, mlp, ok_, voxel, 0, b, out_rgb, out_dz, nullptr, w.hole_idx, &tgt, n_eval, s, n_masked);
 }
 
 // Events that order render_sequence's two streams.  They live for one call:
@@ -725,8 +733,8 @@ int render_rays(const cic_grid *grid, const cic_mlp *mlp, const cic_opts *opts, 
         RenderBufs b = carve_render(cv, nc, opts->n_samples, nb, voxel, false);
         b.rays_o = rays_o + 3 * c0;
         b.rays_d = rays_d + 3 * c0;
-        run_pipeline(grid, gk, mlp, ok_, voxel, b, rgb + 3 * c0, depth_t + c0, acc + c0, nullptr, nullptr, n_eval,
-                     s);
+        run_pipeline(grid, gk, mlp, ok_, voxel, 0, b, rgb + 3 * c0, depth_t + c0, acc + c0, nullptr, nullptr,
+                     n_eval, s);
     }
     return after_launch("render_rays");
 }
@@ -758,8 +766,8 @@ int render_frame(const cic_grid *grid, const cic_mlp *mlp, const cic_opts *opts,
             StageTimer t(CIC_STAGE_RAYGEN, s);
             launch_generate_rays(*cam, nc, c0, nullptr, nullptr, nullptr, (float *)b.rays_o, (float *)b.rays_d, s);
         }
-        run_pipeline(grid, gk, mlp, ok_, voxel, b, rgb + 3 * c0, depth_z + c0, acc ? acc + c0 : nullptr, nullptr,
-                     cam, n_eval, s);
+        run_pipeline(grid, gk, mlp, ok_, voxel, rows_width(*cam, c0, nc), b, rgb + 3 * c0, depth_z + c0,
+                     acc ? acc + c0 : nullptr, nullptr, cam, n_eval, s);
     }
     return after_launch("render_frame");
 }
@@ -1029,7 +1037,8 @@ int render_frame_ds(const cic_grid *grid, const cic_mlp *mlp, const cic_opts *op
             StageTimer t(CIC_STAGE_RAYGEN, s);
             launch_generate_rays(lo, nc, r0, nullptr, nullptr, nullptr, (float *)b.rays_o, (float *)b.rays_d, s);
         }
-        run_pipeline(grid, gk, mlp, ok_, voxel, b, lo_rgb + 3 * r0, lo_dz + r0, nullptr, nullptr, &lo, n_eval, s);
+        run_pipeline(grid, gk, mlp, ok_, voxel, rows_width(lo, r0, nc), b, lo_rgb + 3 * r0, lo_dz + r0, nullptr,
+                     nullptr, &lo, n_eval, s);
     }
     launch_upsample_bilinear(lo_rgb, lo.width, lo.height, rgb, cam->width, cam->height, factor, s);
     return after_launch("render_frame_ds");
@@ -1080,7 +1089,7 @@ int render_backward(const cic_grid *grid, const cic_mlp *mlp, const cic_opts *op
         bb.d_b2 = d_b2;
         {
             StageTimer t(CIC_STAGE_MARCH, s);
-            launch_march<float>(gk, ok_, b, s);
+            launch_march<float>(gk, ok_, b, 0, s);
         }
         {
             StageTimer t(CIC_STAGE_COMPACT, s);

@@ -59,8 +59,10 @@ size_t scan_tmp_elems(int64_t n);
 void launch_exclusive_scan(const uint32_t *in, uint32_t *out, uint32_t *tmp, int64_t n, hipStream_t s);
 
 // render.hip
+// width: the rays are the pixels of whole image rows of this width (all of
+// them active, no slot_t), or 0
 template <typename T>
-void launch_march(const GridK &g, const OptsK &o, const RenderBufs &b, hipStream_t s);
+void launch_march(const GridK &g, const OptsK &o, const RenderBufs &b, int width, hipStream_t s);
 void launch_compact(const GridK &g, const RenderBufs &b, bool voxel_keys, hipStream_t s);
 void launch_brick_scatter(const RenderBufs &b, hipStream_t s);
 void launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
