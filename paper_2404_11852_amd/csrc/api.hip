@@ -203,16 +203,15 @@ RenderBufs carve_render(Carver &cv, int64_t nc, int N, int64_t n_bricks, bool vo
     b.count = cv.take<uint32_t>(nc);
     b.offsets = cv.take<uint32_t>(nc + 1);
     b.scan_tmp = cv.take<uint32_t>((int64_t)scan_tmp_elems(nc));
-    // The per-ray slots are read for the last time by the compaction; the
-    // colours (ray order) or the sample permutation (voxel order) are written
-    // after it, so they take the same bytes.
-    const int64_t kbytes = ((2 * ns + 255) / 256) * 256, slot_bytes = kbytes + 4 * ns;
-    char *u = cv.take<char>(voxel ? slot_bytes : std::max(slot_bytes, 12 * ns));
+    // The slots' sample indices are read for the last time by the compaction;
+    // the colours (ray order) or the sample permutation (voxel order) are
+    // written after it, so they take the same bytes.  The slots' weights stay
+    // for the per-ray accumulation.
+    char *u = cv.take<char>((voxel ? 6 : 12) * ns);
     b.slot_k = (uint16_t *)u;
-    b.slot_w = u ? (float *)(u + kbytes) : nullptr;
+    b.slot_w = cv.take<float>(ns);
     b.rec_ray = cv.take<uint32_t>(ns);
     b.rec_k = cv.take<uint16_t>(ns);
-    b.rec_w = cv.take<float>(ns);
     b.rec_c = voxel ? cv.take<float>(3 * ns) : (float *)u;
     b.z0 = cv.take<float>(128 * nc);
     b.enc = cv.take<uint32_t>(16 * nc);
@@ -279,10 +278,13 @@ constexpr int64_t kChunkRaysBwd = 8192;
 void carve_backward(Carver &cv, int64_t nc, int N, RenderBufs &b, BackwardBufs &bb)
 {
     const int64_t ns = nc * (int64_t)N;
-    b.slot_t = cv.take<float>(ns);
     b.rec_t = cv.take<float>(ns);
+    b.rec_w = cv.take<float>(ns);
     bb.partials = cv.take<float>((int64_t)kWgBlocks * kPartialFloats);
+    // (the slots' transmittances are read for the last time by the compaction,
+    // the feature gradients written after it)
     bb.rec_df = cv.take<float>(12 * ns);
+    b.slot_t = bb.rec_df;
     bb.rec_draw = cv.take<float>(ns);
     bb.seg_tiles = cv.take<float>(fg_max_segments(b.n_bricks, ns) * kFgTileFloats);
 }

@@ -25,10 +25,10 @@ struct RenderBufs {
     uint32_t *offsets;     // [n+1] exclusive scan of count
     uint32_t *scan_tmp;    // block sums
     uint16_t *slot_k;      // [n*N] live sample indices, per-ray fixed slots
-    float *slot_w;         // [n*N] their weights
+    float *slot_w;         // [n*N] their weights (kept until the per-ray accumulation)
     uint32_t *rec_ray;     // [n*N] compacted: ray of each live sample
     uint16_t *rec_k;       // [n*N] its sample index
-    float *rec_w;          // [n*N] its weight
+    float *rec_w;          // [n*N] its weight (adjoint only; nullable)
     float *rec_c;          // [n*N*3] MLP colour per live sample
     float *slot_t;         // [n*N] transmittance T_k of live samples (adjoint only; nullable)
     float *rec_t;          // [n*N] compacted T_k (adjoint only; nullable)

@@ -417,99 +417,137 @@ __device__ __forceinline__ int run_length(uint64_t heads, int active)
     return next - l;
 }
 
-// One wavefront per ray copies its live samples to their compacted position
-// (ray-order), and in voxel mode tags each with its brick and adds each run
-// of equal bricks to counts[brick] (global counters or an LDS histogram).
+// Compaction: the live samples' rays and sample indices from the per-ray slots
+// to consecutive records (the weights stay in the slots), and in voxel mode a
+// brick key per sample and each run of equal bricks added to counts[brick].
+// Bound by the latency of dependent loads, so a wavefront takes several rays:
+// lane l loads ray l's header, and a ray's slots are loaded before the ray
+// before it is stored (as far as the compiler knows the stores could alias
+// the slots, so it would not move the loads up by itself).
 //
-// Ray order: the ray's count and offset are loaded together, and the slots
-// of two 64-sample chunks before any record of them is stored (as far as the
-// compiler knows the stores could alias the slots, so it would not move the
-// second chunk's loads above the first chunk's stores by itself): two round
-// trips to memory per ray instead of three or four (8-view pass: 2.27 to
-// 1.84 ms).  The same form measured slower in voxel mode (4.77 to 6.25 ms with
-// the LDS histogram), which keeps one chunk per step.
-template <bool WITH_T>
-__device__ __forceinline__ void compact_ray_rays(const RenderBufs &b, int64_t ray)
+// Ray order: RAYS rays per wavefront, the first 128 slots of all of them in
+// flight together.  1, 4 or 8 by the number of rays, since small passes need
+// the wavefronts and large ones the loads (us with 1 / 4 / 8 rays per
+// wavefront, and with one whose loads all follow each other: 64x64 frame
+// 3.7 / 5.5 / 8.2, 4.2; 30,000 rays 7.3 / 7.9 / 10.1, 8.6; 333x257 15.8 /
+// 13.4 / 15.2, 22.5; 450x400 30.9 / 24.7 / 26.1, 46.8; 800x800 - / 97.6 /
+// 95.8, 171).
+template <int RAYS> __device__ __forceinline__ void compact_rays(const RenderBufs &b, int64_t ray0)
 {
     const int lane = lane_id();
-    const uint32_t cnt = b.count[ray];
-    const uint32_t off = b.offsets[ray];
-    if (cnt == 0) return;
-    const int64_t slots = ray * (int64_t)b.n_samples;
-    for (uint32_t j0 = 0; j0 < cnt; j0 += 2 * kWave) {
-        // a lane past the count reads slot 0 (the count is positive); a
-        // second chunk past the count stores nothing
-        const uint32_t ja = j0 + lane, jb = ja + kWave;
-        const int64_t sa = slots + (ja < cnt ? ja : 0u), sb = slots + (jb < cnt ? jb : 0u);
-        const uint16_t ka = b.slot_k[sa], kb = b.slot_k[sb];
-        const float wa = b.slot_w[sa], wb = b.slot_w[sb];
-        float ta = 0.f, tb = 0.f;
-        if constexpr (WITH_T) {
-            ta = b.slot_t[sa];
-            tb = b.slot_t[sb];
-        }
-        if (ja < cnt) {
-            b.rec_ray[off + ja] = (uint32_t)ray;
-            b.rec_k[off + ja] = ka;
-            b.rec_w[off + ja] = wa;
-            if constexpr (WITH_T) b.rec_t[off + ja] = ta;
-        }
-        if (jb < cnt) {
-            b.rec_ray[off + jb] = (uint32_t)ray;
-            b.rec_k[off + jb] = kb;
-            b.rec_w[off + jb] = wb;
-            if constexpr (WITH_T) b.rec_t[off + jb] = tb;
-        }
+    uint32_t lc = 0, lo = 0;
+    if (lane < RAYS && ray0 + lane < b.n) {
+        lc = b.count[ray0 + lane];
+        lo = b.offsets[ray0 + lane];
     }
-}
-
-__device__ __forceinline__ void compact_ray(const GridK &g, const RenderBufs &b, int64_t ray, bool voxel,
-                                            uint32_t *counts)
-{
-    if (!voxel) {
-        if (b.rec_t) compact_ray_rays<true>(b, ray);
-        else compact_ray_rays<false>(b, ray);
-        return;
-    }
-    const int lane = lane_id();
-    const uint32_t cnt = b.count[ray];
-    if (cnt == 0) return;
-    const uint32_t off = b.offsets[ray];
-    const int N = b.n_samples;
-    float o[3], d[3];
+    uint32_t cnt[RAYS], off[RAYS];
+    uint16_t ka[RAYS], kb[RAYS];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        o[a] = b.rays_o[3 * ray + a];
-        d[a] = b.rays_d[3 * ray + a];
+    for (int r = 0; r < RAYS; ++r) {
+        cnt[r] = __builtin_amdgcn_readlane(lc, r);
+        off[r] = __builtin_amdgcn_readlane(lo, r);
+        // (a lane past the count reads the ray's first slot, which is in bounds)
+        const uint16_t *sk = b.slot_k + min(ray0 + r, b.n - 1) * (int64_t)b.n_samples;
+        ka[r] = sk[(uint32_t)lane < cnt[r] ? lane : 0];
+        kb[r] = sk[(uint32_t)lane + kWave < cnt[r] ? lane + kWave : 0];
     }
-    const RayInfo inf = b.info[ray];
-    for (uint32_t j0 = 0; j0 < cnt; j0 += kWave) {
-        const uint32_t j = j0 + lane;
-        const bool act = j < cnt;
-        uint32_t key = 0xffffffffu;
-        if (act) {
-            const uint16_t k = b.slot_k[ray * (int64_t)N + j];
-            b.rec_ray[off + j] = (uint32_t)ray;
-            b.rec_k[off + j] = k;
-            b.rec_w[off + j] = b.slot_w[ray * (int64_t)N + j];
-            if (b.rec_t) b.rec_t[off + j] = b.slot_t[ray * (int64_t)N + j];
-            int i0[3];
-            float fr[3], tk;
-            sample_voxel(o, d, inf.tn, inf.delta, k, g, i0, fr, tk);
-            key = brick_of(g, i0);
-            b.rec_key[off + j] = key;
+#pragma unroll
+    for (int r = 0; r < RAYS; ++r) {
+        if (cnt[r] == 0) continue;
+        uint32_t *rr = b.rec_ray + off[r];
+        uint16_t *rk = b.rec_k + off[r];
+        const uint32_t ray = (uint32_t)(ray0 + r);
+        if ((uint32_t)lane < cnt[r]) {
+            rr[lane] = ray;
+            rk[lane] = ka[r];
         }
-        const int active = (int)min(cnt - j0, (uint32_t)kWave);
-        const uint64_t heads = run_heads(key, act);
-        if ((heads >> lane) & 1ull) atomicAdd(&counts[key], (uint32_t)run_length(heads, active));
+        if ((uint32_t)lane + kWave < cnt[r]) {
+            rr[lane + kWave] = ray;
+            rk[lane + kWave] = kb[r];
+        }
+        const uint16_t *sk = b.slot_k + (int64_t)ray * b.n_samples;
+        for (uint32_t j = 2 * kWave + lane; j < cnt[r]; j += kWave) {
+            rr[j] = ray;
+            rk[j] = sk[j];
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_compact(GridK g, RenderBufs b, int voxel)
+template <int RAYS> __global__ __launch_bounds__(256) void k_compact(RenderBufs b)
 {
-    const int64_t ray = (int64_t)blockIdx.x * kRayWaves + (threadIdx.x / kWave);
-    if (ray >= b.n) return;
-    compact_ray(g, b, ray, voxel != 0, b.brick_off);
+    const int64_t wave = (int64_t)blockIdx.x * kRayWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (wave * RAYS < b.n) compact_rays<RAYS>(b, wave * RAYS);
+}
+
+// Voxel mode, up to 64 rays ray0, ray0 + stride, .. of one wavefront: the next
+// ray's first 64 slots are loaded before this ray's are worked through.
+__device__ __forceinline__ void compact_rays_voxel(const GridK &g, const RenderBufs &b, int64_t ray0, int stride,
+                                                   int nrays, uint32_t *counts)
+{
+    const int lane = lane_id();
+    const int64_t mine = ray0 + (int64_t)lane * stride;
+    uint32_t lc = 0, loff = 0;
+    RayInfo linf{};
+    float lo[3] = {}, ld[3] = {};
+    if (lane < nrays) {
+        lc = b.count[mine];
+        loff = b.offsets[mine];
+        linf = b.info[mine];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = b.rays_o[3 * mine + a];
+            ld[a] = b.rays_d[3 * mine + a];
+        }
+    }
+    auto lane_f = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+    auto first_slots = [&](uint64_t todo) -> uint32_t {
+        const int r = todo ? __builtin_ctzll(todo) : 0;
+        const uint32_t cnt = __builtin_amdgcn_readlane(lc, r);
+        const uint16_t *sk = b.slot_k + (ray0 + (int64_t)r * stride) * (int64_t)b.n_samples;
+        return sk[(uint32_t)lane < cnt ? lane : 0];
+    };
+    uint64_t todo = __builtin_amdgcn_ballot_w64(lc != 0);
+    uint32_t kn = todo ? first_slots(todo) : 0u;
+    while (todo) {
+        const int r = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        uint32_t kc = kn;
+        if (todo) kn = first_slots(todo);
+        const int64_t ray = ray0 + (int64_t)r * stride;
+        const uint32_t cnt = __builtin_amdgcn_readlane(lc, r), off = __builtin_amdgcn_readlane(loff, r);
+        const float tn = lane_f(linf.tn, r), delta = lane_f(linf.delta, r);
+        const float o[3] = {lane_f(lo[0], r), lane_f(lo[1], r), lane_f(lo[2], r)};
+        const float d[3] = {lane_f(ld[0], r), lane_f(ld[1], r), lane_f(ld[2], r)};
+        const int64_t slots = ray * (int64_t)b.n_samples;
+        for (uint32_t j0 = 0; j0 < cnt; j0 += kWave) {
+            const uint32_t j = j0 + lane;
+            const bool act = j < cnt;
+            uint32_t key = 0xffffffffu;
+            if (act) {
+                if (j0) kc = b.slot_k[slots + j];
+                b.rec_ray[off + j] = (uint32_t)ray;
+                b.rec_k[off + j] = (uint16_t)kc;
+                if (b.rec_w) {   // the adjoint's
+                    b.rec_w[off + j] = b.slot_w[slots + j];
+                    b.rec_t[off + j] = b.slot_t[slots + j];
+                }
+                int i0[3];
+                float fr[3], tk;
+                sample_voxel(o, d, tn, delta, (int)kc, g, i0, fr, tk);
+                key = brick_of(g, i0);
+                b.rec_key[off + j] = key;
+            }
+            const int active = (int)min(cnt - j0, (uint32_t)kWave);
+            const uint64_t heads = run_heads(key, act);
+            if ((heads >> lane) & 1ull) atomicAdd(&counts[key], (uint32_t)run_length(heads, active));
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_compact_voxel(GridK g, RenderBufs b)
+{
+    const int64_t ray = (int64_t)blockIdx.x * kRayWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (ray < b.n) compact_rays_voxel(g, b, ray, 1, 1, b.brick_off);
 }
 
 // Voxel mode with an LDS histogram of the bricks: a block compacts `rays`
@@ -526,7 +564,8 @@ constexpr int64_t kHistMin = 2048;   // fewest rays of the LDS path
 // 16 wavefronts per block: the rays' dependent load chains overlap across
 // wavefronts (measured on eight 800x800 views with 256 rays per block:
 // compaction + sort 6.5 ms with 4 wavefronts per block, 4.9 ms with 8, 4.7 ms
-// with 16)
+// with 16).  A pass of 2^21 rays takes 488 us, 687 when each ray's loads began
+// after the ray before it and the weights were copied too.
 constexpr int kHistThreads = 1024;
 // Rays per block: 256 where that still gives 512 blocks, else fewer, down to
 // one per wavefront; 0 = the per-run global atomics.
@@ -545,8 +584,9 @@ __global__ __launch_bounds__(kHistThreads) void k_compact_hist(GridK g, RenderBu
     __syncthreads();
     const int64_t ray0 = (int64_t)blockIdx.x * rays;
     const int64_t ray1 = ray0 + rays < b.n ? ray0 + rays : b.n;
-    for (int64_t ray = ray0 + threadIdx.x / kWave; ray < ray1; ray += blockDim.x / kWave)
-        compact_ray(g, b, ray, true, hist);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), stride = kHistThreads / kWave;
+    const int mine = (int)((ray1 - ray0) - wave + stride - 1) / stride;   // this wavefront's rays, at most 16
+    if (mine > 0) compact_rays_voxel(g, b, ray0 + wave, stride, mine, hist);
     __syncthreads();
     for (int64_t i = threadIdx.x; i < b.n_bricks; i += blockDim.x) {
         const uint32_t c = hist[i];
@@ -557,15 +597,20 @@ __global__ __launch_bounds__(kHistThreads) void k_compact_hist(GridK g, RenderBu
 void launch_compact(const GridK &g, const RenderBufs &b, bool voxel_keys, hipStream_t s)
 {
     if (b.n == 0) return;
-    const int rays = voxel_keys ? hist_rays(b) : 0;
-    if (rays) {
-        const unsigned blocks = (unsigned)((b.n + rays - 1) / rays);
-        hipLaunchKernelGGL(k_compact_hist, dim3(blocks), dim3(kHistThreads), b.n_bricks * sizeof(uint32_t), s, g, b,
-                           rays);
+    auto grid = [&](int64_t per) { return dim3((unsigned)((b.n + per - 1) / per)); };
+    if (voxel_keys) {
+        const int rays = hist_rays(b);
+        if (rays)
+            hipLaunchKernelGGL(k_compact_hist, grid(rays), dim3(kHistThreads), b.n_bricks * sizeof(uint32_t), s, g, b,
+                               rays);
+        else hipLaunchKernelGGL(k_compact_voxel, grid(kRayWaves), dim3(256), 0, s, g, b);
         return;
     }
-    const unsigned blocks = (unsigned)((b.n + kRayWaves - 1) / kRayWaves);
-    hipLaunchKernelGGL(k_compact, dim3(blocks), dim3(256), 0, s, g, b, voxel_keys ? 1 : 0);
+    const int rays = b.n < 32768 ? 1 : b.n < 262144 ? 4 : 8;   // per wavefront
+    const dim3 blocks = grid(kRayWaves * rays);
+    if (rays == 1) hipLaunchKernelGGL(k_compact<1>, blocks, dim3(256), 0, s, b);
+    else if (rays == 4) hipLaunchKernelGGL(k_compact<4>, blocks, dim3(256), 0, s, b);
+    else hipLaunchKernelGGL(k_compact<8>, blocks, dim3(256), 0, s, b);
 }
 
 // Bucket scatter: brick_off holds the exclusive scan of brick counts and is
@@ -752,9 +797,10 @@ __global__ __launch_bounds__(256) void k_reduce(RenderBufs b, OptsK op, float *r
     const bool active = ray < b.n && (uint64_t)ray < n_act;
     const uint32_t cnt = active ? b.count[ray] : 0u, off = active ? b.offsets[ray] : 0u;
     float r = 0.f, gg = 0.f, bb = 0.f;
+    const float *ws = b.slot_w + ray * (int64_t)b.n_samples;
     for (uint32_t j = (uint32_t)sub; j < cnt; j += kReduceLanes) {
         const int64_t k = (int64_t)off + j;
-        const float w = b.rec_w[k];
+        const float w = ws[j];
         r = fmaf(w, b.rec_c[3 * k], r);
         gg = fmaf(w, b.rec_c[3 * k + 1], gg);
         bb = fmaf(w, b.rec_c[3 * k + 2], bb);

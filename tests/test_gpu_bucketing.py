@@ -45,3 +45,23 @@ def test_scan_edges(n_rays):
     parts = [cic.render_rays(m, opts, o[a:b], d[a:b]) for a, b in ((0, k), (k, n_rays)) if b > a]
     for i, t in enumerate(whole):
         assert torch.equal(t, torch.cat([p[i] for p in parts]))
+
+
+@pytest.mark.parametrize("n_rays,samples", [(32767, 130), (32769, 63), (32771, 200), (262143, 65), (262145, 129),
+                                            (262151, 64)])
+def test_compaction_edges(n_rays, samples):
+    """Records of 1, 4 or 8 rays per wavefront with ragged last groups, rays of
+    up to three chunks of 64 samples: rays rendered together equal rays
+    rendered in small calls."""
+    import paper_2404_11852_amd as cic
+    print_case("compaction, %d rays, %d samples" % (n_rays, samples))
+    dens, feats = synth.make_scene(24, seed=0)
+    m = cic.Model(dens, feats, synth.make_mlp(1, bias_std=0.1), density_shift=synth.DENSITY_SHIFT)
+    if samples < 100:
+        m.build_occupancy(synth.OCC_SIGMA)
+    o, d = (torch.from_numpy(t).cuda() for t in synth.random_rays(n_rays, seed=4))
+    opts = cic.make_opts(samples, 0.0, samples < 100)
+    whole = cic.render_rays(m, opts, o, d)
+    parts = [cic.render_rays(m, opts, o[a:a + 30000], d[a:a + 30000]) for a in range(0, n_rays, 30000)]
+    for i, t in enumerate(whole):
+        assert torch.equal(t, torch.cat([p[i] for p in parts]))
