@@ -12,9 +12,11 @@
 // bucketing):
 //  - k_mlp_adjoint: per 16-sample batch (ray order), the forward recomputed
 //    on chip (its colours c_k kept for the next kernel), the MLP backward
-//    from dL/dc_k = w_k dL/dC on FP32 MFMA (the 12 feature gradients written
-//    per sample) and the weight-gradient outer products accumulated per
-//    workgroup; k_wgrad_apply adds the workgroups' partials in a fixed order
+//    from dL/dc_k = w_k dL/dC (the 12 feature gradients written per sample)
+//    and the weight-gradient outer products accumulated per workgroup, the
+//    backward's products on split float16; k_mlp_adjoint_f32 repeats in
+//    float32 the workgroups whose values the split cannot hold;
+//    k_wgrad_apply adds the workgroups' partials in a fixed order
 //    (deterministic).
 //  - k_bwd_composite: one wavefront per ray walks its live samples from the
 //    back, 64 at a time, with a reverse wavefront scan for R_k and D_k; it
@@ -27,8 +29,6 @@
 #include "mlp_common.h"
 
 namespace cic {
-
-typedef float f4_t __attribute__((ext_vector_type(4)));
 
 // Reverse inclusive scan (sum over lanes >= this lane).
 __device__ __forceinline__ float wave_rev_incl_scan(float v)
@@ -318,88 +318,701 @@ void launch_feature_grads_bricks(const GridK &g, const RenderBufs &b, const Back
 
 // ---------------------------------------------------------------------------
 // MLP adjoint, fused: per batch of 16 live samples (ray order) a wavefront
-// recomputes the forward (full 40-wide layer-0 input, FP32 MFMA), forms the
-// output-logit gradient from dL/dc_k = w_k g, and runs the backward: dp1 =
-// [h2 > 0] (W2^T dlogit) on the vector ALUs, dh1 = W1^T dp1 and the feature
-// gradient (W0^T dp0)[0:12] on FP32 MFMA, dp0 = [h1 > 0] dh1.  Nothing of
-// it leaves the chip except the 12 feature gradients per sample (for the
-// brick-segment tiles).  Ray order fixes which samples each workgroup sums,
-// so the MLP gradients are the same bits on every call (in brick order the
-// bucketing's atomic cursors would decide it).  The weight gradients are
-// sums over samples of outer products,
+// recomputes the forward (full 40-wide layer-0 input, FP32 MFMA: the ReLU
+// masks have to be those of float32 arithmetic), forms the output-logit
+// gradient from dL/dc_k = w_k g, and runs the backward: dp1 = [h2 > 0]
+// (W2^T dlogit) on the vector ALUs, dh1 = W1^T dp1, dp0 = [h1 > 0] dh1 and the
+// feature gradient (W0^T dp0)[0:12].  Nothing of it leaves the chip except the
+// 12 feature gradients per sample (for the brick-segment tiles).  Ray order
+// fixes which samples each workgroup sums, so the MLP gradients are the same
+// bits on every call (in brick order the bucketing's atomic cursors would
+// decide it).  The weight gradients are sums over samples of outer products,
+//   P0 = dp0^T [x|1] (dW0, db0), P1 = dp1^T h1 (dW1),
+//   P2 = dl^T h2 (dW2), and the sums of dp1 (db1) and dl (db2).
+//
+// Arithmetic.  Everything after the forward multiplies values split into two
+// float16 parts, v = hi + lo, as hi hi + hi lo + lo hi on float16 MFMA (16
+// times the float32 rate), summed in float32.  Every factor is scaled by a
+// power of two first, so that its remainders are normal float16 numbers down
+// to 2^-17 of its largest value: W1 and W0 by their maxima, dl, h1, h2, the
+// features and the direction by the largest value the workgroup has met (its
+// sums are scaled down where one grows).  Values that no such scale fits (2^97
+// and beyond, infinities, NaN) set a flag, and k_mlp_adjoint_f32 does that
+// workgroup's share again.  Gradient error against 64 bits, rms over seeds: 3000
+// rays of 96 samples dW0 8.3e-7 -> 5.1e-7, dW1 7.3e-7 -> 4.3e-7, dW2 9.5e-7 ->
+// 1.7e-7, features 6.1e-7 both (the float32 sums over all samples were rounded
+// 4 to 12 times as often); 100 rays of 8: dW0 2.1e-7 -> 1.8e-7, dW1 1.9e-7 both.
+//
+// Layout.  The products over samples want the samples along a lane's words,
+// the forward leaves them along the lanes: a product with the identity (exact)
+// transposes each 16x16 tile.  P2 and db1 then stay within the wavefront.  P0
+// and P1 are cut into 32x32 tiles, three per wavefront, in registers for the
+// workgroup's lifetime; the wavefronts take turns writing their batch's
+// transposed columns into one of two LDS blocks, while all of them add the
+// other one's 16 samples to their tiles.  LDS: the forward's weight fragments
+// (92.6 KB, W1 padded for its transposed reads, which are split after the
+// read), W0^T fragments (8 KB), the blocks (56 KB).
+//
+// Bound.  2.07 M samples, 8192 rays: 2.67 ms with float32 products and one row
+// block of float32 rows, 1.95 so; the matrix cores are busy 46% of it (two
+// thirds of that with the recomputed forward), the vector ALUs 30%, and two
+// wavefronts per SIMD that the turns hold in step overlap little of either.
+// ---------------------------------------------------------------------------
+constexpr int kAdjWaves = 8;
+// LDS in floats: the forward's weights, W0^T fragments for the feature
+// gradients, then two blocks, each 27 16-column tiles of 16 samples (dp1 8, h1
+// 8, dp0 8, x 3) and an unused one, and the workgroup's maxima.
+typedef F32Lds AdjLds;
+constexpr int kTH1 = 8, kTDP0 = 16, kTX = 24, kTiles = 27;
+constexpr int kAOffW0T = AdjLds::kSize;                 // [part 2][s 4][lane 64][4 words]
+constexpr int kAOffBlocks = kAOffW0T + 8 * 64 * 4;
+constexpr int kBlock = (kTiles + 1) * 256;   // [32 columns][part 2][8 samples h][column 32][4 words]
+constexpr int kAOffTops = kAOffBlocks + 2 * kBlock;
+constexpr int kALds = kAOffTops + 64;
+static_assert(kAOffBlocks % 4 == 0 && kBlock % 4 == 0, "16-byte alignment");
+static_assert(kALds * 4 <= 160 * 1024, "LDS");
+
+// v0, v1 into a float16 and a float16 remainder each
+__device__ __forceinline__ void split_pair(float v0, float v1, uint32_t &hi, uint32_t &lo)
+{
+    h2_t a, b;
+    a[0] = (_Float16)v0;
+    a[1] = (_Float16)v1;
+    hi = __builtin_bit_cast(uint32_t, a);
+    asm("" : "+v"(hi));   // one packed conversion, not two more single ones for the remainders
+    a = __builtin_bit_cast(h2_t, hi);
+    b[0] = (_Float16)fmaf((float)a[0], -1.f, v0);
+    b[1] = (_Float16)fmaf((float)a[1], -1.f, v1);
+    lo = __builtin_bit_cast(uint32_t, b);
+}
+
+typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
+
+// A 16x16 tile from sample-major registers (lane l holds columns 4 (l / 16) ..
+// + 3 of sample l % 16) to column-major ones (column l % 16 of samples 4 (l /
+// 16) .. + 3): a product with the identity, which is exact.
+__device__ __forceinline__ h4_t as_h4(uint32_t a, uint32_t b) { return __builtin_bit_cast(h4_t, u2_t{a, b}); }
+
+__device__ __forceinline__ u2_t transpose16(u2_t v, h4_t identity)
+{
+    const f4_t t = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(h4_t, v), identity,
+                                                         f4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    h4_t r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = (_Float16)t[e];
+    return __builtin_bit_cast(u2_t, r);
+}
+
+// v split into two float16 parts and transposed: the first part in words 0
+// and 1, the remainder in words 2 and 3
+__device__ __forceinline__ u4_t split_transpose(f4_t v, h4_t identity)
+{
+    u2_t hi, lo;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        uint32_t x, y;
+        split_pair(v[2 * e], v[2 * e + 1], x, y);
+        hi[e] = x;
+        lo[e] = y;
+    }
+    hi = transpose16(hi, identity);
+    lo = transpose16(lo, identity);
+    return u4_t{hi[0], hi[1], lo[0], lo[1]};
+}
+
+// k with 2^k top in [2^to, 2^(to + 1)) (0 for zero); it depends on top's exponent alone
+__device__ __forceinline__ int exp_to(float top, int to)
+{
+    return top > 0.f ? to + 127 - (int)(__float_as_uint(top) >> 23) : 0;
+}
+__device__ __forceinline__ float pow2(int k, int lim) { return ldexpf(1.f, min(max(k, -lim), lim)); }
+
+constexpr float kXScale = 64.f;         // of the encoding's sines and cosines
+constexpr float kDP0Scale = 0x1p-12f;   // of dp0 over dp1: |dp0| <= 128 max|s1 W1| |dp1| < 2^12 2^15
+constexpr int kTops = 5;                // dlogit, h1, h2, features, direction
+
+struct Scales {
+    float dl, p2, h1, h2, f, d;   // dlogit as dp1's and dp0's factor, and as P2's; the others
+};
+
+__device__ __forceinline__ uint32_t abs_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
+
+template <int CTRL> __device__ __forceinline__ uint32_t max_dpp(uint32_t v)
+{
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false));
+}
+
+// the wavefront's largest value, in its last lane
+__device__ __forceinline__ uint32_t wave_max_last(uint32_t v)
+{
+    v = max_dpp<0x111>(v);   // row_shr:1, 2, 4, 8
+    v = max_dpp<0x112>(v);
+    v = max_dpp<0x114>(v);
+    v = max_dpp<0x118>(v);
+    v = max_dpp<0x142>(v);   // row_bcast:15, 31
+    return max_dpp<0x143>(v);
+}
+
+// P0's column slot 16 u + 4 g + e is chunk 4 u + e of lane group g; the slots of
+// a wavefront's 32x32 tile
+__device__ __forceinline__ int slot_chunk(int wave, int lane)
+{
+    return 8 * (wave & 1) + 4 * ((lane >> 4) & 1) + (lane & 3);
+}
+__device__ __forceinline__ int slot_group(int lane) { return (lane >> 2) & 3; }
+
+// Two wavefronts per SIMD: a wavefront holds its batch's columns (108 VGPRs)
+// and its sums (57) between its turns at the blocks.
+__global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_adjoint(
+    GridK g, cic_mlp m, RenderBufs b, BackwardBufs bb)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    // Powers of two (exact; taken out again where gradients leave the kernel):
+    // s1 of W1, for its split, and s0 of W0's feature columns, likewise
+    float *blocks = lds + kAOffBlocks;
+    float s1, s0, w2_top;
+    bool bad;   // a value left the range of the split
+    {
+        float v[4] = {0.f, 0.f, 0.f, 0.f};   // max|W1|, max|W0|, max|W2|, the weights' sum
+        if (threadIdx.x < 384) v[2] = v[3] = fabsf(m.w2[threadIdx.x]);
+#pragma unroll
+        for (int i = 0; i < 128 * 128; i += kAdjWaves * 64) {
+            const float w = fabsf(m.w1[i + threadIdx.x]);
+            v[0] = fmaxf(v[0], w);
+            v[3] += w;
+        }
+#pragma unroll
+        for (int i = 0; i < 128 * 12; i += kAdjWaves * 64) {
+            const int e = i + threadIdx.x;
+            const float w = fabsf(m.w0[(e / 12) * 39 + e % 12]);
+            v[1] = fmaxf(v[1], w);
+            v[3] += w;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+            for (int off = kWave / 2; off > 0; off >>= 1) {
+                const float u = __shfl_xor(v[k], off, kWave);
+                v[k] = k < 3 ? fmaxf(v[k], u) : v[k] + u;
+            }
+            if (lane_id() == 0) blocks[4 * (threadIdx.x / kWave) + k] = v[k];
+        }
+        __syncthreads();
+        v[3] = 0.f;
+        for (int w = 0; w < kAdjWaves; ++w) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) v[k] = fmaxf(v[k], blocks[4 * w + k]);
+            v[3] += blocks[4 * w + 3];
+        }
+        s1 = pow2(exp_to(v[0], 4), 60);
+        s0 = pow2(exp_to(v[1], 4), 60);
+        w2_top = v[2] / s1;
+        // (the sum is not finite where a weight is not)
+        bad = __builtin_amdgcn_readfirstlane(!(v[3] < 0x1p50f && w2_top < 0x1p100f));
+    }
+    stage_weights_f32(m, lds, s1);
+    // W0^T's fragments: lane l, word e: feature l % 16 (rows 12 .. of the
+    // product are not used), unit 32 s + 16 (e / 4) + 4 (l / 16) + e % 4
+    if (threadIdx.x < 256) {
+        const int l = threadIdx.x & 63, s = threadIdx.x >> 6;
+        u4_t hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float w[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                w[u] = m.w0[(32 * s + 16 * (e >> 1) + 4 * (l >> 4) + 2 * (e & 1) + u) * 39 + min(l & 15, 11)] * s0;
+            uint32_t x, y;
+            split_pair(w[0], w[1], x, y);
+            hi[e] = x;
+            lo[e] = y;
+        }
+        ((u4_t *)(lds + kAOffW0T))[threadIdx.x] = hi;
+        ((u4_t *)(lds + kAOffW0T))[256 + threadIdx.x] = lo;
+    }
+    __syncthreads();   // (the row blocks' memory is free from here on)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    uint32_t *tops = (uint32_t *)(lds + kAOffTops);   // [wave][8]
+
+    // this workgroup's batches: the XCD's contiguous range, interleaved over
+    // its workgroups and wavefronts; every wavefront runs the same number of
+    // steps (the row-block turns are workgroup-wide)
+    const int64_t total = (int64_t)b.offsets[b.n];
+    const int64_t nbatch = (total + 15) / 16;
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, nslots = gridDim.x / kXcds;
+    const int64_t per = (nbatch + kXcds - 1) / kXcds;
+    const int64_t lo = xcd * per, hi = lo + per < nbatch ? lo + per : nbatch;
+    const int64_t first = lo + (int64_t)slot * kAdjWaves, stride = (int64_t)nslots * kAdjWaves;
+    const int64_t steps = hi > first ? (hi - first + stride - 1) / stride : 0;
+
+    // this wavefront's share of the sums (see the turns)
+    f16_t acc0, acc1[2];
+    f4_t acc2[2];        // rows 0..2: P2, row 3: db1, of unit 64 u + lane
+    float acc4 = 0.f;    // db2, channel q
+    // the scales of what the sums were made from, and the largest values so far
+    Scales sc{1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
+    uint32_t top[kTops] = {0, 0, 0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc0[r] = acc1[0][r] = acc1[1][r] = 0.f;
+    acc2[0] = acc2[1] = f4_t{0.f, 0.f, 0.f, 0.f};
+
+    for (int64_t st = 0; st < steps; ++st) {
+        // (the lane's LDS addresses are formed anew in each step: kept over the
+        // loop they would take the registers of the batch)
+        int lane = lane_id();
+        asm volatile("" : "+v"(lane));
+        const int q = lane >> 4, j = lane & 15;
+        const f2_t *w0f = (const f2_t *)(lds + AdjLds::kW0);
+        const f4_t *w2l = (const f4_t *)(lds + AdjLds::kW2);
+        const h8_t *w0t = (const h8_t *)(lds + kAOffW0T) + lane;
+        // this lane's W1 fragment in block 0 (block k at + k * kW1Block floats)
+        const float *w1f = lds + AdjLds::w1(0, lane);
+        const int64_t bt = first + st * stride + wave;
+        const int64_t s = bt * 16 + j;
+        const bool valid = bt < hi && s < total;
+        // ray order; a lane past the end works on sample 0 (in-bounds inputs,
+        // no branches around the loads) with a zero logit gradient, so it
+        // adds nothing to the weight gradients and stores nothing
+        const uint32_t rec = valid ? (uint32_t)s : 0u;
+        float x[10];
+        sample_inputs(g, b, rec, q, x);
+        // forward: layer 0 (40 -> 128), the same products in the same order
+        // as the forward kernel's full-input path
+        f4_t h1[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) h1[t] = *(const f4_t *)(lds + AdjLds::kB0 + 16 * t + 4 * q);
+#pragma unroll
+        for (int c2 = 0; c2 < 5; ++c2) {
+            f2_t a[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) a[t] = w0f[(t * 5 + c2) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    h1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][e], x[2 * c2 + e], h1[t], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h1[t][r] = relu_bits(h1[t][r]);
+        // layer 1 (128 -> 128)
+        f4_t h2[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) h2[t] = *(const f4_t *)(lds + AdjLds::kB1 + 16 * t + 4 * q);
+        {
+            f4_t a[4], an[4];
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) a[tt] = *(const f4_t *)(w1f + (tt * 8 + 0) * AdjLds::kW1Block);
+#pragma unroll
+            for (int c4 = 0; c4 < 8; ++c4) {
+#pragma unroll
+                for (int tg = 0; tg < 2; ++tg) {
+                    const int step = c4 * 2 + tg, nx = step + 1 < 16 ? step + 1 : step;
+                    const int nc4 = nx >> 1, ntg = nx & 1;
+#pragma unroll
+                    for (int tt = 0; tt < 4; ++tt)
+                        an[tt] = *(const f4_t *)(w1f + ((4 * ntg + tt) * 8 + nc4) * AdjLds::kW1Block);
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+                        for (int tt = 0; tt < 4; ++tt)
+                            h2[4 * tg + tt] =
+                                __builtin_amdgcn_mfma_f32_16x16x4f32(a[tt][rr], h1[c4][rr], h2[4 * tg + tt], 0, 0, 0);
+#pragma unroll
+                    for (int tt = 0; tt < 4; ++tt) a[tt] = an[tt];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h2[t][r] = relu_bits(h2[t][r]);
+        // output layer on the vector ALUs (every lane group ends with the
+        // three sums), sigmoid, and the logit gradient from dL/dc
+        float p0 = 0.f, p1 = 0.f, p2 = 0.f;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const f4_t wa = w2l[(q * 3 + 0) * 8 + t], wb = w2l[(q * 3 + 1) * 8 + t], wc = w2l[(q * 3 + 2) * 8 + t];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                p0 = fmaf(wa[r], h2[t][r], p0);
+                p1 = fmaf(wb[r], h2[t][r], p1);
+                p2 = fmaf(wc[r], h2[t][r], p2);
+            }
+        }
+        p0 += __shfl_xor(p0, 16, kWave);
+        p1 += __shfl_xor(p1, 16, kWave);
+        p2 += __shfl_xor(p2, 16, kWave);
+        p0 += __shfl_xor(p0, 32, kWave);
+        p1 += __shfl_xor(p1, 32, kWave);
+        p2 += __shfl_xor(p2, 32, kWave);
+        // dL/dc_k = w_k g (g = dL/dC of the sample's ray); the colour is kept
+        // for the compositing adjoint, which runs next
+        float dl[3];
+        {
+            const float pp[3] = {p0, p1, p2};
+            const float w = b.rec_w[rec];
+            const uint32_t ray = b.rec_ray[rec];
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                const float c = sigmoid_hw(pp[ch] + lds[AdjLds::kB2 + ch]);
+                const float dc = valid ? w * bb.d_rgb[3 * (int64_t)ray + ch] : 0.f;
+                dl[ch] = dc * c * (1.f - c);
+                acc4 += q == ch ? dl[ch] : 0.f;
+                if (valid && q == ch) b.rec_c[3 * (int64_t)rec + ch] = c;
+            }
+        }
+        // The workgroup's scales: powers of two that put the largest value so far
+        // of dlogit, h1, h2, the features and the direction near the top of
+        // float16's range; where one grows, the sums so far are scaled down.
+        {
+            uint32_t v[kTops] = {0, 0, 0, 0, 0};
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                v[0] = max(v[0], abs_bits(dl[ch]));
+                v[3] = max(v[3], abs_bits(x[ch]));
+            }
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    v[1] = max(v[1], __float_as_uint(h1[t][r]));   // (not negative)
+                    v[2] = max(v[2], __float_as_uint(h2[t][r]));
+                }
+            v[4] = abs_bits(x[3]);
+#pragma unroll
+            for (int k = 0; k < kTops; ++k) {
+                const uint32_t w = wave_max_last(v[k]);
+                if (lane == kWave - 1) tops[wave * 8 + k] = w;
+            }
+            __syncthreads();
+            uint32_t w = tops[lane];
+#pragma unroll
+            for (int off = 8; off < 64; off <<= 1) w = max(w, (uint32_t)__shfl_xor((int)w, off, kWave));
+            bool grown = false;
+#pragma unroll
+            for (int k = 0; k < kTops; ++k) {
+                const uint32_t u = max(top[k], (uint32_t)__builtin_amdgcn_readlane(w, k));
+                grown |= (u >> 23) != (top[k] >> 23);
+                bad |= u >= 0x70000000u;   // 2^97, and what is not finite
+                top[k] = u;
+            }
+            if (grown) {
+                Scales n;
+                auto top_of = [&](int k) { return __uint_as_float(top[k]); };
+                // (3 max|W2 / s1| max|dl| < 3 2^7 2^7)
+                const int e_dl = exp_to(top_of(0), 6) + exp_to(w2_top, 6);
+                bad |= e_dl < -120;
+                n.dl = pow2(e_dl, 120);
+                n.p2 = pow2(exp_to(top_of(0), 14), 120);
+                n.h1 = pow2(exp_to(top_of(1), 14), 120);
+                n.h2 = pow2(exp_to(top_of(2), 14), 120);
+                n.f = pow2(exp_to(top_of(3), 14), 120);
+                n.d = pow2(exp_to(top_of(4), 14), 120);
+                // (a scale grows only from the 1 of a value that was zero so far, as the sums with it are)
+                auto step = [](float to, float from) { return fminf(to / from, 1.f); };
+                const float f0 = step(n.dl, sc.dl), f1 = f0 * step(n.h1, sc.h1);
+                const float f2 = step(n.p2, sc.p2) * step(n.h2, sc.h2);
+                const int c = slot_chunk(wave, lane);
+                const float f3 = f0 * (c < 3 ? step(n.f, sc.f) : c == 3 && slot_group(lane) < 3 ? step(n.d, sc.d) : 1.f);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    acc0[r] *= f3;
+                    acc1[0][r] *= f1;
+                    acc1[1][r] *= f1;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    acc2[0][r] *= r < 3 ? f2 : f0;
+                    acc2[1][r] *= r < 3 ? f2 : f0;
+                }
+                sc = n;
+            }
+        }
+        h4_t identity, replicate;   // [k = 4 q + e][n = j]: k == n, k == n % 4
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            identity[e] = (_Float16)(4 * q + e == j ? 1.f : 0.f);
+            replicate[e] = (_Float16)(4 * q + e == (j & 3) ? 1.f : 0.f);
+        }
+        // dp1 = [h2 > 0] (W2^T dl); and this batch's P2 and db1 within the
+        // wavefront: per 16 units a product of dl^T (rows 4 (t % 4) + channel,
+        // the rest zero, so four tiles share an accumulator) and the transposed h2
+        u4_t dp1h[4], dp1l[4];   // dp1's parts, tiles 2 s and 2 s + 1 in word pairs
+        {
+            const u4_t dt = split_transpose(f4_t{dl[0] * sc.p2, dl[1] * sc.p2, dl[2] * sc.p2, 0.f}, replicate);
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) dl[ch] *= sc.dl;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const f4_t wa = w2l[(q * 3 + 0) * 8 + t], wb = w2l[(q * 3 + 1) * 8 + t], wc = w2l[(q * 3 + 2) * 8 + t];
+                f4_t v;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float u = fmaf(wa[r], dl[0], fmaf(wb[r], dl[1], wc[r] * dl[2]));
+                    v[r] = h2[t][r] > 0.f ? u : 0.f;
+                }
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    uint32_t hi, lo;
+                    split_pair(v[2 * e], v[2 * e + 1], hi, lo);
+                    dp1h[t >> 1][2 * (t & 1) + e] = hi;
+                    dp1l[t >> 1][2 * (t & 1) + e] = lo;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = h2[t][r] * sc.h2;
+                const u4_t ht = split_transpose(v, identity);
+                const bool mine = (j >> 2) == (t & 3);
+                const h4_t dh = as_h4(mine ? dt[0] : 0u, mine ? dt[1] : 0u);
+                const h4_t dlo = as_h4(mine ? dt[2] : 0u, mine ? dt[3] : 0u);
+                f4_t &a = acc2[t >> 2];
+                a = __builtin_amdgcn_mfma_f32_16x16x16f16(dlo, as_h4(ht[0], ht[1]), a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x16f16(dh, as_h4(ht[2], ht[3]), a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x16f16(dh, as_h4(ht[0], ht[1]), a, 0, 0, 0);
+                if (t & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // dh1 = W1^T dp1 (A fragments of W1^T read from the forward's W1
+        // layout and split here), dp0 = [h1 > 0] dh1
+        u4_t dp0h[4], dp0l[4];   // its parts, as dp1's
+        {
+            // lane l needs W1[16 c4 + 4 (l / 16) + rr][16 ti + l % 16]: float
+            // l % 4 of lane 16 g + 4 (l / 16) + rr of block (c4, ti), g =
+            // (l % 16) / 4; the next step's eight values are read while this
+            // step's are split
+            const float *w1l = lds + AdjLds::w1(0, 16 * (j >> 2) + 4 * q) + (lane & 3);
+            float a[8], an[8];
+            auto read8 = [&](int idx, float w[8]) {
+                const int ti = idx >> 2, s = idx & 3;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = w1l[((2 * s + (e >> 2)) * 8 + ti) * AdjLds::kW1Block + (e & 3) * 4];
+            };
+            read8(0, a);
+#pragma unroll
+            for (int ti = 0; ti < 8; ++ti) {
+                f4_t d = f4_t{0.f, 0.f, 0.f, 0.f}, dlow = d;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const int idx = 4 * ti + s;
+                    read8(idx + 1 < 32 ? idx + 1 : idx, an);
+                    u4_t hi, lo;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        uint32_t x, y;
+                        split_pair(a[2 * e], a[2 * e + 1], x, y);
+                        hi[e] = x;
+                        lo[e] = y;
+                    }
+                    const h8_t wh = __builtin_bit_cast(h8_t, hi), wl = __builtin_bit_cast(h8_t, lo);
+                    const h8_t ph = __builtin_bit_cast(h8_t, dp1h[s]), pl = __builtin_bit_cast(h8_t, dp1l[s]);
+                    dlow = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl, ph, dlow, 0, 0, 0);
+                    dlow = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, pl, dlow, 0, 0, 0);
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, ph, d, 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) a[e] = an[e];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                d += dlow;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    uint32_t x, y;
+                    split_pair(h1[ti][2 * e] > 0.f ? d[2 * e] * kDP0Scale : 0.f,
+                               h1[ti][2 * e + 1] > 0.f ? d[2 * e + 1] * kDP0Scale : 0.f, x, y);
+                    dp0h[ti >> 1][2 * (ti & 1) + e] = x;
+                    dp0l[ti >> 1][2 * (ti & 1) + e] = y;
+                }
+            }
+        }
+        // feature gradient (W0^T dp0)[0:12] of the sample (ray order)
+        {
+            f4_t df = f4_t{0.f, 0.f, 0.f, 0.f}, low = df;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const h8_t wh = w0t[s * 64], wl = w0t[(4 + s) * 64];
+                const h8_t ph = __builtin_bit_cast(h8_t, dp0h[s]), pl = __builtin_bit_cast(h8_t, dp0l[s]);
+                low = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl, ph, low, 0, 0, 0);
+                low = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, pl, low, 0, 0, 0);
+                df = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, ph, df, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) df[r] = (df[r] + low[r]) * (1.f / sc.dl) * (1.f / (kDP0Scale * s0));
+            if (valid && q < 3) *(f4_t *)(bb.rec_df + (int64_t)rec * 12 + 4 * q) = df;
+        }
+        // weight gradients.  This batch's columns: split and transposed
+        u4_t cols[kTiles];
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) {
+            if (t < kTH1 || (t >= kTDP0 && t < kTX)) {
+                const int u = t & 7;
+                const u4_t hi = t < kTH1 ? dp1h[u >> 1] : dp0h[u >> 1], lo = t < kTH1 ? dp1l[u >> 1] : dp0l[u >> 1];
+                const u2_t a = transpose16(u2_t{hi[2 * (u & 1)], hi[2 * (u & 1) + 1]}, identity);
+                const u2_t c = transpose16(u2_t{lo[2 * (u & 1)], lo[2 * (u & 1) + 1]}, identity);
+                cols[t] = u4_t{a[0], a[1], c[0], c[1]};
+            } else {
+                f4_t v;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int c = t < kTDP0 ? 0 : 4 * (t - kTX) + r;
+                    if (t < kTDP0) v[r] = h1[t - kTH1][r] * sc.h1;
+                    else if (c < 3) v[r] = x[c] * sc.f;
+                    else if (c == 3) v[r] = q < 3 ? x[3] * sc.d : kXScale;   // (1 in the padding slot)
+                    else v[r] = c < 10 ? x[c] * kXScale : 0.f;
+                }
+                cols[t] = split_transpose(v, identity);
+            }
+            if (t < kTH1) {   // db1
+                const uint32_t one = j == 4 * (t & 3) + 3 ? 0x3c003c00u : 0u;
+                f4_t &a = acc2[t >> 2];
+                a = __builtin_amdgcn_mfma_f32_16x16x16f16(as_h4(one, one), as_h4(cols[t][2], cols[t][3]), a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x16f16(as_h4(one, one), as_h4(cols[t][0], cols[t][1]), a, 0, 0, 0);
+            }
+            if ((t & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        auto write_block = [&](float *blk) {
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t) {
+                u2_t *dst = (u2_t *)(blk + (t >> 1) * 512 + ((q >> 1) * 32 + (t & 1) * 16 + j) * 4 + (q & 1) * 2);
+                dst[0] = u2_t{cols[t][0], cols[t][1]};
+                dst[128] = u2_t{cols[t][2], cols[t][3]};
+            }
+        };
+        // The wavefronts take turns at the two row blocks: turn t works on
+        // wavefront t's while wavefront t + 1 writes the other.
+        // P1: rows 32 (wave / 2) .., columns 64 (wave % 2) .. as two 32x32
+        // tiles; P0: rows 32 (wave / 2) .., column slots 32 (wave % 2) ..
+        const int ta = wave >> 1, tb = 4 + 2 * (wave & 1), tc = 8 + (wave >> 1), td = 12 + (wave & 1);
+        if (wave == 0) write_block(blocks);
+#pragma unroll 1
+        for (int turn = 0; turn < kAdjWaves; ++turn) {
+            __syncthreads();   // this turn's block is written, the other one consumed
+            if (wave == turn + 1) write_block(blocks + ((turn + 1) & 1) * kBlock);
+            const float *blk = blocks + (turn & 1) * kBlock + lane * 4;
+            auto frag = [&](int tile, int part) {
+                return *(const h8_t *)(blk + tile * 512 + part * 256);
+            };
+            const h8_t ah = frag(ta, 0), al = frag(ta, 1);
+            const h8_t ch = frag(tb, 0), cl = frag(tb, 1), dh = frag(tb + 1, 0), dlo = frag(tb + 1, 1);
+            const h8_t eh = frag(tc, 0), el = frag(tc, 1), xh = frag(td, 0), xl = frag(td, 1);
+            acc1[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, ch, acc1[0], 0, 0, 0);
+            acc1[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, dh, acc1[1], 0, 0, 0);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(el, xh, acc0, 0, 0, 0);
+            acc1[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, cl, acc1[0], 0, 0, 0);
+            acc1[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, dlo, acc1[1], 0, 0, 0);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(eh, xl, acc0, 0, 0, 0);
+            acc1[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, ch, acc1[0], 0, 0, 0);
+            acc1[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, dh, acc1[1], 0, 0, 0);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(eh, xh, acc0, 0, 0, 0);
+        }
+    }
+    // the workgroup's partial
+    const int lane = lane_id(), q = lane >> 4, j = lane & 15;
+    float *out = bb.partials + (int64_t)blockIdx.x * kPartialFloats;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int row = 32 * (wave >> 1) + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), col = lane & 31;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            out[kPart1 + row * 128 + 64 * (wave & 1) + 32 * u + col] = acc1[u][r] * (1.f / sc.dl) * (1.f / sc.h1) * s1;
+        const int c = slot_chunk(wave, lane), g = slot_group(lane), src = c < 10 ? l0_input(c, g) : 0;
+        const float sx = c < 3 ? sc.f : c == 3 && g < 3 ? sc.d : kXScale;
+        if (c < 10) out[row * 48 + (src >= 0 ? src : 39)] = acc0[r] * (1.f / sc.dl) * (1.f / sx) * (1.f / kDP0Scale);
+    }
+    // the others added up over the wavefronts in order
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) acc4 += __shfl_xor(acc4, off, kWave);
+    __syncthreads();   // the row blocks are consumed
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) blocks[wave * 516 + r * 128 + 64 * u + lane] = acc2[u][r];
+    if (j == 0) blocks[wave * 516 + 512 + q] = acc4;
+    __syncthreads();
+    for (int i = threadIdx.x; i < 515; i += kAdjWaves * 64) {
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < kAdjWaves; ++k) v += blocks[k * 516 + i];
+        if (i < 384) v = v * (1.f / sc.p2) * (1.f / sc.h2) * (1.f / s1);
+        else if (i < 512) v = v * (1.f / sc.dl) * s1;
+        out[kPart2 + i] = v;
+    }
+    const int redo = __syncthreads_or(bad);
+    if (threadIdx.x == 0) out[kRedoFlag] = redo ? 1.f : 0.f;
+}
+
+// ---------------------------------------------------------------------------
+// The same in float32 throughout, for the workgroups that met a value outside
+// the split's range (the flag in their partial): the same batches, every
+// output overwritten.  Each wavefront owns some of the 105 16x16 output tiles
 //   P0 = dp0^T [x|1|h1[0:8]]   (128 x 48: dW0 and, in column 39, db0)
 //   P1 = dp1^T h1              (128 x 128: dW1)
 //   P2 = dl^T h2               (16 x 128: dW2 in rows 0..2)
 //   P3 = dp1^T [x|1][32:48]    (128 x 16: db1 in column 7)
 //   P4 = dl^T [x|1][32:48]     (16 x 16: db2 in column 7)
-// on FP32 MFMA with the samples as the reduction index.  Each wavefront
-// owns some of the 105 16x16 output tiles and keeps them in registers for
-// the workgroup's lifetime; the workgroup's wavefronts take turns writing
-// their batch's per-sample rows [x|1, h1, h2, dp0, dlogit, dp1] into one LDS
-// row block, and after each write every wavefront adds that block's 16
-// samples to its tiles.  One partial per workgroup, summed in a fixed order
-// by k_wgrad_apply (deterministic).  LDS: the forward's weight fragments
-// (92.6 KB, W1 padded for its transposed reads), W0^T fragments for the
-// feature gradients (8 KB), the row block (37.9 KB).
+// on FP32 MFMA; the wavefronts take turns writing their batch's per-sample
+// rows [x|1, h1, h2, dp0, dlogit, dp1] into one LDS row block, and after each
+// write every wavefront adds that block's 16 samples to its tiles.
 // ---------------------------------------------------------------------------
 constexpr int kWgTiles = 24 + 64 + 8 + 8 + 1;
-constexpr int kAdjWaves = 8;
 constexpr int kAdjTPW = (kWgTiles + kAdjWaves - 1) / kAdjWaves;
 // Row of the LDS block: the staged vectors at the offsets below, padded so
 // that an MFMA operand read (16 consecutive columns of 4 consecutive rows)
 // puts the 64 lanes on 64 distinct banks (row stride 16 mod 64 words).
 constexpr int kAdjRow = kStDP1 + 128 + 24;
 static_assert(kAdjRow % 64 == 16, "adjoint LDS row stride");
-typedef F32Lds AdjLds;                                    // forward weights, W1 padded
-constexpr int kAOffW0T = AdjLds::kSize;                  // [c4 8][lane 64][4]
-constexpr int kAOffRows = kAOffW0T + 8 * 64 * 4;        // [16][kAdjRow]
-constexpr int kALds = kAOffRows + 16 * kAdjRow;
+constexpr int kFOffW0T = AdjLds::kSize;                  // [c4 8][lane 64][4]
+constexpr int kFOffRows = kFOffW0T + 8 * 64 * 4;        // [16][kAdjRow]
+constexpr int kFLds = kFOffRows + 16 * kAdjRow;
 
 struct WgTile {
-    int a_col, b_col, out;   // row columns of A and B, offset of the 16x16 tile in the partial
-    int ld;                  // row length of the partial matrix
+    int a_col, b_col, out;   // row columns of A and B, offset in the partial
+    int ld, rows, col;       // row length of the partial's matrix, rows it has; >= 0: its only column
 };
 
 __device__ __forceinline__ WgTile wg_tile(int t)
 {
-    constexpr int P1 = 128 * 48, P2 = P1 + 128 * 128, P3 = P2 + 16 * 128, P4 = P3 + 128 * 16;
     if (t < 24) {
         const int mt = t / 3, nt = t % 3;
-        return {kStDP0 + 16 * mt, kStX + 16 * nt, (16 * mt) * 48 + 16 * nt, 48};
+        return {kStDP0 + 16 * mt, kStX + 16 * nt, (16 * mt) * 48 + 16 * nt, 48, 16, -1};
     }
     t -= 24;
     if (t < 64) {
         const int mt = t / 8, nt = t % 8;
-        return {kStDP1 + 16 * mt, kStH1 + 16 * nt, P1 + (16 * mt) * 128 + 16 * nt, 128};
+        return {kStDP1 + 16 * mt, kStH1 + 16 * nt, kPart1 + (16 * mt) * 128 + 16 * nt, 128, 16, -1};
     }
     t -= 64;
-    if (t < 8) return {kStDL, kStH2 + 16 * t, P2 + 16 * t, 128};
+    if (t < 8) return {kStDL, kStH2 + 16 * t, kPart2 + 16 * t, 128, 3, -1};
     t -= 8;
-    if (t < 8) return {kStDP1 + 16 * t, kStX + 32, P3 + (16 * t) * 16, 16};
-    return {kStDL, kStX + 32, P4, 16};
+    if (t < 8) return {kStDP1 + 16 * t, kStX + 32, kPart3 + 16 * t, 1, 16, 7};
+    return {kStDL, kStX + 32, kPart4, 1, 3, 7};
 }
 
 // Two wavefronts per SIMD: a wavefront holds its batch's h1, h2, dp0, dp1
 // (128 VGPRs) and its output tiles (56) between its turns at the row block.
-__global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_adjoint(
+__global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_adjoint_f32(
     GridK g, cic_mlp m, RenderBufs b, BackwardBufs bb)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    stage_weights_f32(m, lds);
+    float *out = bb.partials + (int64_t)blockIdx.x * kPartialFloats;
+    if (out[kRedoFlag] == 0.f) return;   // uniform per block
+    stage_weights_f32(m, lds, 1.f);
     for (int i = threadIdx.x; i < 8 * 64 * 4; i += blockDim.x) {
         const int rr = i & 3, l = (i >> 2) & 63, c4 = i >> 8;
         const int col = l & 15;
-        lds[kAOffW0T + i] = col < 12 ? m.w0[(16 * c4 + 4 * (l >> 4) + rr) * 39 + col] : 0.f;
+        lds[kFOffW0T + i] = col < 12 ? m.w0[(16 * c4 + 4 * (l >> 4) + rr) * 39 + col] : 0.f;
     }
     __syncthreads();
     const int lane = lane_id(), q = lane >> 4, j = lane & 15;
     const int wave = threadIdx.x / 64;
     const f2_t *w0f = (const f2_t *)(lds + AdjLds::kW0);
     const f4_t *w2l = (const f4_t *)(lds + AdjLds::kW2);
-    const f4_t *w0t = (const f4_t *)(lds + kAOffW0T);
+    const f4_t *w0t = (const f4_t *)(lds + kFOffW0T);
     // this lane's W1 fragment in block 0 (block k at + k * kW1Block floats)
     const float *w1f = lds + AdjLds::w1(0, lane);
-    float *rows = lds + kAOffRows;
+    float *rows = lds + kFOffRows;
 
     // this workgroup's batches: the XCD's contiguous range, interleaved over
     // its workgroups and wavefronts; every wavefront runs the same number of
@@ -615,14 +1228,17 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
             }
         }
     }
-    float *out = bb.partials + (int64_t)blockIdx.x * kPartialFloats;
 #pragma unroll
     for (int i = 0; i < kAdjTPW; ++i) {
         const int t = wave + kAdjWaves * i;
         if (t < kWgTiles) {
             const WgTile w = wg_tile(t);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) out[w.out + (4 * (lane >> 4) + r) * w.ld + (lane & 15)] = acc[i][r];
+            for (int r = 0; r < 4; ++r) {
+                const int row = 4 * (lane >> 4) + r, col = lane & 15;
+                if (row < w.rows && (w.col < 0 || col == w.col))
+                    out[w.out + row * w.ld + (w.col < 0 ? col : 0)] = acc[i][r];
+            }
         }
     }
 }
@@ -637,7 +1253,6 @@ constexpr int kApplyOut = 64, kApplyGroups = 16;
 
 __device__ __forceinline__ bool wgrad_entry(int e, int &src, float *&dst, const BackwardBufs &bb)
 {
-    constexpr int P1 = 128 * 48, P2 = P1 + 128 * 128, P3 = P2 + 16 * 128, P4 = P3 + 128 * 16;
     if (e < 128 * 39) {
         src = (e / 39) * 48 + e % 39;
         dst = bb.d_w0 + e;
@@ -647,19 +1262,19 @@ __device__ __forceinline__ bool wgrad_entry(int e, int &src, float *&dst, const 
         dst = bb.d_b0 + o;
     } else if (e < 128 * 39 + 128 + 128 * 128) {
         const int k = e - (128 * 39 + 128);
-        src = P1 + k;
+        src = kPart1 + k;
         dst = bb.d_w1 + k;
     } else if (e < 128 * 39 + 128 + 128 * 128 + 3 * 128) {
         const int k = e - (128 * 39 + 128 + 128 * 128);
-        src = P2 + k;
+        src = kPart2 + k;
         dst = bb.d_w2 + k;
     } else if (e < 128 * 39 + 128 + 128 * 128 + 3 * 128 + 128) {
         const int o = e - (128 * 39 + 128 + 128 * 128 + 3 * 128);
-        src = P3 + o * 16 + 7;
+        src = kPart3 + o;
         dst = bb.d_b1 + o;
     } else if (e < 128 * 39 + 128 + 128 * 128 + 3 * 128 + 128 + 3) {
         const int ch = e - (128 * 39 + 128 + 128 * 128 + 3 * 128 + 128);
-        src = P4 + ch * 16 + 7;
+        src = kPart4 + ch;
         dst = bb.d_b2 + ch;
     } else {
         return false;
@@ -693,14 +1308,16 @@ __global__ __launch_bounds__(kApplyOut * kApplyGroups) void k_wgrad_apply(const 
 
 void launch_mlp_adjoint(const GridK &g, const cic_mlp &m, const RenderBufs &b, const BackwardBufs &bb, hipStream_t s)
 {
-    const int lds = kALds * (int)sizeof(float);
+    const int lds = kALds * (int)sizeof(float), lds_f32 = kFLds * (int)sizeof(float);
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute((const void *)k_mlp_adjoint, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        (void)hipFuncSetAttribute((const void *)k_mlp_adjoint_f32, hipFuncAttributeMaxDynamicSharedMemorySize, lds_f32);
         attr_set = true;
     }
     const int nblk = std::min(num_cus_b(), kWgBlocks);
     hipLaunchKernelGGL(k_mlp_adjoint, dim3(nblk), dim3(kAdjWaves * 64), lds, s, g, m, b, bb);
+    hipLaunchKernelGGL(k_mlp_adjoint_f32, dim3(nblk), dim3(kAdjWaves * 64), lds_f32, s, g, m, b, bb);
     const int n_out = 128 * 39 + 128 + 128 * 128 + 3 * 128 + 128 + 3;
     hipLaunchKernelGGL(k_wgrad_apply, dim3((n_out + kApplyOut - 1) / kApplyOut), dim3(kApplyOut * kApplyGroups), 0, s,
                        (const float *)bb.partials, nblk, bb);

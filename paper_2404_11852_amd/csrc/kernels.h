@@ -47,11 +47,11 @@ struct RenderBufs {
                            // persistent kernels' grids
 };
 
-// Per-sample row of MLP vectors the adjoint's weight gradients read from LDS:
-// inputs with a constant 1 in the padding slot (so the bias gradients fall
-// out of the same products), both hidden activations, the first hidden
-// layer's pre-activation gradient, the output-logit gradient (16 wide, 3
-// used) and the second hidden layer's pre-activation gradient.
+// Per-sample row of MLP vectors the float32 adjoint's weight gradients read from LDS:
+// inputs with a constant 1 in the padding slot (so db0 falls out of the same
+// product), both hidden activations, the first hidden layer's pre-activation
+// gradient, the output-logit gradient (3, padded) and the second hidden
+// layer's pre-activation gradient.
 constexpr int kStX = 0, kStH1 = 40, kStH2 = 168, kStDP0 = 296, kStDL = 424, kStDP1 = 440;
 
 // scan.hip
@@ -124,9 +124,11 @@ struct BackwardBufs {
 // 9^3 vertices x (12 feature + 1 density) gradient channels per brick tile
 constexpr int kFgTileFloats = (kBrick + 1) * (kBrick + 1) * (kBrick + 1) * 13;
 constexpr int kWgBlocks = 1024;
-// per-block partial products: dp0^T[x|1] (128x48), dp1^T h1 (128x128),
-// dl^T h2 (16x128), dp1^T ones (128x16), dl^T ones (16x16)
-constexpr int kPartialFloats = 128 * 48 + 128 * 128 + 16 * 128 + 128 * 16 + 16 * 16;
+// per-block partial sums: dp0^T [x|1|..] (128x48), dp1^T h1 (128x128),
+// dl^T h2 (3x128), dp1 (128), dl (3, padded to 4)
+constexpr int kPart1 = 128 * 48, kPart2 = kPart1 + 128 * 128, kPart3 = kPart2 + 3 * 128, kPart4 = kPart3 + 128;
+constexpr int kRedoFlag = kPart4 + 3;   // not 0: the split adjoint met a value out of its range
+constexpr int kPartialFloats = kPart4 + 4;
 void launch_backward_composite(const GridK &g, const OptsK &o, const RenderBufs &b, const BackwardBufs &bb,
                                hipStream_t s);
 // recomputed forward, MLP backward and weight gradients, fused (ray order);

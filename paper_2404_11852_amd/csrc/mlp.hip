@@ -44,11 +44,6 @@
 
 namespace cic {
 
-typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
-typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-typedef float f16_t __attribute__((ext_vector_type(16)));
-typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-
 constexpr int kFwdWaves = 8;    // wavefronts of the CU's one workgroup
 constexpr int kFwdBatch = 32;   // samples per wavefront batch
 

@@ -10,7 +10,6 @@ namespace cic {
 // a ray: for each lane half 15 values and a zero; half 0: the direction and
 // the 12 sines, half 1: the 12 cosines and three ones (layer 0's bias).  Four
 // threads per ray, three encoding arguments each.
-typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void k_ray_encode_bf16(RenderBufs b)
 {
     __shared__ __attribute__((aligned(16))) __bf16 rows[64][32];   // stored 16 bytes per thread
@@ -458,7 +457,6 @@ __device__ __forceinline__ void hash_level3_tiled(const GridK &g, const LevelTil
 // ---------------------------------------------------------------------------
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 
-typedef float f16_t __attribute__((ext_vector_type(16)));
 typedef short s4_t __attribute__((ext_vector_type(4)));
 
 // LDS layout in 16-byte fragments, then floats

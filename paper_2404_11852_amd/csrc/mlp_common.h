@@ -11,6 +11,10 @@ namespace cic {
 
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef float f2_t __attribute__((ext_vector_type(2)));
+typedef float f16_t __attribute__((ext_vector_type(16)));
+typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 
 // Input index (0..38, or -1 for padding) of chunk c for lane group q.
 __host__ __device__ __forceinline__ int l0_input(int c, int q)
@@ -31,7 +35,8 @@ __device__ __forceinline__ float pick3(int i, float a, float b, float c) { retur
 // of output row ch), biases.  4 floats after every 16 lanes of a W1 block keep
 // the fragment reads conflict-free, and put a read of W1 transposed (lane l
 // taking row 16 c4 + 4 (l/16) + rr, column 16 ti + l%16) on 64 distinct banks
-// instead of 16.
+// instead of 16.  W1 and its bias are held times the power of two s1, W2
+// divided by it (exact, and without effect on the outputs).
 struct F32Lds {
     static constexpr int kW1Block = 272;
     static constexpr int kW0 = 0;
@@ -48,7 +53,7 @@ struct F32Lds {
     }
 };
 
-__device__ __forceinline__ void stage_weights_f32(const cic_mlp &m, float *lds)
+__device__ __forceinline__ void stage_weights_f32(const cic_mlp &m, float *lds, float s1)
 {
     typedef F32Lds L;
     const int nt = blockDim.x;
@@ -60,15 +65,15 @@ __device__ __forceinline__ void stage_weights_f32(const cic_mlp &m, float *lds)
     for (int i = threadIdx.x; i < 8 * 32 * 64; i += nt) {
         const int l = i & 63, c = (i >> 6) & 31, t = i >> 11;
         const int row = 16 * t + (l & 15), col = 16 * (c >> 2) + 4 * (l >> 4) + (c & 3);
-        lds[L::w1(t * 8 + (c >> 2), l) + (c & 3)] = m.w1[row * 128 + col];
+        lds[L::w1(t * 8 + (c >> 2), l) + (c & 3)] = m.w1[row * 128 + col] * s1;
     }
     for (int i = threadIdx.x; i < 384; i += nt) {
         const int q = i / 96, ch = (i / 32) % 3, t = (i / 4) % 8, r = i & 3;
-        lds[L::kW2 + i] = m.w2[ch * 128 + 16 * t + 4 * q + r];
+        lds[L::kW2 + i] = m.w2[ch * 128 + 16 * t + 4 * q + r] * (1.f / s1);
     }
     for (int i = threadIdx.x; i < 128; i += nt) {
         lds[L::kB0 + i] = m.b0[i];
-        lds[L::kB1 + i] = m.b1[i];
+        lds[L::kB1 + i] = m.b1[i] * s1;
     }
     if (threadIdx.x < 3) lds[L::kB2 + threadIdx.x] = m.b2[threadIdx.x];
 }
