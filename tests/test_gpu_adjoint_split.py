@@ -99,3 +99,15 @@ def test_scale_edges(seed):
     o, d = synth.random_rays(500, seed=seed)
     d_rgb = np.repeat(rng.uniform(1.0, 2.0, (500, 1)).astype(np.float32), 3, axis=1) * np.float32(1e-3)
     _check(q, 24, o, d, d_rgb)
+
+
+@pytest.mark.parametrize("n,dims", [(600, (18, 10, 26)), (2500, (9, 9, 9)), (40, (70, 66, 74))])
+def test_segments(n, dims):
+    """Feature gradients of bricks with 0 to over 512 samples (several segments)
+    and of 1 to over 512 bricks (one or two levels of the segment's search)."""
+    print_case("feature gradients, %d rays, grid %dx%dx%d" % (n, *dims))
+    dens, feats = synth.make_scene(80, seed=2)
+    a, b, c = dims
+    p = Pair(0, dens=np.ascontiguousarray(dens[:a, :b, :c]), feats=np.ascontiguousarray(feats[:a, :b, :c]),
+             mlp=synth.make_mlp(3, bias_std=0.1))
+    _check(p, 50, *_case(n))
