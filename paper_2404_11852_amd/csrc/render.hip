@@ -564,8 +564,8 @@ constexpr int64_t kHistMin = 2048;   // fewest rays of the LDS path
 // 16 wavefronts per block: the rays' dependent load chains overlap across
 // wavefronts (measured on eight 800x800 views with 256 rays per block:
 // compaction + sort 6.5 ms with 4 wavefronts per block, 4.9 ms with 8, 4.7 ms
-// with 16).  A pass of 2^21 rays takes 488 us, 687 when each ray's loads began
-// after the ray before it and the weights were copied too.
+// with 16).  Mean pass of those views, 95 M samples: 488 us, 687 when each ray's
+// loads began after the ray before it and the weights were copied too.
 constexpr int kHistThreads = 1024;
 // Rays per block: 256 where that still gives 512 blocks, else fewer, down to
 // one per wavefront; 0 = the per-run global atomics.
@@ -643,7 +643,8 @@ __global__ __launch_bounds__(256) void k_brick_scatter(RenderBufs b)
 // samples are one contiguous range of records: count the block's samples
 // per brick in LDS, reserve each touched brick's share of the global cursor
 // with one atomic, then hand out positions from the LDS cursors (one LDS
-// atomic per run of equal bricks).
+// atomic per run of equal bricks).  Bound by the latency of the keys' loads: with
+// four chunks' keys in flight a pass of 95 M samples takes 305 us, one by one 399.
 __global__ __launch_bounds__(kHistThreads) void k_brick_scatter_hist(RenderBufs b, int rays)
 {
     extern __shared__ uint32_t hist[];
@@ -653,13 +654,26 @@ __global__ __launch_bounds__(kHistThreads) void k_brick_scatter_hist(RenderBufs 
     const int64_t ray0 = (int64_t)blockIdx.x * rays;
     const int64_t ray1 = ray0 + rays < b.n ? ray0 + rays : b.n;
     const uint32_t s0 = b.offsets[ray0], s1 = b.offsets[ray1];
-    for (uint32_t w0 = s0 + (uint32_t)wave * kWave; w0 < s1; w0 += (uint32_t)nwaves * kWave) {
-        const uint32_t sidx = w0 + lane;
-        const bool act = sidx < s1;
-        const uint32_t key = act ? b.rec_key[sidx] : 0xffffffffu;
-        const int active = (int)min(s1 - w0, (uint32_t)kWave);
-        const uint64_t heads = run_heads(key, act);
-        if ((heads >> lane) & 1ull) atomicAdd(&hist[key], (uint32_t)run_length(heads, active));
+    constexpr int kAhead = 4;
+    const uint32_t stride = (uint32_t)nwaves * kWave;
+    auto load_keys = [&](uint32_t w0, uint32_t key[kAhead]) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t sidx = w0 + u * stride + lane;
+            key[u] = sidx < s1 ? b.rec_key[sidx] : 0xffffffffu;
+        }
+    };
+    for (uint32_t w0 = s0 + (uint32_t)wave * kWave; w0 < s1; w0 += kAhead * stride) {
+        uint32_t key[kAhead];
+        load_keys(w0, key);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t at = w0 + u * stride;
+            if (at >= s1) break;
+            const uint64_t heads = run_heads(key[u], at + lane < s1);
+            if ((heads >> lane) & 1ull)
+                atomicAdd(&hist[key[u]], (uint32_t)run_length(heads, (int)min(s1 - at, (uint32_t)kWave)));
+        }
     }
     __syncthreads();
     for (int64_t i = threadIdx.x; i < b.n_bricks; i += blockDim.x) {
@@ -667,18 +681,23 @@ __global__ __launch_bounds__(kHistThreads) void k_brick_scatter_hist(RenderBufs 
         if (c) hist[i] = atomicAdd(&b.brick_off[i], c);
     }
     __syncthreads();
-    for (uint32_t w0 = s0 + (uint32_t)wave * kWave; w0 < s1; w0 += (uint32_t)nwaves * kWave) {
-        const uint32_t sidx = w0 + lane;
-        const bool act = sidx < s1;
-        const uint32_t key = act ? b.rec_key[sidx] : 0xffffffffu;
-        const int active = (int)min(s1 - w0, (uint32_t)kWave);
-        const uint64_t heads = run_heads(key, act);
-        uint32_t base = 0;
-        if ((heads >> lane) & 1ull) base = atomicAdd(&hist[key], (uint32_t)run_length(heads, active));
-        const uint64_t upto = heads & ((lane == kWave - 1) ? ~0ull : ((2ull << lane) - 1ull));
-        const int head = upto ? (63 - __clzll((long long)upto)) : 0;
-        const uint32_t hb = __shfl(base, head, kWave);
-        if (act) b.perm[hb + (uint32_t)(lane - head)] = sidx;
+    for (uint32_t w0 = s0 + (uint32_t)wave * kWave; w0 < s1; w0 += kAhead * stride) {
+        uint32_t key[kAhead];
+        load_keys(w0, key);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t at = w0 + u * stride;
+            if (at >= s1) break;
+            const bool act = at + lane < s1;
+            const uint64_t heads = run_heads(key[u], act);
+            uint32_t base = 0;
+            if ((heads >> lane) & 1ull)
+                base = atomicAdd(&hist[key[u]], (uint32_t)run_length(heads, (int)min(s1 - at, (uint32_t)kWave)));
+            const uint64_t upto = heads & ((lane == kWave - 1) ? ~0ull : ((2ull << lane) - 1ull));
+            const int head = upto ? (63 - __clzll((long long)upto)) : 0;
+            const uint32_t hb = __shfl(base, head, kWave);
+            if (act) b.perm[hb + (uint32_t)(lane - head)] = at + lane;
+        }
     }
 }
 
@@ -769,7 +788,9 @@ void launch_fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s)
 // of the MLP stage).  The four rays' loads go out together, which is what a
 // stage bound by the latency of its dependent loads needs (measured on eight
 // 800x800 views: 1.55 ms with 16 lanes per ray, 1.82 with 8, 1.64 with 32,
-// 2.37 with a wavefront per ray).
+// 2.37 with a wavefront per ray), and four samples of each lane with them (mean
+// pass of those views, 95 M samples: 349 -> 325 us, 4.7 TB/s of the samples' 16
+// bytes).
 constexpr int kReduceLanes = 16;
 constexpr int kReduceRays = kRayWaves * (kWave / kReduceLanes);   // rays per 256-thread block
 
@@ -798,12 +819,24 @@ __global__ __launch_bounds__(256) void k_reduce(RenderBufs b, OptsK op, float *r
     const uint32_t cnt = active ? b.count[ray] : 0u, off = active ? b.offsets[ray] : 0u;
     float r = 0.f, gg = 0.f, bb = 0.f;
     const float *ws = b.slot_w + ray * (int64_t)b.n_samples;
-    for (uint32_t j = (uint32_t)sub; j < cnt; j += kReduceLanes) {
-        const int64_t k = (int64_t)off + j;
-        const float w = ws[j];
-        r = fmaf(w, b.rec_c[3 * k], r);
-        gg = fmaf(w, b.rec_c[3 * k + 1], gg);
-        bb = fmaf(w, b.rec_c[3 * k + 2], bb);
+    for (uint32_t j0 = (uint32_t)sub; j0 < cnt; j0 += 4 * kReduceLanes) {
+        // four samples' loads in flight (one past the count re-reads the first and adds nothing)
+        float w[4], c[4][3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t j = j0 + u * kReduceLanes < cnt ? j0 + u * kReduceLanes : j0;
+            const float *p = b.rec_c + 3 * ((int64_t)off + j);
+            w[u] = ws[j];
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) c[u][ch] = p[ch];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool in = j0 + u * kReduceLanes < cnt;
+            r = in ? fmaf(w[u], c[u][0], r) : r;
+            gg = in ? fmaf(w[u], c[u][1], gg) : gg;
+            bb = in ? fmaf(w[u], c[u][2], bb) : bb;
+        }
     }
     r = group16_sum(r);
     gg = group16_sum(gg);
