@@ -389,9 +389,11 @@ void launch_feature_grads_bricks(const GridK &g, const RenderBufs &b, const Back
 // read), W0^T fragments (8 KB), the blocks (56 KB).
 //
 // Bound.  2.07 M samples, 8192 rays: 2.67 ms with float32 products and one row
-// block of float32 rows, 1.95 so; the matrix cores are busy 46% of it (two
-// thirds of that with the recomputed forward), the vector ALUs 30%, and two
-// wavefronts per SIMD that the turns hold in step overlap little of either.
+// block of float32 rows, 1.87 so; the matrix cores are busy 48% of it (two
+// thirds of that with the recomputed forward, whose float32 MFMA no vector
+// instruction runs beside), the vector ALUs 28%, and a third of the wavefronts'
+// time are waits (halves of the workgroup half a step apart, so that one's
+// forward runs beside the other's backward, took the same time).
 // ---------------------------------------------------------------------------
 constexpr int kAdjWaves = 8;
 // LDS in floats: the forward's weights, W0^T fragments for the feature
@@ -416,8 +418,13 @@ __device__ __forceinline__ void split_pair(float v0, float v1, uint32_t &hi, uin
     hi = __builtin_bit_cast(uint32_t, a);
     asm("" : "+v"(hi));   // one packed conversion, not two more single ones for the remainders
     a = __builtin_bit_cast(h2_t, hi);
-    b[0] = (_Float16)fmaf((float)a[0], -1.f, v0);
-    b[1] = (_Float16)fmaf((float)a[1], -1.f, v1);
+    // v - hi (exact), rounded to float16: one mixed-precision multiply-add each,
+    // which the compiler does not use where it knows the factor to be -1 (the
+    // kernel 1.95 -> 1.91 ms)
+    float minus = -1.f;
+    asm("" : "+s"(minus));
+    b[0] = (_Float16)fmaf((float)a[0], minus, v0);
+    b[1] = (_Float16)fmaf((float)a[1], minus, v1);
     lo = __builtin_bit_cast(uint32_t, b);
 }
 
@@ -496,6 +503,22 @@ __device__ __forceinline__ int slot_chunk(int wave, int lane)
     return 8 * (wave & 1) + 4 * ((lane >> 4) & 1) + (lane & 3);
 }
 __device__ __forceinline__ int slot_group(int lane) { return (lane >> 2) & 3; }
+
+// The layer-0 inputs of a lane group q that depend on the ray alone, once per
+// ray, in the rows that the forward pass uses for z0 (8192 rays: 5 us; per
+// sample they are three sincosf a lane: the adjoint 1.91 -> 1.87 ms): row of a
+// ray: [q 4][8], 7 used.
+__global__ __launch_bounds__(256) void k_ray_encode(RenderBufs b)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, ray = t >> 2;
+    if (ray >= b.n) return;
+    const float d[3] = {b.rays_d[3 * ray], b.rays_d[3 * ray + 1], b.rays_d[3 * ray + 2]};
+    float x[7];
+    encode_group(d, (int)(t & 3), x);
+    f4_t *row = (f4_t *)b.z0 + 2 * t;
+    row[0] = f4_t{x[0], x[1], x[2], x[3]};
+    row[1] = f4_t{x[4], x[5], x[6], 0.f};
+}
 
 // Two wavefronts per SIMD: a wavefront holds its batch's columns (108 VGPRs)
 // and its sums (57) between its turns at the blocks.
@@ -611,7 +634,24 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
         // adds nothing to the weight gradients and stores nothing
         const uint32_t rec = valid ? (uint32_t)s : 0u;
         float x[10];
-        sample_inputs(g, b, rec, q, x);
+        const uint32_t ray = b.rec_ray[rec];
+        {
+            const f4_t *row = (const f4_t *)b.z0 + 2 * (4 * (int64_t)ray + q);
+            const f4_t e0 = row[0], e1 = row[1];
+            SampleRay r;
+            load_sample_ray(b, ray, b.rec_k[rec], r);
+            int i0[3];
+            float fr[3], tk;
+            sample_voxel(r.o, r.d, r.tn, r.delta, r.k, g, i0, fr, tk);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) x[c] = trilerp1((const float *)g.features, g, i0, fr, 12, 3 * q + c);
+            x[3] = e0[0];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x[4 + c] = e0[1 + c];
+                x[7 + c] = e1[c];
+            }
+        }
         // forward: layer 0 (40 -> 128), the same products in the same order
         // as the forward kernel's full-input path
         f4_t h1[8];
@@ -691,7 +731,6 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
         {
             const float pp[3] = {p0, p1, p2};
             const float w = b.rec_w[rec];
-            const uint32_t ray = b.rec_ray[rec];
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
                 const float c = sigmoid_hw(pp[ch] + lds[AdjLds::kB2 + ch]);
@@ -1351,6 +1390,7 @@ void launch_mlp_adjoint(const GridK &g, const cic_mlp &m, const RenderBufs &b, c
         attr_set = true;
     }
     const int nblk = std::min(num_cus_b(), kWgBlocks);
+    hipLaunchKernelGGL(k_ray_encode, dim3((unsigned)((4 * b.n + 255) / 256)), dim3(256), 0, s, b);
     hipLaunchKernelGGL(k_mlp_adjoint, dim3(nblk), dim3(kAdjWaves * 64), lds, s, g, m, b, bb);
     hipLaunchKernelGGL(k_mlp_adjoint_f32, dim3(nblk), dim3(kAdjWaves * 64), lds_f32, s, g, m, b, bb);
     const int n_out = 128 * 39 + 128 + 128 * 128 + 3 * 128 + 128 + 3;

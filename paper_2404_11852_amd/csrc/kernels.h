@@ -32,7 +32,8 @@ struct RenderBufs {
     float *rec_c;          // [n*N*3] MLP colour per live sample
     float *slot_t;         // [n*N] transmittance T_k of live samples (adjoint only; nullable)
     float *rec_t;          // [n*N] compacted T_k (adjoint only; nullable)
-    float *z0;             // [n][128] per-ray direction term of layer 0, times 2^e0 (FP32 compute)
+    float *z0;             // [n][128] per-ray direction term of layer 0, times 2^e0 (FP32 compute);
+                           // in the adjoint [n][32], the direction's inputs of layer 0
     uint32_t *enc;         // [n][16] per-ray view encoding in BF16: lane half h's inputs in words 8h..8h+7
     // voxel order
     uint32_t *rec_key;     // [n*N] brick of each live sample
