@@ -184,66 +184,76 @@ __device__ int stage_weights_split(const cic_mlp &m, float *lds)
 // then forms output o for every ray with its 27 weights held in registers.
 // The weight rows (whose first 12 entries give e0) and the rays are loaded
 // together, before the first barrier.  64 rays per block amortise the weight
-// reads in large passes; small ones take 16, so that the launch spreads over
-// the chip (4096 rays: 19.4 -> 7.3 us; 85,581: 16 per block 22.7, 64 27.3;
+// reads in large passes; small ones, and the holes of a warped frame, take 16,
+// so that the launch spreads over the chip (4096 rays: 19.4 -> 7.3 us; 85,581: 16 per block 22.7, 64 27.3;
 // 640,000: 110 and 90).
-template <int RAYS>
+template <int RAYS, bool COUNTED>
 __global__ __launch_bounds__(128) void k_ray_embed(cic_mlp m, RenderBufs b, float *z0)
 {
     __shared__ __attribute__((aligned(16))) float pe[RAYS][28];
     __shared__ uint32_t live[RAYS];
     __shared__ float red[2];
     const int o = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * RAYS;
-    // a pass over a device-counted set of rays (the holes of a warped frame)
-    // skips the blocks past its count, whose rays have no live samples
-    if (b.n_active && (uint64_t)base >= *b.n_active) return;
+    // (a device-counted pass, the holes of a warped frame, has rays up to its count)
+    const int64_t n = COUNTED ? min((int64_t)*b.n_active, b.n) : b.n;
+    if ((int64_t)blockIdx.x * RAYS >= n) return;
     float w[39];
 #pragma unroll
     for (int i = 0; i < 39; ++i) w[i] = m.w0[o * 39 + i];
     const float bias = m.b0[o];
-    for (int r = threadIdx.x; r < RAYS; r += 128) live[r] = base + r < b.n ? b.count[base + r] : 0u;
-    // entries 0..2: the direction; argument k = 4c + octave (k < 12): sine at
-    // 3 + k, cosine at 15 + k (also for rays without live samples: their
-    // entries are not used)
-    for (int e = threadIdx.x; e < RAYS * 15; e += 128) {
-        const int r = e / 15, i = e % 15;
-        if (base + r >= b.n) continue;
-        const float *d = b.rays_d + 3 * (base + r);
-        if (i < 3) {
-            pe[r][i] = d[i];
-        } else {
-            const int k = i - 3, c = k >> 2, oc = k & 3;
-            float sn, cs;
-            sincosf(ldexpf(d[c], oc), &sn, &cs);
-            pe[r][3 + k] = sn;
-            pe[r][15 + k] = cs;
+    int e0 = 0;
+    const int64_t first = (int64_t)blockIdx.x * RAYS;
+    for (int64_t base = first; base < n; base += (int64_t)gridDim.x * RAYS) {
+        if (base != first) __syncthreads();   // the rays before are done with
+        for (int r = threadIdx.x; r < RAYS; r += 128) live[r] = base + r < n ? b.count[base + r] : 0u;
+        // entries 0..2: the direction; argument k = 4c + octave (k < 12): sine at
+        // 3 + k, cosine at 15 + k (also for rays without live samples: their
+        // entries are not used)
+        for (int e = threadIdx.x; e < RAYS * 15; e += 128) {
+            const int r = e / 15, i = e % 15;
+            if (base + r >= n) continue;
+            const float *d = b.rays_d + 3 * (base + r);
+            if (i < 3) {
+                pe[r][i] = d[i];
+            } else {
+                const int k = i - 3, c = k >> 2, oc = k & 3;
+                float sn, cs;
+                sincosf(ldexpf(d[c], oc), &sn, &cs);
+                pe[r][3 + k] = sn;
+                pe[r][15 + k] = cs;
+            }
         }
-    }
-    float top = 0.f;
+        if (base == first) {
+            float top = 0.f;
 #pragma unroll
-    for (int i = 0; i < 12; ++i) top = fmaxf(top, fabsf(w[i]));
-    const int e0 = block_exp(block_max(top, red), 0);   // its barrier also covers pe and live
-    for (int r = 0; r < RAYS; ++r) {
-        if (!live[r]) continue;
-        float acc = bias;
+            for (int i = 0; i < 12; ++i) top = fmaxf(top, fabsf(w[i]));
+            e0 = block_exp(block_max(top, red), 0);   // its barrier also covers pe and live
+        } else {
+            __syncthreads();
+        }
+        for (int r = 0; r < RAYS; ++r) {
+            if (!live[r]) continue;
+            float acc = bias;
 #pragma unroll
-        for (int i = 0; i < 27; ++i) acc = fmaf(w[12 + i], pe[r][i], acc);
-        z0[(base + r) * 128 + o] = ldexpf(acc, e0);
+            for (int i = 0; i < 27; ++i) acc = fmaf(w[12 + i], pe[r][i], acc);
+            z0[(base + r) * 128 + o] = ldexpf(acc, e0);
+        }
+        if constexpr (!COUNTED) break;   // one group per block
     }
 }
 
-template <int RAYS>
+template <int RAYS, bool COUNTED>
 static void launch_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_ray_embed<RAYS>, dim3((unsigned)((b.n + RAYS - 1) / RAYS)), dim3(128), 0, s, m, b, b.z0);
+    hipLaunchKernelGGL((k_ray_embed<RAYS, COUNTED>), ray_grid(b, RAYS), dim3(128), 0, s, m, b, b.z0);
 }
 
 void launch_ray_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s)
 {
     if (b.n == 0 || m.compute != CIC_F32) return;
-    if (b.n < 131072) launch_embed<16>(m, b, s);
-    else launch_embed<64>(m, b, s);
+    if (b.n_active) launch_embed<16, true>(m, b, s);
+    else if (b.n < 131072) launch_embed<16, false>(m, b, s);
+    else launch_embed<64, false>(m, b, s);
 }
 
 // The colour of one sample on the vector ALUs in float32, by a whole
