@@ -9,7 +9,7 @@
 // are kept times 2^11, so they are normal float16 values wherever the first
 // part is one; weights are scaled by powers of two to use float16's range,
 // and a sample whose features or activations leave it (65504, after the
-// scaling of layer 0) is computed again in plain float32.  The low products
+// scaling of layer 0) is computed again with float32 products.  The low products
 // have their own accumulators, so the high ones are rounded 8 times over a
 // 128-long sum where a float32 chain rounds 128 times.  Colour error against
 // 64 bits, rms over 300,000 single-sample rays: 2.80e-8, and 2.90e-8 for the
@@ -53,7 +53,7 @@ constexpr int kXW0 = kXW1 + 2 * 4 * 8 * 64;      // [t 4][s 3][lane 64]
 constexpr int kXFrags = kXW0 + 4 * 3 * 64;
 constexpr int kXB1 = 0, kXW2 = 128;              // [128]; [t 4][i 4][h 2][ch 4][r 4]
 constexpr int kXB2 = kXW2 + 512, kXFloats = kXB2 + 4;
-constexpr int kXLdsBytes = kXFrags * 16 + kXFloats * 4;
+constexpr int kXLdsBytes = std::max(kXFrags * 16 + kXFloats * 4, F32Lds::kSize * 4);
 constexpr float kLoScale = 2048.f;               // the low parts are kept times 2^11
 
 // v0, v1 into a float16 and a second float16 that holds the remainder times
@@ -256,43 +256,79 @@ void launch_ray_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s)
     else launch_embed<64, false>(m, b, s);
 }
 
-// The colour of one sample on the vector ALUs in float32, by a whole
-// wavefront (lane l holds hidden units l and l + 64): for the samples whose
-// features or activations leave the range in which the split is exact.
+// float32 MFMA for the samples whose features or activations leave the range of
+// the split: 16 samples per step of a wavefront, 16x16x4 products as in the
+// adjoint's recomputed forward, the weights staged anew over the split's.
+// Bound by the float32 products: a call of 1.6 M samples takes 0.37 ms, 0.94 when
+// all of them come here (13.0 with a wavefront per sample on the vector ALUs,
+// which read W1 from memory for each).
 template <typename T, bool HASH>
-__device__ void redo_sample(const GridK &g, const cic_mlp &m, const RenderBufs &b, int64_t rec, int e0)
+__device__ __forceinline__ void colours_f32(const GridK &g, const RenderBufs &b, const float *lds, uint32_t rec,
+                                            bool write, int e0)
 {
-    const int lane = lane_id();
+    typedef F32Lds L;
+    const int lane = lane_id(), q = lane >> 4;
+    const f2_t *w0f = (const f2_t *)(lds + L::kW0);
+    const f4_t *w2l = (const f4_t *)(lds + L::kW2);
+    const float *w1f = lds + L::w1(0, lane);   // (block k at + k * kW1Block floats)
     SampleRay r;
     load_sample_ray(b, b.rec_ray[rec], b.rec_k[rec], r);
-    Gather<T, HASH> gt;
-    float xp[3];
-    sample_position(r, xp);
-    gt.issue(g, xp, lane & 1);
-    float x[6];
+    float x[3];
+    {
+        Gather<T, HASH> gt;
+        float xp[3], f[6];
+        sample_position(r, xp);
+        gt.issue(g, xp, q >> 1);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) x[k] = gt.feature(k);
-    float h1[2], h2[2];
+        for (int k = 0; k < 6; ++k) f[k] = gt.feature(k);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int row = lane + 64 * u;
-        float acc = ldexpf(b.z0[(int64_t)r.ray * 128 + row], -e0);
-#pragma unroll
-        for (int k = 0; k < 12; ++k) acc = fmaf(m.w0[row * 39 + k], __shfl(x[k % 6], k / 6, kWave), acc);
-        h1[u] = relu_bits(acc);
-        h2[u] = m.b1[row];
+        for (int c = 0; c < 3; ++c) x[c] = q & 1 ? f[3 + c] : f[c];
     }
-    for (int k = 0; k < 128; ++k) {
-        const float hk = __shfl(k < 64 ? h1[0] : h1[1], k & 63, kWave);
-        h2[0] = fmaf(m.w1[lane * 128 + k], hk, h2[0]);
-        h2[1] = fmaf(m.w1[(lane + 64) * 128 + k], hk, h2[1]);
+    f4_t h1[8], h2[8];
+    const float *zr = b.z0 + (int64_t)r.ray * 128 + 4 * q;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const f4_t z = *(const f4_t *)(zr + 16 * t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h1[t][e] = ldexpf(z[e], -e0);
+        h2[t] = *(const f4_t *)(lds + L::kB1 + 16 * t + 4 * q);
     }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            h1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w0f[(t * 5 + (c >> 1)) * 64 + lane][c & 1], x[c], h1[t], 0, 0, 0);
+#pragma unroll
+    for (int c4 = 0; c4 < 8; ++c4) {
+#pragma unroll
+        for (int tg = 0; tg < 2; ++tg) {
+            f4_t a[4];
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) a[tt] = *(const f4_t *)(w1f + ((4 * tg + tt) * 8 + c4) * L::kW1Block);
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const float h = relu_bits(h1[c4][rr]);
+#pragma unroll
+                for (int tt = 0; tt < 4; ++tt)
+                    h2[4 * tg + tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[tt][rr], h, h2[4 * tg + tt], 0, 0, 0);
+            }
+        }
+    }
+    float p[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            const f4_t w = w2l[(q * 3 + ch) * 8 + t];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[ch] = fmaf(w[e], relu_bits(h2[t][e]), p[ch]);
+        }
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
-        const float p = wave_sum(fmaf(m.w2[ch * 128 + lane], relu_bits(h2[0]),
-                                      m.w2[ch * 128 + 64 + lane] * relu_bits(h2[1])));
-        if (lane == ch) b.rec_c[3 * rec + ch] = sigmoid_hw(p + m.b2[ch]);
+        p[ch] += __shfl_xor(p[ch], 16, kWave);
+        p[ch] += __shfl_xor(p[ch], 32, kWave);
     }
+    if (write && q < 3) b.rec_c[3 * (int64_t)rec + q] = sigmoid_hw(pick3(q, p[0], p[1], p[2]) + lds[L::kB2 + q]);
 }
 
 constexpr uint32_t kRedo = 0x7fc0c0deu;   // a NaN that marks a colour to be redone
@@ -517,14 +553,16 @@ k_mlp_fwd_f32(GridK g, cic_mlp m, RenderBufs b, int voxel)
         }
     }
     if (!__syncthreads_or(redo)) return;
+    // (every wavefront is past the barrier, so the split's weights are done with)
+    stage_weights_f32(m, lds, 1.f);
+    __syncthreads();
     for (uint32_t k = wave;; k += kFwdWaves) {
         const uint32_t rbt = batch_of(k);
         if (rbt >= bcount) break;
-        for (int i = 0; i < kFwdBatch; ++i) {
-            const uint32_t s = (bfirst + rbt) * kFwdBatch + i;
-            if (s >= total) break;
-            const int64_t rec = voxel ? b.perm[s] : s;
-            if (__float_as_uint(b.rec_c[3 * rec]) == kRedo) redo_sample<T, HASH>(g, m, b, rec, e0);
+        for (uint32_t s0 = (bfirst + rbt) * kFwdBatch, end = s0 + kFwdBatch; s0 < end && s0 < total; s0 += 16) {
+            const uint32_t s = min(s0 + (lane & 15), total - 1), rec = voxel ? b.perm[s] : s;
+            const bool marked = __float_as_uint(b.rec_c[3 * (int64_t)rec]) == kRedo;
+            if (__builtin_amdgcn_ballot_w64(marked)) colours_f32<T, HASH>(g, b, lds, rec, marked, e0);
         }
     }
 }
