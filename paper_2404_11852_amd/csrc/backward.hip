@@ -480,22 +480,6 @@ struct Scales {
 
 __device__ __forceinline__ uint32_t abs_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
-template <int CTRL> __device__ __forceinline__ uint32_t max_dpp(uint32_t v)
-{
-    return max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false));
-}
-
-// the wavefront's largest value, in its last lane
-__device__ __forceinline__ uint32_t wave_max_last(uint32_t v)
-{
-    v = max_dpp<0x111>(v);   // row_shr:1, 2, 4, 8
-    v = max_dpp<0x112>(v);
-    v = max_dpp<0x114>(v);
-    v = max_dpp<0x118>(v);
-    v = max_dpp<0x142>(v);   // row_bcast:15, 31
-    return max_dpp<0x143>(v);
-}
-
 // P0's column slot 16 u + 4 g + e is chunk 4 u + e of lane group g; the slots of
 // a wavefront's 32x32 tile
 __device__ __forceinline__ int slot_chunk(int wave, int lane)

@@ -455,8 +455,6 @@ __device__ __forceinline__ void hash_level3_tiled(const GridK &g, const LevelTil
 // lane's own sample.  Every kernel below runs the same sums in the same order
 // for a sample, so ray and voxel order give the same bits.
 // ---------------------------------------------------------------------------
-typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
-
 typedef short s4_t __attribute__((ext_vector_type(4)));
 
 // LDS layout in 16-byte fragments, then floats
@@ -468,15 +466,6 @@ constexpr int kBfB1 = 0, kBfB2 = 128, kBfFloats = 132;
 constexpr int kLdsBf16 = kBfFrags * 16 + kBfFloats * 4;
 static_assert(kLdsBf16 + (kFTileFloats + kSegWords) * 4 <= 160 * 1024 - 1024, "brick tile kernel LDS");
 static_assert(kLdsBf16 + kHSegWords * 4 + kHTileBytes <= 160 * 1024 - 2048, "level box kernel LDS");
-
-// part p of float32 b split into three BF16 values b0 + b1 + b2 = b (each
-// remainder is exact in float32, and the last has at most 8 significant bits)
-__device__ __forceinline__ float bf16_part(float b, int p)
-{
-    const float hi = (float)(__bf16)b, r1 = b - hi;
-    const float mid = (float)(__bf16)r1, r2 = r1 - mid;
-    return p == 0 ? hi : p == 1 ? mid : r2;
-}
 
 // (every load goes out before the first conversion: a small launch waits for
 // one round trip to memory here)
@@ -532,15 +521,6 @@ __device__ void stage_weights_bf16(const cic_mlp &m, bf8_t *frag, float *fl)
     if (tid < 512) ((__bf16 *)(frag + kBfW2))[tid] = (__bf16)(ch2 < 3 ? v2 : 0.f);
     if (tid < 128) fl[kBfB1 + tid] = vb1;
     if (tid < 4) fl[kBfB2 + tid] = tid < 3 ? vb2 : 0.f;
-}
-
-__device__ __forceinline__ uint32_t pack_bf2(float a, float b)
-{
-    typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
-    bf2_t v;
-    v[0] = (__bf16)a;
-    v[1] = (__bf16)b;
-    return __builtin_bit_cast(uint32_t, v);
 }
 
 // ReLU of BF16 values as 16-bit integers: a negative BF16 (sign bit set) is

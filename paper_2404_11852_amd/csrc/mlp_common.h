@@ -15,6 +15,7 @@ typedef float f16_t __attribute__((ext_vector_type(16)));
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 
 // Input index (0..38, or -1 for padding) of chunk c for lane group q.
 __host__ __device__ __forceinline__ int l0_input(int c, int q)
@@ -256,6 +257,40 @@ __device__ __forceinline__ void interleave_mfma()
 __host__ __device__ __forceinline__ int x_hid(int c, int h, int e)
 {
     return 16 * c + 8 * (e >> 2) + 4 * h + (e & 3);
+}
+
+// part p of float32 b split into three BF16 values b0 + b1 + b2 = b (each
+// remainder is exact in float32, and the last has at most 8 significant bits)
+__device__ __forceinline__ float bf16_part(float b, int p)
+{
+    const float hi = (float)(__bf16)b, r1 = b - hi;
+    const float mid = (float)(__bf16)r1, r2 = r1 - mid;
+    return p == 0 ? hi : p == 1 ? mid : r2;
+}
+
+__device__ __forceinline__ uint32_t pack_bf2(float a, float b)
+{
+    typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+    bf2_t v;
+    v[0] = (__bf16)a;
+    v[1] = (__bf16)b;
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+template <int CTRL> __device__ __forceinline__ uint32_t max_dpp(uint32_t v)
+{
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false));
+}
+
+// the wavefront's largest value, in its last lane
+__device__ __forceinline__ uint32_t wave_max_last(uint32_t v)
+{
+    v = max_dpp<0x111>(v);   // row_shr:1, 2, 4, 8
+    v = max_dpp<0x112>(v);
+    v = max_dpp<0x114>(v);
+    v = max_dpp<0x118>(v);
+    v = max_dpp<0x142>(v);   // row_bcast:15, 31
+    return max_dpp<0x143>(v);
 }
 
 // Output sigmoid from the hardware base-2 exponential and reciprocal:

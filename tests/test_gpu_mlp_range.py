@@ -1,0 +1,83 @@
+"""Float32 MLP over models that compute the same function at other magnitudes:
+powers of two moved between features, layers and hidden units.  Plain float32
+arithmetic gives the same bits for all of them, so an exact evaluation may not
+tell them apart either.
+
+Tolerance: the largest error against float64 may be twice that of the model as
+it was, and two units in the last place of 1 more (the sums are rounded
+elsewhere)."""
+import numpy as np
+import pytest
+import torch
+
+import helpers
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+ULP = 2.0 ** -23
+
+
+def _parts():
+    dens, feats = synth.make_scene(24, seed=0)
+    return np.full_like(dens, 50.0), feats, synth.make_mlp(1, bias_std=0.05)
+
+
+def _rays(n):
+    o, d = synth.random_rays(n + 40, seed=21, aim_half=1.2)
+    return np.ascontiguousarray(o[-n:]), np.ascontiguousarray(d[-n:])
+
+
+def _render(pair, o, d):
+    import paper_2404_11852_amd as cic
+    rgb, _, _ = cic.render_rays(pair.gpu, cic.make_opts(1), torch.from_numpy(o).cuda(), torch.from_numpy(d).cuda())
+    return helpers.to_np(rgb)
+
+
+def _error(dens, feats, mlp):
+    o, d = _rays(1500)
+    pair = helpers.Pair(24, dens=dens, feats=feats, mlp=mlp, shift=0.0)
+    want, _, _ = oracle.render_rays(pair.orc, oracle.opts(1, 0.0), o, d)
+    return np.abs(_render(pair, o, d).astype(np.float64) - want).max()
+
+
+def _scaled(what, k):
+    dens, feats, mlp = _parts()
+    s = np.float32(2.0 ** k)
+    if what == "channel":     # one feature channel and its column
+        feats[..., 3] /= s
+        mlp["w0"][:, 3] *= s
+    elif what == "features":  # all of them
+        feats /= s
+        mlp["w0"][:, :12] *= s
+    elif what == "outlier":   # a large weight on a channel that is zero everywhere
+        feats[..., 3] = 0
+        mlp["w0"][5, 3] = s
+    elif what == "layer1":    # first activations
+        mlp["w0"], mlp["b0"], mlp["w1"] = mlp["w0"] / s, mlp["b0"] / s, mlp["w1"] * s
+    elif what == "unit1":     # some of them
+        mlp["w0"][::3] /= s
+        mlp["b0"][::3] /= s
+        mlp["w1"][:, ::3] *= s
+    elif what == "layer2":    # second activations
+        mlp["w1"], mlp["b1"], mlp["w2"] = mlp["w1"] / s, mlp["b1"] / s, mlp["w2"] * s
+    elif what == "unit2":
+        mlp["w1"][::3] /= s
+        mlp["b1"][::3] /= s
+        mlp["w2"][:, ::3] *= s
+    return dens, feats, mlp
+
+
+@pytest.mark.parametrize("what,k", [
+    ("channel", 10), ("channel", 14), ("channel", 24), ("channel", 40), ("channel", -14), ("channel", -40),
+    ("features", 24), ("features", 30), ("features", -24), ("features", 60), ("outlier", 10), ("outlier", 14),
+    ("outlier", 40), ("layer1", 20), ("layer1", 30), ("layer1", 50), ("layer1", -30), ("unit1", 14), ("unit1", 19),
+    ("unit1", 24), ("unit1", 40), ("unit1", -19), ("unit1", -30), ("layer2", 30), ("layer2", -30), ("unit2", 14),
+    ("unit2", 19), ("unit2", 30), ("unit2", -19), ("unit2", -30)])
+def test_magnitudes(what, k):
+    helpers.print_case("float32 MLP, %s x 2^%d" % (what, -k))
+    plain = _error(*(_scaled("outlier", 0) if what == "outlier" else _parts()))
+    got = _error(*_scaled(what, k))
+    print("max error %.2e, as it was %.2e" % (got, plain))
+    assert got <= 2 * plain + 2 * ULP
