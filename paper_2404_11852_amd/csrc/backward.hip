@@ -366,17 +366,32 @@ void launch_feature_grads_bricks(const GridK &g, const RenderBufs &b, const Back
 //   P2 = dl^T h2 (dW2), and the sums of dp1 (db1) and dl (db2).
 //
 // Arithmetic.  Everything after the forward multiplies values split into two
-// float16 parts, v = hi + lo, as hi hi + hi lo + lo hi on float16 MFMA (16
-// times the float32 rate), summed in float32.  Every factor is scaled by a
-// power of two first, so that its remainders are normal float16 numbers down
-// to 2^-17 of its largest value: W1 and W0 by their maxima, dl, h1, h2, the
-// features and the direction by the largest value the workgroup has met (its
-// sums are scaled down where one grows).  Values that no such scale fits (2^97
-// and beyond, infinities, NaN) set a flag, and k_mlp_adjoint_f32 does that
-// workgroup's share again.  Gradient error against 64 bits, rms over seeds: 3000
-// rays of 96 samples dW0 8.3e-7 -> 5.1e-7, dW1 7.3e-7 -> 4.3e-7, dW2 9.5e-7 ->
-// 1.7e-7, features 6.1e-7 both (the float32 sums over all samples were rounded
+// float16 parts, v = hi + lo, as hi hi + hi lo + lo hi on float16 MFMA (16 times
+// the float32 rate), summed in float32.  Every factor is scaled by a power of
+// two first, to a largest value in [2^14, 2^15) (dp1 below 3 2^14, mostly near
+// 2^11); a remainder is then exact to 2^-25, 2^-39 of the largest value that
+// shares its scale, and a normal float16 number down to 2^-17 of it:
+//  - in the products that stay with a sample (dp1 -> dh1 -> dp0 -> the feature
+//    gradients) dp1 and dp0 have scales of that sample, by its dlogit and its
+//    largest dp0, so its feature gradients do not depend on any other sample;
+//  - W1 has one scale, W0 one per feature;
+//  - in the products over samples (the weight gradients) the workgroup's 128
+//    samples of a step have one for dp1 and one for dp0, and the activations and
+//    the direction one each and the features one per channel, by the largest so
+//    far.  What a sample's dlogit (its dp0) is below the step's largest, 2^-d, is
+//    carried half by each of its two factors, so that entries to which only such
+//    samples add keep float32's bits down to d = 30.  From step to step the sums
+//    are brought to the new scale, which is exact.
+// k_mlp_adjoint_f32 does a workgroup's share again where the scales do not hold
+// a value (dlogit or dp0 from about 2^100, inputs and activations from 2^51,
+// infinities, NaN), where its rays' upstream gradients are more than 2^36
+// apart, or W1's rows or columns more than 2^12 in their largest entries.
+// Gradient error against 64 bits, rms over seeds, float32 products -> these:
+// 3000 rays of 96 samples dW0 8.3e-7 -> 5.1e-7, dW1 7.3e-7 -> 4.3e-7, dW2 9.5e-7
+// -> 1.8e-7, features 6.1e-7 both (the float32 sums over all samples were rounded
 // 4 to 12 times as often); 100 rays of 8: dW0 2.1e-7 -> 1.8e-7, dW1 1.9e-7 both.
+// With one scale for all that a workgroup met (1.90 ms), feature gradients of
+// rays 2^-24 below others were off by 1% and rows of dW0 by 7%.
 //
 // Layout.  The products over samples want the samples along a lane's words,
 // the forward leaves them along the lanes: a product with the identity (exact)
@@ -389,44 +404,27 @@ void launch_feature_grads_bricks(const GridK &g, const RenderBufs &b, const Back
 // read), W0^T fragments (8 KB), the blocks (56 KB).
 //
 // Bound.  2.07 M samples, 8192 rays: 2.67 ms with float32 products and one row
-// block of float32 rows, 1.87 so; the matrix cores are busy 48% of it (two
-// thirds of that with the recomputed forward, whose float32 MFMA no vector
-// instruction runs beside), the vector ALUs 28%, and a third of the wavefronts'
-// time are waits (halves of the workgroup half a step apart, so that one's
-// forward runs beside the other's backward, took the same time).
+// block of float32 rows, 2.10 so.  Of the 1.90 ms with one scale per workgroup
+// the matrix cores were busy 48% (two thirds of that with the recomputed forward,
+// whose float32 MFMA no vector instruction runs beside), the vector ALUs 28%, and
+// a third of the wavefronts' time were waits (halves of the workgroup half a step
+// apart, so that one's forward runs beside the other's backward, took the same
+// time).
 // ---------------------------------------------------------------------------
 constexpr int kAdjWaves = 8;
 // LDS in floats: the forward's weights, W0^T fragments for the feature
 // gradients, then two blocks, each 27 16-column tiles of 16 samples (dp1 8, h1
-// 8, dp0 8, x 3) and an unused one, and the workgroup's maxima.
+// 8, dp0 8, x 3) and an unused one, W0's scales and the step's maxima.
 typedef F32Lds AdjLds;
 constexpr int kTH1 = 8, kTDP0 = 16, kTX = 24, kTiles = 27;
 constexpr int kAOffW0T = AdjLds::kSize;                 // [part 2][s 4][lane 64][4 words]
 constexpr int kAOffBlocks = kAOffW0T + 8 * 64 * 4;
 constexpr int kBlock = (kTiles + 1) * 256;   // [32 columns][part 2][8 samples h][column 32][4 words]
-constexpr int kAOffTops = kAOffBlocks + 2 * kBlock;
-constexpr int kALds = kAOffTops + 64;
-static_assert(kAOffBlocks % 4 == 0 && kBlock % 4 == 0, "16-byte alignment");
+constexpr int kAOffS0 = kAOffBlocks + 2 * kBlock;   // [16] W0's scales taken out again, per feature
+constexpr int kAOffTops = kAOffS0 + 16;             // [wave 8][16] the step's largest values
+constexpr int kALds = kAOffTops + 128;
+static_assert(kAOffBlocks % 4 == 0 && kBlock % 4 == 0 && kAOffS0 % 4 == 0, "16-byte alignment");
 static_assert(kALds * 4 <= 160 * 1024, "LDS");
-
-// v0, v1 into a float16 and a float16 remainder each
-__device__ __forceinline__ void split_pair(float v0, float v1, uint32_t &hi, uint32_t &lo)
-{
-    h2_t a, b;
-    a[0] = (_Float16)v0;
-    a[1] = (_Float16)v1;
-    hi = __builtin_bit_cast(uint32_t, a);
-    asm("" : "+v"(hi));   // one packed conversion, not two more single ones for the remainders
-    a = __builtin_bit_cast(h2_t, hi);
-    // v - hi (exact), rounded to float16: one mixed-precision multiply-add each,
-    // which the compiler does not use where it knows the factor to be -1 (the
-    // kernel 1.95 -> 1.91 ms)
-    float minus = -1.f;
-    asm("" : "+s"(minus));
-    b[0] = (_Float16)fmaf((float)a[0], minus, v0);
-    b[1] = (_Float16)fmaf((float)a[1], minus, v1);
-    lo = __builtin_bit_cast(uint32_t, b);
-}
 
 typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
@@ -446,15 +444,36 @@ __device__ __forceinline__ u2_t transpose16(u2_t v, h4_t identity)
     return __builtin_bit_cast(u2_t, r);
 }
 
-// v split into two float16 parts and transposed: the first part in words 0
-// and 1, the remainder in words 2 and 3
-__device__ __forceinline__ u4_t split_transpose(f4_t v, h4_t identity)
+// v0 and v1 times `scale` into a float16 and a float16 remainder each
+__device__ __forceinline__ void split_pair(float v0, float v1, float scale, uint32_t &hi, uint32_t &lo)
+{
+    h2_t a, b;
+    v0 *= scale;
+    v1 *= scale;
+    a[0] = (_Float16)v0;
+    a[1] = (_Float16)v1;
+    hi = __builtin_bit_cast(uint32_t, a);
+    asm("" : "+v"(hi));   // one packed conversion, not two more single ones for the remainders
+    a = __builtin_bit_cast(h2_t, hi);
+    // v - hi (exact), rounded to float16: one mixed-precision multiply-add each,
+    // which the compiler does not use where it knows the factor to be -1 (the
+    // kernel 1.95 -> 1.91 ms)
+    float minus = -1.f;
+    asm("" : "+s"(minus));
+    b[0] = (_Float16)fmaf((float)a[0], minus, v0);
+    b[1] = (_Float16)fmaf((float)a[1], minus, v1);
+    lo = __builtin_bit_cast(uint32_t, b);
+}
+
+// the same of four values, transposed: the first parts in words 0 and 1, the
+// remainders in words 2 and 3
+__device__ __forceinline__ u4_t split_transpose(f4_t v, float scale, h4_t identity)
 {
     u2_t hi, lo;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
         uint32_t x, y;
-        split_pair(v[2 * e], v[2 * e + 1], x, y);
+        split_pair(v[2 * e], v[2 * e + 1], scale, x, y);
         hi[e] = x;
         lo[e] = y;
     }
@@ -463,20 +482,49 @@ __device__ __forceinline__ u4_t split_transpose(f4_t v, h4_t identity)
     return u4_t{hi[0], hi[1], lo[0], lo[1]};
 }
 
-// k with 2^k top in [2^to, 2^(to + 1)) (0 for zero); it depends on top's exponent alone
-__device__ __forceinline__ int exp_to(float top, int to)
+// the largest of a value over the four lanes j, j + 16, j + 32, j + 48, in each of them
+__device__ __forceinline__ uint32_t across_rows_max(uint32_t v)
 {
-    return top > 0.f ? to + 127 - (int)(__float_as_uint(top) >> 23) : 0;
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = max((uint32_t)a[0], (uint32_t)a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return max((uint32_t)b[0], (uint32_t)b[1]);
 }
-__device__ __forceinline__ float pow2(int k, int lim) { return ldexpf(1.f, min(max(k, -lim), lim)); }
 
-constexpr float kXScale = 64.f;         // of the encoding's sines and cosines
-constexpr float kDP0Scale = 0x1p-12f;   // of dp0 over dp1: |dp0| <= 128 max|s1 W1| |dp1| < 2^12 2^15
-constexpr int kTops = 5;                // dlogit, h1, h2, features, direction
+// both float16 of a word times f
+__device__ __forceinline__ uint32_t scale_h2(uint32_t v, float f)
+{
+    const h2_t a = __builtin_bit_cast(h2_t, v), b = {(_Float16)f, (_Float16)f};
+    return __builtin_bit_cast(uint32_t, a * b);
+}
 
-struct Scales {
-    float dl, p2, h1, h2, f, d;   // dlogit as dp1's and dp0's factor, and as P2's; the others
-};
+// the largest of a value over the 16 lanes of a row, in each of them
+__device__ __forceinline__ uint32_t row_max(uint32_t v)
+{
+    v = max_dpp<0x121>(v);   // row_ror:1, 2, 4, 8
+    v = max_dpp<0x122>(v);
+    v = max_dpp<0x124>(v);
+    return max_dpp<0x128>(v);
+}
+
+// 2^k, k in [-126, 126]
+__device__ __forceinline__ float pow2(int k) { return __int_as_float((127 + min(max(k, -126), 126)) << 23); }
+// k with 2^k top in [2^to, 2^(to + 1)) (for zero more than any limit)
+__device__ __forceinline__ int exp_to(uint32_t top, int to) { return to + 127 - (int)(top >> 23); }
+__device__ __forceinline__ int clamp_exp(int k, int lim) { return min(max(k, -lim), lim); }
+
+// half (rounded up, at most 30) of the powers of two between a value and the largest (0 for zero)
+__device__ __forceinline__ int half_below(uint32_t v, uint32_t top)
+{
+    return v ? min(((int)(top >> 23) - (int)(v >> 23) + 1) >> 1, 30) : 0;
+}
+
+constexpr int kXExp = 14;     // of the encoding's sines and cosines and the constant 1
+// limits of the exponents of a gradient and of what it is multiplied with (their sums are powers of two)
+constexpr int kGradExp = 90, kActExp = 36;
+constexpr int kStepExp = 60;            // a step's gradient exponent above the smallest so far
+constexpr int kRaySpread = 36;          // largest ratio of its rays' upstream gradients, 2^this
+constexpr float kAdjSpread = 0x1p12f;   // largest ratio of W1's rows' largest entries, and of its columns'
 
 __device__ __forceinline__ uint32_t abs_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
@@ -505,53 +553,94 @@ __global__ __launch_bounds__(256) void k_ray_encode(RenderBufs b)
 }
 
 // Two wavefronts per SIMD: a wavefront holds its batch's columns (108 VGPRs)
-// and its sums (57) between its turns at the blocks.
+// and its sums (57) between its turns at the blocks.  (Sums of a step in
+// registers of their own, to be added at its end, spill: 2.96 ms a training step
+// of 8192 rays against 2.87.)
 __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_adjoint(
     GridK g, cic_mlp m, RenderBufs b, BackwardBufs bb)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     // Powers of two (exact; taken out again where gradients leave the kernel):
-    // s1 of W1, for its split, and s0 of W0's feature columns, likewise
+    // s1 of W1, and W0's feature columns', s0
     float *blocks = lds + kAOffBlocks;
-    float s1, s0, w2_top;
-    bool bad;   // a value left the range of the split
+    float s1, s0;   // (s0 of the feature that this thread stages)
+    int e_s1, e_w2;    // of s1, and of W2 / s1
+    bool bad;          // a value left the range of the split
     {
-        float v[4] = {0.f, 0.f, 0.f, 0.f};   // max|W1|, max|W0|, max|W2|, the weights' sum
-        if (threadIdx.x < 384) v[2] = v[3] = fabsf(m.w2[threadIdx.x]);
+        const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+        // max|W2|, |W1| (whole, row tid / 4, column tid % 128), W0's features wave / 2 + 4 k; the weights' sum
+        uint32_t w2 = 0, w1, row = 0, col = 0, f0[3], lo = 0x7f800000u;
+        float sum = 0.f;
+        if (tid < 384) sum = fabsf(m.w2[tid]);
+        w2 = wave_max_last(__float_as_uint(sum));
 #pragma unroll
         for (int i = 0; i < 128 * 128; i += kAdjWaves * 64) {
-            const float w = fabsf(m.w1[i + threadIdx.x]);
-            v[0] = fmaxf(v[0], w);
-            v[3] += w;
+            const float w = fabsf(m.w1[i + tid]);
+            col = max(col, __float_as_uint(w));
+            sum += w;
         }
 #pragma unroll
-        for (int i = 0; i < 128 * 12; i += kAdjWaves * 64) {
-            const int e = i + threadIdx.x;
-            const float w = fabsf(m.w0[(e / 12) * 39 + e % 12]);
-            v[1] = fmaxf(v[1], w);
-            v[3] += w;
+        for (int i = 0; i < 8; ++i) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) row = max(row, abs_bits(m.w1[4 * (8 * tid + i) + e]));
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 3; ++k) {
+            const float w = fabsf(m.w0[(tid & 127) * 39 + (tid >> 7) + 4 * k]);
+            f0[k] = wave_max_last(__float_as_uint(w));
+            sum += w;
+        }
+        row = max(row, (uint32_t)__shfl_xor((int)row, 1, kWave));
+        row = max(row, (uint32_t)__shfl_xor((int)row, 2, kWave));
+        uint32_t *cols = (uint32_t *)blocks + 256;
+        cols[tid] = col;
+        __syncthreads();
 #pragma unroll
-            for (int off = kWave / 2; off > 0; off >>= 1) {
-                const float u = __shfl_xor(v[k], off, kWave);
-                v[k] = k < 3 ? fmaxf(v[k], u) : v[k] + u;
-            }
-            if (lane_id() == 0) blocks[4 * (threadIdx.x / kWave) + k] = v[k];
+        for (int k = 0; k < 4; ++k) col = max(col, cols[(tid & 127) + 128 * k]);
+        w1 = wave_max_last(row);
+        if (row) lo = row;
+        if (col) lo = min(lo, col);
+        lo = ~wave_max_last(~lo);
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+        uint32_t *red = (uint32_t *)blocks;   // [wave][8]
+        if (lane == kWave - 1) {
+            red[8 * wave] = w1;
+            red[8 * wave + 1] = lo;
+            red[8 * wave + 2] = w2;
+            red[8 * wave + 3] = __float_as_uint(sum);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) red[8 * wave + 4 + k] = f0[k];
         }
         __syncthreads();
-        v[3] = 0.f;
+        sum = 0.f;
         for (int w = 0; w < kAdjWaves; ++w) {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) v[k] = fmaxf(v[k], blocks[4 * w + k]);
-            v[3] += blocks[4 * w + 3];
+            w1 = max(w1, red[8 * w]);
+            lo = min(lo, red[8 * w + 1]);
+            w2 = max(w2, red[8 * w + 2]);
+            sum += __uint_as_float(red[8 * w + 3]);
         }
-        s1 = pow2(exp_to(v[0], 4), 60);
-        s0 = pow2(exp_to(v[1], 4), 60);
-        w2_top = v[2] / s1;
+        w1 = __builtin_amdgcn_readlane(w1, kWave - 1);
+        w2 = __builtin_amdgcn_readlane(w2, kWave - 1);
+        lo = __builtin_amdgcn_readlane(lo, kWave - 1);
+        e_s1 = clamp_exp(exp_to(w1, 14), 60);
+        s1 = pow2(e_s1);
+        e_w2 = exp_to(w2, 6) + e_s1;
         // (the sum is not finite where a weight is not)
-        bad = __builtin_amdgcn_readfirstlane(!(v[3] < 0x1p50f && w2_top < 0x1p100f));
+        bad = __builtin_amdgcn_readfirstlane(!(sum < 0x1p50f) || e_w2 < -94 ||
+                                             __uint_as_float(w1) > kAdjSpread * __uint_as_float(lo));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) f0[k] = max(red[16 * (wave >> 1) + 4 + k], red[16 * (wave >> 1) + 12 + k]);
+        __syncthreads();
+        // W0's scale per feature: f % 4 is its wavefront pair, f / 4 its k
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int e0 = clamp_exp(exp_to(f0[k], 14), 60);
+            if ((tid & 127) == 0) lds[kAOffS0 + (tid >> 7) + 4 * k] = pow2(-e0);
+        }
+        if (tid < 4) lds[kAOffS0 + 12 + tid] = 1.f;
+        __syncthreads();
+        s0 = 1.f / lds[kAOffS0 + min(tid & 15, 11)];
     }
     stage_weights_f32(m, lds, s1);
     // W0^T's fragments: lane l, word e: feature l % 16 (rows 12 .. of the
@@ -564,9 +653,9 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
             float w[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u)
-                w[u] = m.w0[(32 * s + 16 * (e >> 1) + 4 * (l >> 4) + 2 * (e & 1) + u) * 39 + min(l & 15, 11)] * s0;
+                w[u] = m.w0[(32 * s + 16 * (e >> 1) + 4 * (l >> 4) + 2 * (e & 1) + u) * 39 + min(l & 15, 11)];
             uint32_t x, y;
-            split_pair(w[0], w[1], x, y);
+            split_pair(w[0], w[1], s0, x, y);
             hi[e] = x;
             lo[e] = y;
         }
@@ -575,7 +664,6 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
     }
     __syncthreads();   // (the row blocks' memory is free from here on)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    uint32_t *tops = (uint32_t *)(lds + kAOffTops);   // [wave][8]
 
     // this workgroup's batches: the XCD's contiguous range, interleaved over
     // its workgroups and wavefronts; every wavefront runs the same number of
@@ -586,18 +674,21 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
     const int64_t per = (nbatch + kXcds - 1) / kXcds;
     const int64_t lo = xcd * per, hi = lo + per < nbatch ? lo + per : nbatch;
     const int64_t first = lo + (int64_t)slot * kAdjWaves, stride = (int64_t)nslots * kAdjWaves;
-    const int64_t steps = hi > first ? (hi - first + stride - 1) / stride : 0;
+    const int64_t steps = !bad && hi > first ? (hi - first + stride - 1) / stride : 0;   // (bad: the weights)
 
     // this wavefront's share of the sums (see the turns)
     f16_t acc0, acc1[2];
     f4_t acc2[2];        // rows 0..2: P2, row 3: db1, of unit 64 u + lane
     float acc4 = 0.f;    // db2, channel q
-    // the scales of what the sums were made from, and the largest values so far
-    Scales sc{1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
-    uint32_t top[kTops] = {0, 0, 0, 0, 0};
+    uint32_t g_hi = 0, g_lo = 0x7f800000u;   // largest and smallest (but zero) upstream gradient of this lane's rays
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc0[r] = acc1[0][r] = acc1[1][r] = 0.f;
     acc2[0] = acc2[1] = f4_t{0.f, 0.f, 0.f, 0.f};
+
+    // exponents of the sums' scales (see the steps), eb and e0 with their smallest so far
+    int eb = kGradExp, e0 = kGradExp, eb_low = kGradExp, e0_low = kGradExp, e1 = kActExp, ed = kActExp;
+    int ef[3] = {kActExp, kActExp, kActExp};
+    int ec = kActExp;   // that of the inputs in this lane's column of P0
 
     for (int64_t st = 0; st < steps; ++st) {
         // (the lane's LDS addresses are formed anew in each step: kept over the
@@ -636,8 +727,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
                 x[7 + c] = e1[c];
             }
         }
-        // forward: layer 0 (40 -> 128), the same products in the same order
-        // as the forward kernel's full-input path
+        // forward: layer 0 (40 -> 128)
         f4_t h1[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) h1[t] = *(const f4_t *)(lds + AdjLds::kB0 + 16 * t + 4 * q);
@@ -715,81 +805,43 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
         {
             const float pp[3] = {p0, p1, p2};
             const float w = b.rec_w[rec];
+            uint32_t g = 0;
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
                 const float c = sigmoid_hw(pp[ch] + lds[AdjLds::kB2 + ch]);
-                const float dc = valid ? w * bb.d_rgb[3 * (int64_t)ray + ch] : 0.f;
+                const float gr = valid ? bb.d_rgb[3 * (int64_t)ray + ch] : 0.f;
+                g = max(g, abs_bits(gr));
+                const float dc = valid ? w * gr : 0.f;
                 dl[ch] = dc * c * (1.f - c);
                 acc4 += q == ch ? dl[ch] : 0.f;
                 if (valid && q == ch) b.rec_c[3 * (int64_t)rec + ch] = c;
             }
+            g_hi = max(g_hi, g);
+            g_lo = min(g_lo, g ? g : g_lo);
         }
-        // The workgroup's scales: powers of two that put the largest value so far
-        // of dlogit, h1, h2, the features and the direction near the top of
-        // float16's range; where one grows, the sums so far are scaled down.
+        // Exponents.  Of the sample: es, its dlogit's with W2's (its dp1 is at most
+        // 3 2^7 2^7).  Of this batch, for P2: ep of its largest dlogit, e2 of its
+        // second activations; sh2 is half of what the sample's dlogit is below.
+        uint32_t dl_top = 0, dl_batch;
+        int es, ep, e2, sh2;
         {
-            uint32_t v[kTops] = {0, 0, 0, 0, 0};
+            uint32_t v = 0;
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                v[0] = max(v[0], abs_bits(dl[ch]));
-                v[3] = max(v[3], abs_bits(x[ch]));
-            }
+            for (int ch = 0; ch < 3; ++ch) dl_top = max(dl_top, abs_bits(dl[ch]));
 #pragma unroll
             for (int t = 0; t < 8; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    v[1] = max(v[1], __float_as_uint(h1[t][r]));   // (not negative)
-                    v[2] = max(v[2], __float_as_uint(h2[t][r]));
-                }
-            v[4] = abs_bits(x[3]);
-#pragma unroll
-            for (int k = 0; k < kTops; ++k) {
-                const uint32_t w = wave_max_last(v[k]);
-                if (lane == kWave - 1) tops[wave * 8 + k] = w;
-            }
-            __syncthreads();
-            uint32_t w = tops[lane];
-#pragma unroll
-            for (int off = 8; off < 64; off <<= 1) w = max(w, (uint32_t)__shfl_xor((int)w, off, kWave));
-            bool grown = false;
-#pragma unroll
-            for (int k = 0; k < kTops; ++k) {
-                const uint32_t u = max(top[k], (uint32_t)__builtin_amdgcn_readlane(w, k));
-                grown |= (u >> 23) != (top[k] >> 23);
-                bad |= u >= 0x70000000u;   // 2^97, and what is not finite
-                top[k] = u;
-            }
-            if (grown) {
-                Scales n;
-                auto top_of = [&](int k) { return __uint_as_float(top[k]); };
-                // (3 max|W2 / s1| max|dl| < 3 2^7 2^7)
-                const int e_dl = exp_to(top_of(0), 6) + exp_to(w2_top, 6);
-                bad |= e_dl < -120;
-                n.dl = pow2(e_dl, 120);
-                n.p2 = pow2(exp_to(top_of(0), 14), 120);
-                n.h1 = pow2(exp_to(top_of(1), 14), 120);
-                n.h2 = pow2(exp_to(top_of(2), 14), 120);
-                n.f = pow2(exp_to(top_of(3), 14), 120);
-                n.d = pow2(exp_to(top_of(4), 14), 120);
-                // (a scale grows only from the 1 of a value that was zero so far, as the sums with it are)
-                auto step = [](float to, float from) { return fminf(to / from, 1.f); };
-                const float f0 = step(n.dl, sc.dl), f1 = f0 * step(n.h1, sc.h1);
-                const float f2 = step(n.p2, sc.p2) * step(n.h2, sc.h2);
-                const int c = slot_chunk(wave, lane);
-                const float f3 = f0 * (c < 3 ? step(n.f, sc.f) : c == 3 && slot_group(lane) < 3 ? step(n.d, sc.d) : 1.f);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    acc0[r] *= f3;
-                    acc1[0][r] *= f1;
-                    acc1[1][r] *= f1;
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    acc2[0][r] *= r < 3 ? f2 : f0;
-                    acc2[1][r] *= r < 3 ? f2 : f0;
-                }
-                sc = n;
-            }
+                for (int r = 0; r < 4; ++r) v = max(v, __float_as_uint(h2[t][r]));   // (not negative)
+            dl_batch = __builtin_amdgcn_readlane(wave_max_last(dl_top), kWave - 1);
+            es = clamp_exp(exp_to(dl_top, 6) + e_w2, 120);
+            sh2 = half_below(dl_top, dl_batch);
+            ep = exp_to(dl_batch, 14);
+            // (h2 is times s1 here; 2^-(ep + e2) takes both out)
+            e2 = exp_to(__builtin_amdgcn_readlane(wave_max_last(v), kWave - 1), 14) + e_s1;
+            // (what is not finite has the largest bits)
+            bad |= ep < -kGradExp || e2 < -kActExp;
+            ep = clamp_exp(ep, kGradExp);
+            e2 = clamp_exp(e2, kActExp);
         }
         h4_t identity, replicate;   // [k = 4 q + e][n = j]: k == n, k == n % 4
 #pragma unroll
@@ -802,9 +854,13 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
         // the rest zero, so four tiles share an accumulator) and the transposed h2
         u4_t dp1h[4], dp1l[4];   // dp1's parts, tiles 2 s and 2 s + 1 in word pairs
         {
-            const u4_t dt = split_transpose(f4_t{dl[0] * sc.p2, dl[1] * sc.p2, dl[2] * sc.p2, 0.f}, replicate);
+            const float p2 = pow2(ep + sh2);
+            const u4_t dt = split_transpose(f4_t{dl[0], dl[1], dl[2], 0.f}, p2, replicate);
+            const float scale = pow2(es), scale2 = pow2(e2 - e_s1 - sh2);
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) dl[ch] *= sc.dl;
+            for (int ch = 0; ch < 3; ++ch) dl[ch] *= scale;
+            f4_t sum[2];
+            sum[0] = sum[1] = f4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
                 const f4_t wa = w2l[(q * 3 + 0) * 8 + t], wb = w2l[(q * 3 + 1) * 8 + t], wc = w2l[(q * 3 + 2) * 8 + t];
@@ -817,26 +873,29 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     uint32_t hi, lo;
-                    split_pair(v[2 * e], v[2 * e + 1], hi, lo);
+                    split_pair(v[2 * e], v[2 * e + 1], 1.f, hi, lo);
                     dp1h[t >> 1][2 * (t & 1) + e] = hi;
                     dp1l[t >> 1][2 * (t & 1) + e] = lo;
                 }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = h2[t][r] * sc.h2;
-                const u4_t ht = split_transpose(v, identity);
+                const u4_t ht = split_transpose(h2[t], scale2, identity);
                 const bool mine = (j >> 2) == (t & 3);
                 const h4_t dh = as_h4(mine ? dt[0] : 0u, mine ? dt[1] : 0u);
                 const h4_t dlo = as_h4(mine ? dt[2] : 0u, mine ? dt[3] : 0u);
-                f4_t &a = acc2[t >> 2];
+                f4_t &a = sum[t >> 2];
                 a = __builtin_amdgcn_mfma_f32_16x16x16f16(dlo, as_h4(ht[0], ht[1]), a, 0, 0, 0);
                 a = __builtin_amdgcn_mfma_f32_16x16x16f16(dh, as_h4(ht[2], ht[3]), a, 0, 0, 0);
                 a = __builtin_amdgcn_mfma_f32_16x16x16f16(dh, as_h4(ht[0], ht[1]), a, 0, 0, 0);
                 if (t & 1) __builtin_amdgcn_sched_barrier(0);
             }
+            const float out = pow2(-(ep + e2));
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int r = 0; r < 3; ++r) acc2[u][r] = fmaf(sum[u][r], out, acc2[u][r]);
         }
         // dh1 = W1^T dp1 (A fragments of W1^T read from the forward's W1
         // layout and split here), dp0 = [h1 > 0] dh1
-        u4_t dp0h[4], dp0l[4];   // its parts, as dp1's
+        f4_t dp0[8];   // times 2^es
         {
             // lane l needs W1[16 c4 + 4 (l / 16) + rr][16 ti + l % 16]: float
             // l % 4 of lane 16 g + 4 (l / 16) + rr of block (c4, ti), g =
@@ -861,7 +920,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         uint32_t x, y;
-                        split_pair(a[2 * e], a[2 * e + 1], x, y);
+                        split_pair(a[2 * e], a[2 * e + 1], 1.f, x, y);
                         hi[e] = x;
                         lo[e] = y;
                     }
@@ -874,61 +933,157 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
                     for (int e = 0; e < 8; ++e) a[e] = an[e];
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                d += dlow;
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    uint32_t x, y;
-                    split_pair(h1[ti][2 * e] > 0.f ? d[2 * e] * kDP0Scale : 0.f,
-                               h1[ti][2 * e + 1] > 0.f ? d[2 * e + 1] * kDP0Scale : 0.f, x, y);
-                    dp0h[ti >> 1][2 * (ti & 1) + e] = x;
-                    dp0l[ti >> 1][2 * (ti & 1) + e] = y;
-                }
+                for (int r = 0; r < 4; ++r)
+                    dp0[ti][r] = h1[ti][r] > 0.f ? d[r] + dlow[r] : 0.f;
             }
         }
-        // feature gradient (W0^T dp0)[0:12] of the sample (ray order)
+        // feature gradient (W0^T dp0)[0:12] of the sample (ray order); dp0 scaled by
+        // the sample's largest, 2^e0s
+        uint32_t dp0_top;   // the sample's largest dp0 (without 2^es)
         {
+            uint32_t v = 0;
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v = max(v, abs_bits(dp0[t][r]));
+            v = across_rows_max(v);
+            dp0_top = __float_as_uint(__uint_as_float(v) * pow2(-es));
+            const int e0s = clamp_exp(exp_to(v, 14), 120);
+            const float scale = pow2(e0s);
             f4_t df = f4_t{0.f, 0.f, 0.f, 0.f}, low = df;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
+                u4_t hi, lo;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const f4_t &d = dp0[2 * s + (e >> 1)];
+                    uint32_t x, y;
+                    split_pair(d[2 * (e & 1)], d[2 * (e & 1) + 1], scale, x, y);
+                    hi[e] = x;
+                    lo[e] = y;
+                }
                 const h8_t wh = w0t[s * 64], wl = w0t[(4 + s) * 64];
-                const h8_t ph = __builtin_bit_cast(h8_t, dp0h[s]), pl = __builtin_bit_cast(h8_t, dp0l[s]);
+                const h8_t ph = __builtin_bit_cast(h8_t, hi), pl = __builtin_bit_cast(h8_t, lo);
                 low = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl, ph, low, 0, 0, 0);
                 low = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, pl, low, 0, 0, 0);
                 df = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, ph, df, 0, 0, 0);
             }
+            const f4_t unscale = *(const f4_t *)(lds + kAOffS0 + 4 * q);
+            const float fs = pow2(-es), f0 = pow2(-e0s);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) df[r] = (df[r] + low[r]) * (1.f / sc.dl) * (1.f / (kDP0Scale * s0));
+            for (int r = 0; r < 4; ++r) df[r] = (df[r] + low[r]) * unscale[r] * f0 * fs;
             if (valid && q < 3) *(f4_t *)(bb.rec_df + (int64_t)rec * 12 + 4 * q) = df;
         }
-        // weight gradients.  This batch's columns: split and transposed
+        // Weight gradients.  Exponents of the step's 128 samples by their largest
+        // values, eb of dp1 (the dlogit's with W2's) and e0 of dp0, and of all samples
+        // so far, e1 of h1, ed of the direction and ef of this lane's features; sh
+        // and sh0: half of what the sample's dlogit and dp0 are below the largest.
+        // The sums are brought to the step's scale.
+        int sh, sh0;
+        {
+            uint32_t *tops = (uint32_t *)(lds + kAOffTops);
+            uint32_t v = 0;
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v = max(v, __float_as_uint(h1[t][r]));
+            const u4_t tw = {dl_batch, wave_max_last(v), wave_max_last(dp0_top), wave_max_last(abs_bits(x[3]))};
+            if (lane == kWave - 1) *(u4_t *)(tops + 16 * wave) = tw;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const uint32_t f = row_max(abs_bits(x[k]));
+                if (j == 0) tops[16 * wave + 4 + 3 * q + k] = f;
+            }
+            __syncthreads();
+            uint32_t w = 0;   // the lane % 16-th value's largest
+#pragma unroll
+            for (int k = 0; k < kAdjWaves; ++k) w = max(w, tops[16 * k + j]);
+            // this lane's column of P0 and its three features (a lane without a feature's column takes the direction's)
+            const int c = slot_chunk(wave, lane), gr = slot_group(lane);
+            const uint32_t wc = (uint32_t)__shfl((int)w, c < 3 ? 4 + 3 * gr + c : 3, kWave);
+            uint32_t wf[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) wf[k] = (uint32_t)__shfl((int)w, 4 + 3 * q + k, kWave);
+            const uint32_t dl_all = __builtin_amdgcn_readlane(w, 0), dp0_all = __builtin_amdgcn_readlane(w, 2);
+            sh = half_below(dl_top, dl_all);
+            sh0 = half_below(dp0_top, dp0_all);
+            const int was1 = eb + e1, was0 = e0 + ec;
+            eb = exp_to(dl_all, 6) + e_w2 - e_s1;   // (without W1's s1)
+            e0 = exp_to(dp0_all, 14);
+            e1 = min(e1, exp_to(__builtin_amdgcn_readlane(w, 1), 14));
+            ed = min(ed, exp_to(__builtin_amdgcn_readlane(w, 3), 14));
+            bad |= min(eb, e0) < -kGradExp || min(e1, ed) < -kActExp;
+            eb = max(min(eb, kGradExp), -kGradExp);
+            e0 = max(min(e0, kGradExp), -kGradExp);
+            eb_low = min(eb_low, eb);
+            e0_low = min(e0_low, e0);
+            eb = min(eb, eb_low + kStepExp);
+            e0 = min(e0, e0_low + kStepExp);
+            e1 = max(e1, -kActExp);
+            ed = max(ed, -kActExp);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                ef[k] = min(ef[k], exp_to(wf[k], 14));
+                bad |= ef[k] < -kActExp;
+                ef[k] = max(ef[k], -kActExp);
+            }
+            ec = c < 3 || (c == 3 && gr < 3) ? max(min(ec, exp_to(wc, 14)), -kActExp) : kXExp;
+            const float f1 = pow2(eb + e1 - was1), f0 = pow2(e0 + ec - was0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc1[0][r] *= f1;
+                acc1[1][r] *= f1;
+                acc0[r] *= f0;
+            }
+        }
+        // this batch's columns: split and transposed
         u4_t cols[kTiles];
+        {
+            const float c1 = pow2(min(max(eb + e_s1 - es + sh, -24), 0)), c0 = pow2(e0 - es + sh0), ch = pow2(e1 - sh);
+            const float cd = pow2(ed - sh0), cx = pow2(kXExp - sh0);
+            const h2_t one2 = {(_Float16)pow2(kXExp - sh), (_Float16)0.f};
+            const u2_t ones = transpose16(u2_t{0u, __builtin_bit_cast(uint32_t, one2) << 16}, replicate);
+            f4_t sum[2];   // db1
+            sum[0] = sum[1] = f4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < kTiles; ++t) {
-            if (t < kTH1 || (t >= kTDP0 && t < kTX)) {
-                const int u = t & 7;
-                const u4_t hi = t < kTH1 ? dp1h[u >> 1] : dp0h[u >> 1], lo = t < kTH1 ? dp1l[u >> 1] : dp0l[u >> 1];
-                const u2_t a = transpose16(u2_t{hi[2 * (u & 1)], hi[2 * (u & 1) + 1]}, identity);
-                const u2_t c = transpose16(u2_t{lo[2 * (u & 1)], lo[2 * (u & 1) + 1]}, identity);
-                cols[t] = u4_t{a[0], a[1], c[0], c[1]};
-            } else {
-                f4_t v;
+            for (int t = 0; t < kTiles; ++t) {
+                if (t < kTH1) {
+                    // (in float16: what that cuts off is no more than what a remainder does)
+                    u2_t hi, lo;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int c = t < kTDP0 ? 0 : 4 * (t - kTX) + r;
-                    if (t < kTDP0) v[r] = h1[t - kTH1][r] * sc.h1;
-                    else if (c < 3) v[r] = x[c] * sc.f;
-                    else if (c == 3) v[r] = q < 3 ? x[3] * sc.d : kXScale;   // (1 in the padding slot)
-                    else v[r] = c < 10 ? x[c] * kXScale : 0.f;
+                    for (int e = 0; e < 2; ++e) {
+                        hi[e] = scale_h2(dp1h[t >> 1][2 * (t & 1) + e], c1);
+                        lo[e] = scale_h2(dp1l[t >> 1][2 * (t & 1) + e], c1);
+                    }
+                    hi = transpose16(hi, identity);
+                    lo = transpose16(lo, identity);
+                    cols[t] = u4_t{hi[0], hi[1], lo[0], lo[1]};
+                    const bool mine = j == 4 * (t & 3) + 3;   // (the fourth row of four)
+                    const h4_t one = as_h4(mine ? ones[0] : 0u, mine ? ones[1] : 0u);
+                    f4_t &a = sum[t >> 2];
+                    a = __builtin_amdgcn_mfma_f32_16x16x16f16(one, as_h4(lo[0], lo[1]), a, 0, 0, 0);
+                    a = __builtin_amdgcn_mfma_f32_16x16x16f16(one, as_h4(hi[0], hi[1]), a, 0, 0, 0);
+                } else if (t < kTDP0) {
+                    cols[t] = split_transpose(h1[t - kTH1], ch, identity);
+                } else if (t < kTX) {
+                    cols[t] = split_transpose(dp0[t - kTDP0], c0, identity);
+                } else {
+                    f4_t v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int c = 4 * (t - kTX) + r;
+                        if (c < 3) v[r] = x[c] * pow2(ef[c] - sh0);
+                        else if (c == 3) v[r] = q < 3 ? x[3] * cd : cx;   // (1 in the padding slot)
+                        else v[r] = c < 10 ? x[c] * cx : 0.f;
+                    }
+                    cols[t] = split_transpose(v, 1.f, identity);
                 }
-                cols[t] = split_transpose(v, identity);
+                if ((t & 3) == 3) __builtin_amdgcn_sched_barrier(0);
             }
-            if (t < kTH1) {   // db1
-                const uint32_t one = j == 4 * (t & 3) + 3 ? 0x3c003c00u : 0u;
-                f4_t &a = acc2[t >> 2];
-                a = __builtin_amdgcn_mfma_f32_16x16x16f16(as_h4(one, one), as_h4(cols[t][2], cols[t][3]), a, 0, 0, 0);
-                a = __builtin_amdgcn_mfma_f32_16x16x16f16(as_h4(one, one), as_h4(cols[t][0], cols[t][1]), a, 0, 0, 0);
-            }
-            if ((t & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            const float out = pow2(-(eb + kXExp));
+#pragma unroll
+            for (int u = 0; u < 2; ++u) acc2[u][3] = fmaf(sum[u][3], out, acc2[u][3]);
         }
         auto write_block = [&](float *blk) {
 #pragma unroll
@@ -969,15 +1124,15 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
     // the workgroup's partial
     const int lane = lane_id(), q = lane >> 4, j = lane & 15;
     float *out = bb.partials + (int64_t)blockIdx.x * kPartialFloats;
+    const float out1 = pow2(-(eb + e1)), out0 = pow2(-(e0 + ec));
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int row = 32 * (wave >> 1) + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), col = lane & 31;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
-            out[kPart1 + row * 128 + 64 * (wave & 1) + 32 * u + col] = acc1[u][r] * (1.f / sc.dl) * (1.f / sc.h1) * s1;
+            out[kPart1 + row * 128 + 64 * (wave & 1) + 32 * u + col] = acc1[u][r] * out1;
         const int c = slot_chunk(wave, lane), g = slot_group(lane), src = c < 10 ? l0_input(c, g) : 0;
-        const float sx = c < 3 ? sc.f : c == 3 && g < 3 ? sc.d : kXScale;
-        if (c < 10) out[row * 48 + (src >= 0 ? src : 39)] = acc0[r] * (1.f / sc.dl) * (1.f / sx) * (1.f / kDP0Scale);
+        if (c < 10) out[row * 48 + (src >= 0 ? src : 39)] = acc0[r] * out0;
     }
     // the others added up over the wavefronts in order
 #pragma unroll
@@ -993,9 +1148,23 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
         float v = 0.f;
 #pragma unroll
         for (int k = 0; k < kAdjWaves; ++k) v += blocks[k * 516 + i];
-        if (i < 384) v = v * (1.f / sc.p2) * (1.f / sc.h2) * (1.f / s1);
-        else if (i < 512) v = v * (1.f / sc.dl) * s1;
         out[kPart2 + i] = v;
+    }
+    // rays whose gradients are so far apart that the halves of it that each factor carries cost bits
+    {
+        const uint32_t hi = __builtin_amdgcn_readlane(wave_max_last(g_hi), kWave - 1);
+        const uint32_t lo = ~(uint32_t)__builtin_amdgcn_readlane(wave_max_last(~g_lo), kWave - 1);
+        if (lane == 0) {
+            ((uint32_t *)lds)[kAOffTops + wave] = hi;
+            ((uint32_t *)lds)[kAOffTops + kAdjWaves + wave] = lo;
+        }
+        __syncthreads();
+        uint32_t h = 0, l = 0x7f800000u;
+        for (int k = 0; k < kAdjWaves; ++k) {
+            h = max(h, ((uint32_t *)lds)[kAOffTops + k]);
+            l = min(l, ((uint32_t *)lds)[kAOffTops + kAdjWaves + k]);
+        }
+        bad |= (int)(h >> 23) - (int)(l >> 23) > kRaySpread;
     }
     const int redo = __syncthreads_or(bad);
     if (threadIdx.x == 0) out[kRedoFlag] = redo ? 1.f : 0.f;
@@ -1097,8 +1266,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
         const uint32_t rec = valid ? (uint32_t)s : 0u;
         float x[10];
         sample_inputs(g, b, rec, q, x);
-        // forward: layer 0 (40 -> 128), the same products in the same order
-        // as the forward kernel's full-input path
+        // forward: layer 0 (40 -> 128)
         f4_t h1[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) h1[t] = *(const f4_t *)(lds + AdjLds::kB0 + 16 * t + 4 * q);

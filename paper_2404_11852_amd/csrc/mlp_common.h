@@ -279,7 +279,8 @@ __device__ __forceinline__ uint32_t pack_bf2(float a, float b)
 
 template <int CTRL> __device__ __forceinline__ uint32_t max_dpp(uint32_t v)
 {
-    return max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false));
+    // (a lane without a source takes 0: one instruction)
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true));
 }
 
 // the wavefront's largest value, in its last lane
