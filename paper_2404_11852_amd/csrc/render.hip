@@ -210,9 +210,9 @@ __global__ __launch_bounds__(256) void k_march(GridK g, OptsK op, RenderBufs b)
 // registers (prefix16, and the row constants below); the chunk's depth sum is
 // the same tree.  Live samples are collected in LDS per lane and row, then
 // written 16 per ray at a time.  Bound by its vector instructions (89% of its
-// cycles, half of them the lookups' positions).  800x800 frame 582 -> 335 us,
-// 1000x900 926 -> 464-512, 512x512 277 -> 205, 450x450 226 -> 191; at 400x400 as
-// fast as k_march, below that too few wavefronts.  Caller's rays stay with
+// cycles, half of them the lookups' positions).  800x800 frame of a 160^3 grid
+// with empty space 582 -> 335 us, 1000x900 926 -> 464-512; smaller frames see
+// kMarchTileMin.  Caller's rays stay with
 // k_march: 64 consecutive rays of one image row are faster here (640,000: 564
 // -> 442 us), but rays that are not neighbours up to 1.8 times slower.
 constexpr int kTileRow = 16;
@@ -392,13 +392,19 @@ __global__ __launch_bounds__(256) void k_march_tile(GridK g, OptsK op, RenderBuf
     }
 }
 
-constexpr int64_t kMarchTileMin = 196608;   // fewest pixels that march in tiles
+// Fewest pixels that march in tiles: below, too few wavefronts are left, and the
+// longest decide.  Less so without an occupancy grid, where the rays' lengths are
+// alike.  us in tiles and one wavefront per ray (96^3 and 160^3 grids): 450x450
+// 223 / 187 and 242 / 241, without occupancy 173 / 167 and 193 / 232; 512x512 291
+// / 252 and 306 / 296, without 186 / 210 and 208 / 286; 640x480 302 / 305 and 319
+// / 352, without 209 / 252 and 232 / 348.
+constexpr int64_t kMarchTileMinOcc = 300000, kMarchTileMin = 250000;
 
 template <typename T>
 void launch_march(const GridK &g, const OptsK &o, const RenderBufs &b, int width, hipStream_t s)
 {
     if (b.n == 0) return;
-    if (width > 0 && b.n >= kMarchTileMin) {
+    if (width > 0 && b.n >= (g.occ ? kMarchTileMinOcc : kMarchTileMin)) {
         const int rows = (int)(b.n / width), tiles = ((width + 7) / 8) * ((rows + 7) / 8);
         hipLaunchKernelGGL(k_march_tile<T>, dim3((unsigned)((tiles + kRayWaves - 1) / kRayWaves)), dim3(256), 0, s, g,
                            o, b, width, rows);
