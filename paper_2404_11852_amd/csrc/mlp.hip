@@ -343,20 +343,22 @@ void launch_ray_embed(const cic_mlp &m, const RenderBufs &b, hipStream_t s)
 // float32 MFMA for the samples that leave the range of the split, or for all of
 // them where the weights do: 16 samples per step of a wavefront, 16x16x4 products as in the
 // adjoint's recomputed forward, the weights staged anew over the split's.
-// Bound by the float32 products: a call of 1.6 M samples takes 0.37 ms, 0.94 when
+// Bound by the float32 products: a call of 1.6 M samples takes 0.37 ms, 0.87 when
 // all of them come here (13.0 with a wavefront per sample on the vector ALUs,
 // which read W1 from memory for each).
-template <typename T, bool HASH>
+// ahead(k): the loads of the next step's samples, in three rounds, each of which
+// uses the one before (an 800x800 frame whose every sample comes here: 11.87 ms
+// without, 11.37 so; 10.88 with four wavefronts per SIMD, which the split's
+// registers do not leave).
+template <typename T, bool HASH, typename Ahead>
 __device__ __forceinline__ void colours_f32(const GridK &g, const RenderBufs &b, const float *lds, uint32_t rec,
-                                            bool write)
+                                            const SampleRay &r, bool write, const Ahead &ahead)
 {
     typedef F32Lds L;
     const int lane = lane_id(), q = lane >> 4;
     const f2_t *w0f = (const f2_t *)(lds + L::kW0);
     const f4_t *w2l = (const f4_t *)(lds + L::kW2);
     const float *w1f = lds + L::w1(0, lane);   // (block k at + k * kW1Block floats)
-    SampleRay r;
-    load_sample_ray(b, b.rec_ray[rec], b.rec_k[rec], r);
     float x[3];
     {
         Gather<T, HASH> gt;
@@ -380,8 +382,11 @@ __device__ __forceinline__ void colours_f32(const GridK &g, const RenderBufs &b,
 #pragma unroll
         for (int t = 0; t < 8; ++t)
             h1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w0f[(t * 5 + (c >> 1)) * 64 + lane][c & 1], x[c], h1[t], 0, 0, 0);
+    // (the wavefront that is further through its step wins the matrix unit)
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int c4 = 0; c4 < 8; ++c4) {
+        if (c4 % 2 == 0 && c4 < 6) ahead(c4 / 2);
 #pragma unroll
         for (int tg = 0; tg < 2; ++tg) {
             f4_t a[4];
@@ -394,8 +399,10 @@ __device__ __forceinline__ void colours_f32(const GridK &g, const RenderBufs &b,
                 for (int tt = 0; tt < 4; ++tt)
                     h2[4 * tg + tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[tt][rr], h, h2[4 * tg + tt], 0, 0, 0);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
+    __builtin_amdgcn_s_setprio(0);
     float p[3] = {0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 8; ++t)
@@ -649,14 +656,43 @@ k_mlp_fwd_f32(GridK g, cic_mlp m, RenderBufs b, int voxel)
     // (every wavefront is past the barrier, so the split's weights are done with)
     stage_weights_f32(m, lds, 1.f);
     __syncthreads();
-    for (uint32_t k = wave;; k += kFwdWaves) {
-        const uint32_t rbt = batch_of(k);
-        if (rbt >= bcount) break;
-        for (uint32_t s0 = (bfirst + rbt) * kFwdBatch, end = s0 + kFwdBatch; s0 < end && s0 < total; s0 += 16) {
-            const uint32_t s = min(s0 + (lane & 15), total - 1), rec = voxel ? b.perm[s] : s;
-            const bool marked = plain || __float_as_uint(b.rec_c[3 * (int64_t)rec]) == kRedo;
-            if (__builtin_amdgcn_ballot_w64(marked)) colours_f32<T, HASH>(g, b, lds, rec, marked);
+    // step u of this wavefront: half of its batch u / 2; its first sample, or total past the last
+    auto step_start = [&](uint32_t u) -> uint32_t {
+        const uint32_t rbt = batch_of(wave + (u >> 1) * kFwdWaves);
+        return rbt < bcount ? min((bfirst + rbt) * kFwdBatch + 16 * (u & 1), total) : total;
+    };
+    auto step_record = [&](uint32_t s0) -> uint32_t {
+        const uint32_t s = min(s0 + (lane & 15), total - 1);
+        return voxel ? b.perm[s] : s;
+    };
+    uint32_t s0 = step_start(0), u = 0;
+    if (s0 >= total) return;
+    uint32_t rec = step_record(s0);
+    SampleRay cur;
+    load_sample_ray(b, b.rec_ray[rec], b.rec_k[rec], cur);
+    while (s0 < total) {   // (the starts grow)
+        const uint32_t n0 = step_start(++u);
+        uint32_t nrec = 0, nray = 0;
+        int nk = 0;
+        SampleRay next;
+        auto ahead = [&](int k) {
+            if (k == 0) nrec = step_record(n0);
+            if (k == 1) {
+                nray = b.rec_ray[nrec];
+                nk = b.rec_k[nrec];
+            }
+            if (k == 2) load_sample_ray(b, nray, nk, next);
+        };
+        const bool marked = plain || __float_as_uint(b.rec_c[3 * (int64_t)rec]) == kRedo;
+        if (__builtin_amdgcn_ballot_w64(marked)) {
+            colours_f32<T, HASH>(g, b, lds, rec, cur, marked, ahead);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ahead(k);
         }
+        s0 = n0;
+        rec = nrec;
+        cur = next;
     }
 }
 
