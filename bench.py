@@ -28,7 +28,8 @@ sys.path.insert(0, ROOT)
 METRIC = "ray samples/s + 800x800 FPS (full vs SpaRW); fwd+bwd samples/s; BF16 vs FP32"
 MLP_FLOP_PER_SAMPLE = 2 * (12 * 128 + 128 * 128 + 128 * 3)   # 36,608 useful FLOP
 PEAK_FP32_TFLOPS = 157.3
-# float32 products as three float16 ones (split operands): a third of the dense float16 rate
+# float32 products as three float16 ones (split operands; layer 0's 12 features, 8% of the
+# work, as six BF16 ones): a third of the dense 16-bit rate
 PEAK_SPLIT_TFLOPS = 2500.0 / 3
 PEAK_HBM_GBS = 8000.0
 # Training step, per evaluated sample, the method's own work on MFMA:
@@ -826,7 +827,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": "800x800 full-frame render, 160^3 dense grid (raw density + 12 features, FP32), "
                                "up to 256 samples/ray, occupancy skip, termination at T<1e-4, "
-                               "39-128-128-3 MLP (float32 products as split float16 on MFMA)",
+                               "39-128-128-3 MLP (float32 products as split 16-bit ones on MFMA)",
                    "width": W, "height": H, "grid_res": 160, "n_samples": 256, "order": args.order},
         "fps_full_800x800": 1e3 / ms_step,
         "evaluated_samples_per_frame": samples_per_frame,

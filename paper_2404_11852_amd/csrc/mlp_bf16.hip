@@ -65,11 +65,12 @@ constexpr int kTileThreads = kBfWaves * 64;   // threads of a workgroup there
 constexpr int kFTileV = kBrick + 1;
 // Brick tile: channel ch of vertex (lx, ly, lz) at
 // ch * kFTileS + lx * kFTileSX + ly * kFTileSY + lz * kFTileSZ.  One gather
-// instruction reads channel 3q + c of the 16 samples' corner for the four
-// lane groups q; the samples of a batch lie along one or two rays through
-// the brick, so their cells are near neighbours.  The strides are chosen for
-// few LDS bank collisions among those 64 words (64 banks): the channel
-// stride puts the lane groups 16 banks apart, so two cells collide when
+// instruction reads one channel of the 32 samples' corner for either lane half,
+// six channels apart; the samples of a batch lie along one or two rays through
+// the brick, so their cells are near neighbours.  The strides were chosen for
+// few LDS bank collisions (64 banks) of a gather by 16 samples and four lane
+// groups, three channels apart, and not measured again for this one: there the
+// channel stride puts the lane groups 16 banks apart, so two cells collide when
 // their offsets differ by a multiple of 16 words.  Among cell steps of at
 // most 2 per axis, 10 do so with the dense x stride of 81 (+-(1, 0, -1) among
 // them: 80 words) and 6 with the x stride of 102 (+-(1, 1, 1): 112 words,
@@ -641,7 +642,8 @@ __device__ __forceinline__ void bf_inputs(const float x[6], const u4_t e0, const
 // M live samples: 2.36 -> 1.77 ms (the matrix power limit of the 46,000
 // operations per sample that the padded tiles execute is 1.43 ms), multi-level
 // encoding 2.45 -> 2.16 ms.  The brick kernel with the same 32-row tiles: 5.04
-// -> 4.90 ms per 2^21 rays of eight views, its own power limit being 4.7 ms.
+// -> 4.90 ms per pass of 95 M samples of eight views, 51 ps per sample against 49
+// here and 39 at that limit: it is held by its staging between barriers.
 template <typename T, bool HASH>
 __global__ __launch_bounds__(kRayWaves8 * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 k_mlp_fwd_bf16_gather(GridK g, cic_mlp m, RenderBufs b, int voxel)
