@@ -385,7 +385,8 @@ void launch_feature_grads_bricks(const GridK &g, const RenderBufs &b, const Back
 // k_mlp_adjoint_f32 does a workgroup's share again where the scales do not hold
 // a value (dlogit or dp0 from about 2^100, inputs and activations from 2^51,
 // infinities, NaN), where its rays' upstream gradients are more than 2^36
-// apart, or W1's rows or columns more than 2^12 in their largest entries.
+// apart, or W1's rows and columns more than 2^17, multiplied, in their largest
+// entries (at 2^20 feature gradients are off by 3e-7 in place of 2e-7).
 // Gradient error against 64 bits, rms over seeds, float32 products -> these:
 // 3000 rays of 96 samples dW0 8.3e-7 -> 5.1e-7, dW1 7.3e-7 -> 4.3e-7, dW2 9.5e-7
 // -> 1.8e-7, features 6.1e-7 both (the float32 sums over all samples were rounded
@@ -524,7 +525,7 @@ constexpr int kXExp = 14;     // of the encoding's sines and cosines and the con
 constexpr int kGradExp = 90, kActExp = 36;
 constexpr int kStepExp = 60;            // a step's gradient exponent above the smallest so far
 constexpr int kRaySpread = 36;          // largest ratio of its rays' upstream gradients, 2^this
-constexpr float kAdjSpread = 0x1p12f;   // largest ratio of W1's rows' largest entries, and of its columns'
+constexpr float kAdjSpread = 0x1p17f;   // largest product of the ratios of W1's rows' and of its columns' largest entries
 
 __device__ __forceinline__ uint32_t abs_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
     {
         const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
         // max|W2|, |W1| (whole, row tid / 4, column tid % 128), W0's features wave / 2 + 4 k; the weights' sum
-        uint32_t w2 = 0, w1, row = 0, col = 0, f0[3], lo = 0x7f800000u;
+        uint32_t w2 = 0, w1, row = 0, col = 0, f0[3], lo, rows_lo;
         float sum = 0.f;
         if (tid < 384) sum = fabsf(m.w2[tid]);
         w2 = wave_max_last(__float_as_uint(sum));
@@ -598,9 +599,8 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int k = 0; k < 4; ++k) col = max(col, cols[(tid & 127) + 128 * k]);
         w1 = wave_max_last(row);
-        if (row) lo = row;
-        if (col) lo = min(lo, col);
-        lo = ~wave_max_last(~lo);
+        lo = ~wave_max_last(~(col ? col : 0x7f800000u));
+        rows_lo = ~wave_max_last(~(row ? row : 0x7f800000u));
 #pragma unroll
         for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
         uint32_t *red = (uint32_t *)blocks;   // [wave][8]
@@ -611,24 +611,29 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
             red[8 * wave + 3] = __float_as_uint(sum);
 #pragma unroll
             for (int k = 0; k < 3; ++k) red[8 * wave + 4 + k] = f0[k];
+            red[8 * wave + 7] = rows_lo;
         }
         __syncthreads();
         sum = 0.f;
         for (int w = 0; w < kAdjWaves; ++w) {
             w1 = max(w1, red[8 * w]);
             lo = min(lo, red[8 * w + 1]);
+            rows_lo = min(rows_lo, red[8 * w + 7]);
             w2 = max(w2, red[8 * w + 2]);
             sum += __uint_as_float(red[8 * w + 3]);
         }
         w1 = __builtin_amdgcn_readlane(w1, kWave - 1);
         w2 = __builtin_amdgcn_readlane(w2, kWave - 1);
         lo = __builtin_amdgcn_readlane(lo, kWave - 1);
+        rows_lo = __builtin_amdgcn_readlane(rows_lo, kWave - 1);
         e_s1 = clamp_exp(exp_to(w1, 14), 60);
         s1 = pow2(e_s1);
         e_w2 = exp_to(w2, 6) + e_s1;
         // (the sum is not finite where a weight is not)
         bad = __builtin_amdgcn_readfirstlane(!(sum < 0x1p50f) || e_w2 < -94 ||
-                                             __uint_as_float(w1) > kAdjSpread * __uint_as_float(lo));
+                                             (w1 && !(__uint_as_float(w1) / __uint_as_float(lo) *
+                                                          (__uint_as_float(w1) / __uint_as_float(rows_lo)) <=
+                                                      kAdjSpread)));
 #pragma unroll
         for (int k = 0; k < 3; ++k) f0[k] = max(red[16 * (wave >> 1) + 4 + k], red[16 * (wave >> 1) + 12 + k]);
         __syncthreads();

@@ -16,10 +16,10 @@
 // accumulators, so the high ones are rounded 8 times over a 128-long sum where
 // a float32 chain rounds 128 times.  The output layer is float32.
 //
-// Float32 products instead, for whole calls: where W1's rows or columns (its
-// hidden units) differ by more than 2^20 in their largest entries, so that
-// units of small activations may decide a sum; where a weight is not finite or
-// beyond 2^60.  And for single samples: features and weights whose products are
+// Float32 products instead, for whole calls: where W1's rows and its columns (the
+// hidden units on either side) differ by more than 2^26, multiplied, in their
+// largest entries, so that small entries may decide a sum; where a weight is not
+// finite or beyond 2^60.  And for single samples: features and weights whose products are
 // beyond 2^100, an output that is not finite.
 //
 // Colour error against 64 bits, rms over 300,000 single-sample rays: 2.82e-8,
@@ -107,7 +107,7 @@ __host__ __device__ constexpr int l0_wpart(int p) { return p == 0 ? 2 : p == 2 |
 __host__ __device__ constexpr int l0_xpart(int p) { return p == 1 ? 2 : p == 2 || p == 4 ? 1 : 0; }
 
 constexpr float kWMax = 0x1p60f;    // largest weight of the split path, and W1's largest at least 2^-60
-constexpr float kSpread = 0x1p20f;  // largest ratio of its units' largest entries
+constexpr float kSpread = 0x1p26f;  // largest product of the ratios of its rows' and of its columns' largest entries
 
 // Weights into LDS in fragment order.  W1 is scaled by the power of two 2^e1
 // that puts its largest entry in [2^14, 2^15) before the split (so both parts
@@ -179,7 +179,7 @@ __device__ int stage_weights_split(const cic_mlp &m, float *lds)
     for (int k = 0; k < 3; ++k) f0[k] = wave_max_last(__float_as_uint(fabsf(v0[k])));
     // largest of the weights that only have to be within kWMax
     uint32_t any = wave_max_last(max(__float_as_uint(fabsf(v2)), __float_as_uint(fabsf(vb1))));
-    uint32_t hi = 0, lo = 0x7f800000u;   // largest and smallest (but zero) of the columns, later of the rows too
+    uint32_t hi = 0, lo = 0x7f800000u;   // largest and smallest (but zero) of the columns, hi later of the rows too
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         // (lanes 31 and 63 end with the maxima of their 32 lanes, the others with some of them)
@@ -209,7 +209,8 @@ __device__ int stage_weights_split(const cic_mlp &m, float *lds)
             for (int h = 0; h < 2; ++h)
                 row = max(row, ((const uint32_t *)w1)[(c * kIt + (tid >> 5)) * 64 + 32 * h + (tid & 31)]);
         hi = max(hi, row);
-        if (row) lo = min(lo, row);
+        const uint32_t rows_lo = ~wave_max_last(~(row ? row : 0x7f800000u));
+        if (lane == 63) red[64 + wave] = rows_lo;
     }
     hi = wave_max_last(hi);
     lo = ~wave_max_last(~lo);
@@ -234,8 +235,10 @@ __device__ int stage_weights_split(const cic_mlp &m, float *lds)
     const uint32_t feat = (tid & 7) < 6 ? max(red[(f & 3) * 16 + 4 + (f >> 2)], red[(f & 3) * 16 + 12 + (f >> 2)])
                                         : (tid & 7) == 6 ? dir : rest;
     __syncthreads();
+    const uint32_t rows_lo = min(red[64], red[65]);
     const float top = __uint_as_float(hi), all = __uint_as_float(max(max(hi, any), max(dir, rest)));
-    if (!(all <= kWMax) || (hi && (top < 1.f / kWMax || top > kSpread * __uint_as_float(lo)))) return kPlain;
+    const float spread = top / __uint_as_float(lo) * (top / __uint_as_float(rows_lo));
+    if (!(all <= kWMax) || (hi && !(top >= 1.f / kWMax && spread <= kSpread))) return kPlain;
     const int e1 = hi ? 14 + 127 - (int)(hi >> 23) : 0;
     const float s1 = ldexpf(1.f, e1);
     // layer 0's slot of feature ff of half h in product p: 6 p + ff, 8 of them per step

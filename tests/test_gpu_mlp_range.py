@@ -81,3 +81,21 @@ def test_magnitudes(what, k):
     got = _error(*_scaled(what, k))
     print("max error %.2e, as it was %.2e" % (got, plain))
     assert got <= 2 * plain + 2 * ULP
+
+
+@pytest.mark.parametrize("k", [3, 7, 9, 14])
+def test_units_of_both_layers(k):
+    """Every unit of both hidden layers, and every feature, times its own power of two."""
+    helpers.print_case("float32 MLP, units of both layers x 2^-%d to 2^%d" % (k, k))
+    dens, feats, mlp = _parts()
+    plain = _error(dens, feats, mlp)
+    rng = np.random.default_rng(k)
+    a, b, c = (2.0 ** rng.integers(-k, k + 1, n) for n in (12, 128, 128))
+    w = {name: v.astype(np.float64) for name, v in mlp.items()}
+    w["w0"] = w["w0"] * b[:, None]
+    w["w0"][:, :12] /= a
+    w["w1"] = w["w1"] / b * c[:, None]
+    w["b0"], w["b1"], w["w2"] = w["b0"] * b, w["b1"] * c, w["w2"] / c
+    got = _error(dens, (feats * a).astype(np.float32), {name: v.astype(np.float32) for name, v in w.items()})
+    print("max error %.2e, as it was %.2e" % (got, plain))
+    assert got <= 2 * plain + 2 * ULP
